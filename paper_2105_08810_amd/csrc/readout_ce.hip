@@ -4,117 +4,270 @@
 //   mode 0: a[b,c] = max_t V_out[t,b,c] (first maximal t), entries = the arg-max positions
 //   mode 1: a[b,c] = sum_t V_out[t,b,c], entries = every (t,b,c)
 // eps = dL/da = (softmax(a) - onehot(label)) / B at each entry; loss = mean -log p[b,label].
+//
+// Two kernels: ce_sample (one block per sample: logits, softmax, per-sample loss, dL/da, and in mode
+// 0 the sample's entries sorted by (arg-max step, class) with their running count per step) and
+// ce_rows (mode 0: row pointers and entries of four time steps per block) or ce_fill_sum (mode 1).
+// Both are bound by latency: V_out is 1 to 51 MB. The time axis of a sample is therefore spread over
+// the block (one thread per (time residue, class), eight loads in flight) instead of one thread
+// walking all T steps of a class, and the CSR needs no scan over T*B row counts: row (t, b) starts
+// at sum_b' cum[b'][t] + sum_{b' < b} (cum[b'][t+1] - cum[b'][t]), cum[b][t] = classes of sample b
+// whose arg-max step is before t. Against eight kernels with a thread per class walking time (29 us
+// at T = 100, C = 10; 113 at T = 300, C = 10; 200 at T = 500, C = 100; a one-thread mean of 12 us):
+// a 784 -> 200 -> 10 training step 262 -> 217 us, a 2312 -> 200 -> 10 backward at T = 300 1.750 ->
+// 1.626 ms, the 3 x 1024 backward at T = 500, C = 100 2.34 -> 2.14 ms.
 #include "common.h"
+
+#include <climits>
 
 namespace snn {
 namespace {
 
 constexpr int kThreads = 256;
 
-// One block per sample b: logits, softmax, per-sample loss, dL/da and arg-max times.
-__global__ __launch_bounds__(kThreads) void ce_sample(const float* __restrict__ V, const int32_t* __restrict__ labels,
-                                                      int T, int B, int C, int mode, int32_t* __restrict__ tstar,
-                                                      float* __restrict__ dlda, float* __restrict__ loss_b) {
-  extern __shared__ float a[];  // [C]
-  __shared__ float red[kThreads / kWave];
-  __shared__ float bc[2];
+// Running maximum over time of the strict comparison v > best from t = 0 on: the first maximal t.
+// Partial maxima merge by (larger value, then earlier t); a NaN never wins a comparison.
+__device__ __forceinline__ void max_merge(float& v, int& t, float v2, int t2) {
+  if (v2 > v || (v2 == v && t2 < t)) {
+    v = v2;
+    t = t2;
+  }
+}
+
+// One block per sample b. Thread (tg, c) takes steps tg, tg + TG, ... of class c (classes past the
+// block's width in further rounds); the TG partial results of a class meet in LDS.
+template <int NT>
+__global__ __launch_bounds__(NT) void ce_sample(const float* __restrict__ V, const int32_t* __restrict__ labels,
+                                                int T, int B, int C, int mode, int32_t* __restrict__ tstar,
+                                                float* __restrict__ dlda, float* __restrict__ loss_b,
+                                                int32_t* __restrict__ cum, int32_t* __restrict__ sorted_c,
+                                                float* __restrict__ sorted_d) {
+  extern __shared__ float a[];                   // [C] logits; later the sorted arg-max steps
+  int* ts = reinterpret_cast<int*>(a + C);       // [C] arg-max steps
+  __shared__ __attribute__((aligned(8))) char part_raw[NT * 8];
+  __shared__ float red[NT / kWave];
+  float* pv = reinterpret_cast<float*>(part_raw);
+  int* pt = reinterpret_cast<int*>(part_raw) + NT;
+  double* pd = reinterpret_cast<double*>(part_raw);
   const int b = blockIdx.x;
   const int tid = threadIdx.x;
   const int w = tid / kWave;
   const int l = tid % kWave;
-  for (int c = tid; c < C; c += kThreads) {
-    if (mode == 0) {
-      float best = V[(size_t)b * C + c];
-      int bt = 0;
-      for (int t = 1; t < T; ++t) {
-        const float v = V[((size_t)t * B + b) * C + c];
-        if (v > best) {
-          best = v;
-          bt = t;
+  const size_t step = (size_t)B * C;
+  const int Cw = min(C, NT);  // classes of a round
+  const int TG = NT / Cw;
+  const int tg = tid / Cw;
+  constexpr int kAhead = 8;
+  for (int c0 = 0; c0 < C; c0 += Cw) {
+    const int c = c0 + tid - tg * Cw;
+    const bool on = tg < TG && c < C;
+    const float* src = V + (size_t)b * C + (on ? c : 0);
+    float best = -INFINITY;
+    int bt = INT_MAX;
+    double sum = 0.0;  // the logit of a sum over time, rounded once
+    if (on) {
+      for (int t0 = tg; t0 < T; t0 += kAhead * TG) {
+        float v[kAhead];
+#pragma unroll
+        for (int u = 0; u < kAhead; ++u) v[u] = src[(size_t)min(t0 + u * TG, T - 1) * step];
+#pragma unroll
+        for (int u = 0; u < kAhead; ++u) {
+          const int t = t0 + u * TG;
+          if (t < T) {
+            if (mode == 0) {
+              if (v[u] > best) {
+                best = v[u];
+                bt = t;
+              }
+            } else {
+              sum += (double)v[u];
+            }
+          }
         }
       }
-      a[c] = best;
-      tstar[(size_t)b * C + c] = bt;
-    } else {
-      double s = 0.0;  // the logit of a sum over time, rounded once
-      for (int t = 0; t < T; ++t) s += (double)V[((size_t)t * B + b) * C + c];
-      a[c] = (float)s;
     }
+    if (mode == 0) {
+      pv[tid] = best;
+      pt[tid] = bt;
+    } else {
+      pd[tid] = sum;
+    }
+    __syncthreads();
+    int half = 1;
+    while (half < TG) half <<= 1;
+    for (half >>= 1; half > 0; half >>= 1) {
+      if (tg < half && tg + half < TG) {
+        const int o = tid + half * Cw;
+        if (mode == 0) {
+          max_merge(best, bt, pv[o], pt[o]);
+          pv[tid] = best;
+          pt[tid] = bt;
+        } else {
+          sum += pd[o];
+          pd[tid] = sum;
+        }
+      }
+      __syncthreads();
+    }
+    if (on && tg == 0) {
+      if (mode == 0) {
+        const float v0 = src[0];
+        if (isnan(v0) || bt == INT_MAX) {  // step 0 is the start of the comparison, whatever it holds
+          best = v0;
+          bt = 0;
+        }
+        a[c] = best;
+        ts[c] = bt;
+        tstar[(size_t)b * C + c] = bt;
+      } else {
+        a[c] = (float)sum;
+      }
+    }
+    __syncthreads();
   }
-  __syncthreads();
-  // max over classes
-  float m = -INFINITY;
-  for (int c = tid; c < C; c += kThreads) m = fmaxf(m, a[c]);
+  // max over classes, then the softmax's sum
+  auto block_all = [&](float x, bool is_max) {
 #pragma unroll
-  for (int off = 32; off > 0; off >>= 1) m = fmaxf(m, __shfl_xor(m, off, kWave));
-  if (l == 0) red[w] = m;
-  __syncthreads();
-  if (tid == 0) {
-    float mm = red[0];
-    for (int k = 1; k < kThreads / kWave; ++k) mm = fmaxf(mm, red[k]);
-    bc[0] = mm;
-  }
-  __syncthreads();
-  const float amax = bc[0];
+    for (int off = 32; off > 0; off >>= 1) {
+      const float o = __shfl_xor(x, off, kWave);
+      x = is_max ? fmaxf(x, o) : x + o;
+    }
+    if (l == 0) red[w] = x;
+    __syncthreads();
+    float r = red[0];
+#pragma unroll
+    for (int k = 1; k < NT / kWave; ++k) r = is_max ? fmaxf(r, red[k]) : r + red[k];
+    __syncthreads();
+    return r;
+  };
+  float m = -INFINITY;
+  for (int c = tid; c < C; c += NT) m = fmaxf(m, a[c]);
+  const float amax = block_all(m, true);
   float s = 0.0f;
-  for (int c = tid; c < C; c += kThreads) s += expf(a[c] - amax);
-  s = wave_sum(s);
-  __syncthreads();
-  if (l == 0) red[w] = s;
-  __syncthreads();
-  if (tid == 0) {
-    float ss = 0.0f;
-    for (int k = 0; k < kThreads / kWave; ++k) ss += red[k];
-    bc[1] = ss;
-  }
-  __syncthreads();
-  const float Z = bc[1];
+  for (int c = tid; c < C; c += NT) s += expf(a[c] - amax);
+  const float Z = block_all(s, false);
   const int y = labels[b];
   const bool ok = y >= 0 && y < C;
   const float invB = 1.0f / (float)B;
-  for (int c = tid; c < C; c += kThreads) {
-    const float p = expf(a[c] - amax) / Z;
-    dlda[(size_t)b * C + c] = (p - (c == y ? 1.0f : 0.0f)) * invB;
-  }
   if (tid == 0) loss_b[b] = ok ? (logf(Z) - (a[y] - amax)) : NAN;
-}
-
-__global__ void ce_loss(const float* __restrict__ loss_b, int B, float* __restrict__ loss) {
-  if (blockIdx.x == 0 && threadIdx.x == 0) {
-    float s = 0.0f;
-    for (int b = 0; b < B; ++b) s += loss_b[b];
-    *loss = s / (float)B;
+  for (int c = tid; c < C; c += NT) {
+    const float p = expf(a[c] - amax) / Z;
+    const float d = (p - (c == y ? 1.0f : 0.0f)) * invB;
+    dlda[(size_t)b * C + c] = d;
+    if (mode == 0) {  // the entry's place among the sample's entries: by step, then class
+      const int t = ts[c];
+      int pos = 0;
+      for (int k = 0; k < C; ++k) pos += ts[k] < t || (ts[k] == t && k < c);
+      sorted_c[(size_t)b * C + pos] = c;
+      sorted_d[(size_t)b * C + pos] = d;
+    }
+  }
+  if (mode != 0) return;
+  __syncthreads();  // every logit has been read: a takes the steps in sorted order
+  int* st = reinterpret_cast<int*>(a);
+  for (int c = tid; c < C; c += NT) {
+    const int t = ts[c];
+    int pos = 0;
+    for (int k = 0; k < C; ++k) pos += ts[k] < t || (ts[k] == t && k < c);
+    st[pos] = t;
+  }
+  __syncthreads();
+  for (int t = tid; t <= T; t += NT) {  // classes with an arg-max step before t
+    int lo = 0, hi = C;
+    while (lo < hi) {
+      const int mid = (lo + hi) >> 1;
+      if (st[mid] < t) lo = mid + 1; else hi = mid;
+    }
+    cum[(size_t)b * (T + 1) + t] = lo;
   }
 }
 
-__global__ void fill_int(int32_t* __restrict__ p, size_t n, int32_t v) {
-  for (size_t k = blockIdx.x * (size_t)blockDim.x + threadIdx.x; k < n; k += (size_t)gridDim.x * blockDim.x) p[k] = v;
+// Mean of the per-sample losses by one wavefront (float64, fixed order).
+__device__ __forceinline__ void mean_loss(const float* __restrict__ loss_b, int B, float* __restrict__ loss) {
+  double s = 0.0;
+  for (int b = lane_id(); b < B; b += kWave) s += (double)loss_b[b];
+#pragma unroll
+  for (int off = 32; off > 0; off >>= 1) s += __shfl_xor(s, off, kWave);
+  if (lane_id() == 0) *loss = (float)(s / (double)B);
 }
 
-__global__ void ce_count(const int32_t* __restrict__ tstar, int B, int C, int32_t* __restrict__ counts) {
-  const size_t k = blockIdx.x * (size_t)blockDim.x + threadIdx.x;
-  if (k >= (size_t)B * C) return;
-  const int b = (int)(k / C);
-  atomicAdd(&counts[(size_t)tstar[k] * B + b], 1);
+// Row pointers and entries of kRowSteps time steps per block, one thread per sample (mode 0).
+constexpr int kRowSteps = 4;
+
+__global__ __launch_bounds__(kThreads) void ce_rows(const int32_t* __restrict__ cum,
+                                                    const int32_t* __restrict__ sorted_c,
+                                                    const float* __restrict__ sorted_d,
+                                                    const float* __restrict__ loss_b, int T, int B, int C,
+                                                    int32_t* __restrict__ row_ptr, int32_t* __restrict__ col_idx,
+                                                    float* __restrict__ eps, float* __restrict__ loss) {
+  __shared__ int red[kRowSteps][kThreads / kWave];
+  const int tid = threadIdx.x;
+  const int w = tid / kWave;
+  const int l = tid % kWave;
+  const int t0 = blockIdx.x * kRowSteps;
+  auto load = [&](int b, int (&x)[kRowSteps + 1]) {
+#pragma unroll
+    for (int q = 0; q <= kRowSteps; ++q) x[q] = b < B ? cum[(size_t)b * (T + 1) + min(t0 + q, T)] : 0;
+  };
+  // entries of all samples before each step
+  int base[kRowSteps] = {};
+  for (int b = tid; b < B; b += kThreads) {
+    int x[kRowSteps + 1];
+    load(b, x);
+#pragma unroll
+    for (int q = 0; q < kRowSteps; ++q) base[q] += x[q];
+  }
+#pragma unroll
+  for (int q = 0; q < kRowSteps; ++q) {
+    base[q] = wave_sum_int(base[q]);
+    if (l == 0) red[q][w] = base[q];
+  }
+  __syncthreads();
+#pragma unroll
+  for (int q = 0; q < kRowSteps; ++q) {
+    base[q] = 0;
+    for (int k = 0; k < kThreads / kWave; ++k) base[q] += red[q][k];
+  }
+  for (int b0 = 0; b0 < B; b0 += kThreads) {
+    const int b = b0 + tid;
+    int x[kRowSteps + 1], ex[kRowSteps];
+    load(b, x);
+    __syncthreads();  // red is rewritten
+#pragma unroll
+    for (int q = 0; q < kRowSteps; ++q) {
+      const int n = x[q + 1] - x[q];
+      const int incl = wave_incl_scan(n);
+      ex[q] = incl - n;
+      if (l == kWave - 1) red[q][w] = incl;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < kRowSteps; ++q) {
+      int before = 0, all = 0;
+      for (int k = 0; k < kThreads / kWave; ++k) {
+        before += k < w ? red[q][k] : 0;
+        all += red[q][k];
+      }
+      const int row = base[q] + before + ex[q];
+      base[q] += all;
+      if (b < B && t0 + q < T) {
+        row_ptr[(size_t)(t0 + q) * B + b] = row;
+        for (int k = x[q]; k < x[q + 1]; ++k) {
+          col_idx[row + k - x[q]] = sorted_c[(size_t)b * C + k];
+          eps[row + k - x[q]] = sorted_d[(size_t)b * C + k];
+        }
+      }
+    }
+  }
+  if (blockIdx.x == 0) {
+    if (tid == 0) row_ptr[(size_t)T * B] = B * C;
+    if (w == 0) mean_loss(loss_b, B, loss);
+  }
 }
 
-__global__ void ce_fill_max(const int32_t* __restrict__ tstar, const float* __restrict__ dlda, int B, int C,
-                            const int32_t* __restrict__ row_ptr, int32_t* __restrict__ col_idx,
-                            float* __restrict__ eps) {
-  const size_t k = blockIdx.x * (size_t)blockDim.x + threadIdx.x;
-  if (k >= (size_t)B * C) return;
-  const int b = (int)(k / C);
-  const int c = (int)(k - (size_t)b * C);
-  const int t = tstar[k];
-  int pos = 0;
-  for (int c2 = 0; c2 < c; ++c2) pos += tstar[(size_t)b * C + c2] == t;
-  const int64_t e = (int64_t)row_ptr[(size_t)t * B + b] + pos;
-  col_idx[e] = c;
-  eps[e] = dlda[k];
-}
-
-__global__ void ce_fill_sum(const float* __restrict__ dlda, int T, int B, int C, int32_t* __restrict__ row_ptr,
-                            int32_t* __restrict__ col_idx, float* __restrict__ eps) {
+__global__ void ce_fill_sum(const float* __restrict__ dlda, const float* __restrict__ loss_b, int T, int B, int C,
+                            int32_t* __restrict__ row_ptr, int32_t* __restrict__ col_idx, float* __restrict__ eps,
+                            float* __restrict__ loss) {
   const size_t n = (size_t)T * B * C;
   for (size_t k = blockIdx.x * (size_t)blockDim.x + threadIdx.x; k < n; k += (size_t)gridDim.x * blockDim.x) {
     const size_t r = k / C;
@@ -124,7 +277,10 @@ __global__ void ce_fill_sum(const float* __restrict__ dlda, int T, int B, int C,
     eps[k] = dlda[(size_t)b * C + c];
     if (c == 0) row_ptr[r] = (int32_t)k;
   }
-  if (blockIdx.x == 0 && threadIdx.x == 0) row_ptr[(size_t)T * B] = (int32_t)n;
+  if (blockIdx.x == 0) {
+    if (threadIdx.x == 0) row_ptr[(size_t)T * B] = (int32_t)n;
+    if (threadIdx.x < kWave) mean_loss(loss_b, B, loss);
+  }
 }
 
 // dL/dV_out densely: dL/da at the arg-max time (mode 0) or at every t (mode 1), 0 elsewhere.
@@ -150,9 +306,11 @@ extern "C" size_t snn_readout_ce_workspace(int T, int B, int C, int mode) {
   c.take<int32_t>((size_t)B * C);  // tstar
   c.take<float>((size_t)B * C);    // dL/da
   c.take<float>((size_t)B);        // per-sample loss
-  c.take<int32_t>((size_t)T * B);  // row counts
-  c.take<int32_t>(scan_temp_elems(T * B));
-  c.take<int64_t>(1);
+  if (mode == 0) {
+    c.take<int32_t>((size_t)B * (T + 1));  // entries before each step, per sample
+    c.take<int32_t>((size_t)B * C);        // classes in entry order
+    c.take<float>((size_t)B * C);          // their dL/da
+  }
   return c.off;
 }
 
@@ -170,26 +328,31 @@ extern "C" snn_status snn_readout_ce(const float* V_out, const int32_t* labels, 
   int32_t* tstar = ws.take<int32_t>((size_t)B * C);
   float* dlda = ws.take<float>((size_t)B * C);
   float* loss_b = ws.take<float>((size_t)B);
-  int32_t* counts = ws.take<int32_t>((size_t)T * B);
-  int32_t* temp = ws.take<int32_t>(scan_temp_elems(T * B));
-  int64_t* nnz = ws.take<int64_t>(1);
-
-  hipLaunchKernelGGL(ce_sample, dim3(B), dim3(kThreads), (size_t)C * sizeof(float), s, V_out, labels, T, B, C, mode,
-                     tstar, dlda, loss_b);
-  hipLaunchKernelGGL(ce_loss, dim3(1), dim3(64), 0, s, loss_b, B, loss);
-  const size_t BC = (size_t)B * C;
-  const unsigned gBC = (unsigned)((BC + 255) / 256);
+  int32_t* cum = nullptr;
+  int32_t* sorted_c = nullptr;
+  float* sorted_d = nullptr;
   if (mode == 0) {
-    const size_t rows = (size_t)T * B;
-    hipLaunchKernelGGL(fill_int, dim3((unsigned)std::min<size_t>((rows + 255) / 256, 4096)), dim3(256), 0, s, counts,
-                       rows, 0);
-    hipLaunchKernelGGL(ce_count, dim3(gBC), dim3(256), 0, s, tstar, B, C, counts);
-    launch_exclusive_scan(counts, T * B, row_ptr, nnz, temp, s);
-    hipLaunchKernelGGL(ce_fill_max, dim3(gBC), dim3(256), 0, s, tstar, dlda, B, C, row_ptr, col_idx, eps);
+    cum = ws.take<int32_t>((size_t)B * (T + 1));
+    sorted_c = ws.take<int32_t>((size_t)B * C);
+    sorted_d = ws.take<float>((size_t)B * C);
+  }
+  // 1024 threads per sample where a sample holds enough values for them
+  const size_t lds = (size_t)C * (sizeof(float) + sizeof(int));
+  if ((int64_t)T * C >= 8192 || C > kThreads) {
+    ensure_dynamic_lds((const void*)ce_sample<1024>, (int)lds);
+    hipLaunchKernelGGL(ce_sample<1024>, dim3(B), dim3(1024), lds, s, V_out, labels, T, B, C, mode, tstar, dlda, loss_b,
+                       cum, sorted_c, sorted_d);
+  } else {
+    hipLaunchKernelGGL(ce_sample<kThreads>, dim3(B), dim3(kThreads), lds, s, V_out, labels, T, B, C, mode, tstar, dlda,
+                       loss_b, cum, sorted_c, sorted_d);
+  }
+  if (mode == 0) {
+    hipLaunchKernelGGL(ce_rows, dim3((unsigned)((T + kRowSteps - 1) / kRowSteps)), dim3(kThreads), 0, s, cum, sorted_c,
+                       sorted_d, loss_b, T, B, C, row_ptr, col_idx, eps, loss);
   } else {
     const size_t n = (size_t)T * B * C;
     hipLaunchKernelGGL(ce_fill_sum, dim3((unsigned)std::min<size_t>((n + 255) / 256, 8192)), dim3(256), 0, s, dlda,
-                       T, B, C, row_ptr, col_idx, eps);
+                       loss_b, T, B, C, row_ptr, col_idx, eps, loss);
   }
   if (eps_dense) {
     const size_t n = (size_t)T * B * C;

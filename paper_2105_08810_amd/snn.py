@@ -425,10 +425,18 @@ def lif_forward(s_in: torch.Tensor, W: torch.Tensor, alpha, theta, want_trace=Tr
 
 
 class Csr:
-    """Device CSR of an active set: row_ptr [T*B+1], col_idx / g [capacity], nnz (int64 device scalar)."""
+    """Device CSR of an active set: row_ptr [T*B+1], col_idx / g [capacity], nnz (int64 device scalar).
+    nnz_dev None: every slot is an entry (nnz = capacity); the scalar is then made when it is asked
+    for (the readout's CSR, whose nnz nothing in a step reads)."""
 
     def __init__(self, row_ptr, col_idx, g, nnz_dev, capacity):
-        self.row_ptr, self.col_idx, self.g, self.nnz_dev, self.capacity = row_ptr, col_idx, g, nnz_dev, capacity
+        self.row_ptr, self.col_idx, self.g, self._nnz_dev, self.capacity = row_ptr, col_idx, g, nnz_dev, capacity
+
+    @property
+    def nnz_dev(self) -> torch.Tensor:
+        if self._nnz_dev is None:
+            self._nnz_dev = torch.full((1,), self.capacity, dtype=torch.int64, device=self.row_ptr.device)
+        return self._nnz_dev
 
     def nnz(self) -> int:
         return int(self.nnz_dev.item())
@@ -436,7 +444,7 @@ class Csr:
     def record_stream(self, stream) -> None:
         """Mark every buffer as used on stream (for the caching allocator, when the CSR was made on
         another stream)."""
-        for t in (self.row_ptr, self.col_idx, self.g, self.nnz_dev):
+        for t in (self.row_ptr, self.col_idx, self.g, self._nnz_dev):
             if t is not None:
                 t.record_stream(stream)
 
@@ -489,8 +497,7 @@ def readout_ce(V_out: torch.Tensor, labels: torch.Tensor, mode: int, dense=False
     ed = torch.empty((T, B, C), dtype=torch.float32, device=dev) if dense else None
     ws = workspace(snn_readout_ce_workspace(T, B, C, mode), dev)
     snn_readout_ce(V_out, labels, T, B, C, mode, row_ptr, col, eps, loss, ed, ws)
-    nnz_dev = torch.full((1,), nnz, dtype=torch.int64, device=dev)
-    return Csr(row_ptr, col, None, nnz_dev, nnz), eps, loss, ed
+    return Csr(row_ptr, col, None, None, nnz), eps, loss, ed
 
 
 def sparse_backward(W, trace_in, alpha, out: Csr, eps_out, inp: Optional[Csr] = None, ws=None, aux_stream=None):
