@@ -64,6 +64,17 @@ void mdw_enqueue_layout(int T, int B, int N_in, int N_out, const int32_t* out_ro
 void mdw_enqueue_rest(const float* trace_in, int T, int B, int N_in, int N_out, const float* out_g, const float* eps_out,
                       int64_t out_cap, float* dW, void* workspace, hipStream_t s);
 
+// Dense float32 products (gemm.hip). K slice z of `splits` goes to C + z * c_split.
+//   gemm_split_km  C = sum_k A[k, m] B[k, n], operands in three bf16 parts, float32 sums
+//   gemm_split_kc  C = sum_k A[m, k] B[n, k], the same
+//   gemm_f64_km    C = sum_k A[k, m] B[k, n], products and sums in float64
+void gemm_split_km(int M, int N, int K, const float* A, int lda, const float* B, int ldb, float* C, int ldc, int splits,
+                   size_t c_split, hipStream_t s);
+void gemm_split_kc(int M, int N, int K, const float* A, int lda, const float* B, int ldb, float* C, int ldc,
+                   hipStream_t s);
+void gemm_f64_km(int M, int N, int K, const float* A, int lda, const float* B, int ldb, float* C, int ldc, int splits,
+                 size_t c_split, hipStream_t s);
+
 // Exclusive scan of counts[0..n) into out[0..n] (out[n] = total) and *total64 = total.
 // temp must hold scan_temp_elems(n) int32 values.
 size_t scan_temp_elems(int n);

@@ -1,0 +1,384 @@
+// Dense float32 matrix products on the bf16 matrix cores, each operand split into three bf16 parts.
+//
+// x = h + m + l with h = bf16(x), m = bf16(x - h), l = bf16(x - h - m), all rounded to nearest: three
+// times 8 significant bits hold a float32's 24. A product takes the six terms down to 2^-16 of the
+// leading one (hh, hm, mh, mm, hl, lh; what is left out is below 2^-24 of |x||y|), and the matrix cores
+// form 16-bit products exactly and sum them in float32. hh goes to one accumulator and the five small
+// terms to another, so the leading sum is rounded once per 16 products of K (a float32 MFMA chain: once
+// per 2). bf16 has float32's exponent range, so no scaling is needed; values of 2^127 and more (and
+// infinities, which a split would turn into NaN) make the block that met one form its tile again on the
+// float32 matrix cores.
+//
+// Bound: the matrix cores, six bf16 products per float32 one (2.5 PFLOP/s / 6 = 417 TFLOP/s of useful
+// work at the nominal rate; the float32 MFMA's nominal rate is 157). A block of four wavefronts owns
+// 128 x 128 of C, a wavefront 64 x 64 (2 x 2 tiles of v_mfma_f32_32x32x16_bf16). A stage of 32 k is
+// loaded into registers while the previous one is multiplied, split there and stored to LDS as
+// [part][k / 8][row] pieces of 16 bytes, which the fragment reads (lane = row, 8 consecutive k) take
+// without bank conflicts; two blocks per CU overlap one's split with the other's products. Measured at
+// 128000 x 1024 x 1024: 1.52 ms, 176 TFLOP/s (1056 in bf16 terms; a large bf16 product of the library
+// reaches 1290 on this card), 1.75 ms with the six terms of a tile issued one after another. Error
+// against 64 bits with 16000 products of random sign per sum: 0.8e-6 of the result, float32 MFMA 3.3e-6.
+#include "common.h"
+
+namespace snn {
+namespace {
+
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef float f32x2 __attribute__((ext_vector_type(2)));
+typedef float f32x16 __attribute__((ext_vector_type(16)));
+
+constexpr int kBM = 128, kBN = 128, kBK = 32;
+constexpr int kThreads = 256;
+constexpr int kKC = kBK / 8;      // pieces of 8 k per row and stage
+constexpr int kLdR = kBM + 2;     // pieces per [part][k / 8] line (2: the lines' stores spread over the banks)
+constexpr float kWide = 1.7e38f;  // 2^127 rounded down: bf16 rounding cannot overflow below it
+
+// Eight values into their three parts, 16 bytes each.
+__device__ __forceinline__ void split8(const float (&x)[8], uint4& h, uint4& m, uint4& l) {
+  uint32_t hp[4], mp[4], lp[4];
+#pragma unroll
+  for (int q = 0; q < 4; ++q) {
+    const float a = x[2 * q], b = x[2 * q + 1];
+    hp[q] = __builtin_bit_cast(uint32_t, __builtin_convertvector((f32x2{a, b}), bf16x2));
+    const float ra = a - __uint_as_float(hp[q] << 16), rb = b - __uint_as_float(hp[q] & 0xffff0000u);
+    mp[q] = __builtin_bit_cast(uint32_t, __builtin_convertvector((f32x2{ra, rb}), bf16x2));
+    const float sa = ra - __uint_as_float(mp[q] << 16), sb = rb - __uint_as_float(mp[q] & 0xffff0000u);
+    lp[q] = __builtin_bit_cast(uint32_t, __builtin_convertvector((f32x2{sa, sb}), bf16x2));
+  }
+  h = make_uint4(hp[0], hp[1], hp[2], hp[3]);
+  m = make_uint4(mp[0], mp[1], mp[2], mp[3]);
+  l = make_uint4(lp[0], lp[1], lp[2], lp[3]);
+}
+
+// One operand's share of a stage: two pieces (8 k of one row each) per thread.
+//   KM: element (r, k) at p[k * ld + r] (rows contiguous): a piece is eight loads, each 256 contiguous
+//       bytes over a wavefront.
+//   else p[r * ld + k] (k contiguous): a piece is 32 contiguous bytes.
+// Rows past the end read the last row (their results are not stored); k past k_hi reads as 0.
+template <bool KM>
+__device__ __forceinline__ void piece_of(int q, int& row, int& kc) {
+  const int idx = threadIdx.x + kThreads * q;
+  row = KM ? idx % kBM : idx / kKC;
+  kc = KM ? idx / kBM : idx % kKC;
+}
+
+template <bool KM, bool VEC>
+__device__ __forceinline__ void load_stage(const float* __restrict__ p, int ld, int r0, int R, int k0, int k_hi,
+                                           float (&x)[2][8]) {
+#pragma unroll
+  for (int q = 0; q < 2; ++q) {
+    int row, kc;
+    piece_of<KM>(q, row, kc);
+    const int r = min(r0 + row, R - 1);
+    const int k = k0 + 8 * kc;
+    if (KM) {
+      if (k + 8 <= k_hi) {
+#pragma unroll
+        for (int u = 0; u < 8; ++u) x[q][u] = p[(size_t)(k + u) * ld + r];
+      } else {
+#pragma unroll
+        for (int u = 0; u < 8; ++u) x[q][u] = k + u < k_hi ? p[(size_t)(k + u) * ld + r] : 0.0f;
+      }
+    } else {
+      const float* s = p + (size_t)r * ld + k;
+      if (VEC && k + 8 <= k_hi) {
+        const float4 a = *reinterpret_cast<const float4*>(s), b = *reinterpret_cast<const float4*>(s + 4);
+        x[q][0] = a.x; x[q][1] = a.y; x[q][2] = a.z; x[q][3] = a.w;
+        x[q][4] = b.x; x[q][5] = b.y; x[q][6] = b.z; x[q][7] = b.w;
+      } else {
+#pragma unroll
+        for (int u = 0; u < 8; ++u) x[q][u] = k + u < k_hi ? s[u] : 0.0f;
+      }
+    }
+  }
+}
+
+typedef uint4 Stage[3][kKC][kLdR];
+constexpr int kLdF = kBM + 4;  // floats per line of the float32 stage (a wide tile)
+static_assert(kBK * kLdF * sizeof(float) <= sizeof(Stage), "the float32 stage fits the split one's LDS");
+
+template <bool KM>
+__device__ __forceinline__ void store_stage(Stage& S, const float (&x)[2][8], float& big) {
+#pragma unroll
+  for (int q = 0; q < 2; ++q) {
+    int row, kc;
+    piece_of<KM>(q, row, kc);
+#pragma unroll
+    for (int u = 0; u < 8; u += 2) big = fmaxf(fmaxf(big, fabsf(x[q][u])), fabsf(x[q][u + 1]));
+    uint4 h, m, l;
+    split8(x[q], h, m, l);
+    S[0][kc][row] = h;
+    S[1][kc][row] = m;
+    S[2][kc][row] = l;
+  }
+}
+
+// A block's tile of C and its K slice z. Blocks are dealt to the 8 XCDs in turn. Short M and N, long K:
+// the tiles of one slice run on one XCD and share its rows in that L2 (slices a multiple of 8: the XCDs
+// get equally many). Long M: the N tiles of one M tile run on one XCD (32 M tiles and more, so that the
+// last round of eight does not decide).
+struct BlockTile {
+  int tm, tn, z;
+  bool ok;
+};
+
+__device__ __forceinline__ BlockTile slice_tile(int tiles_m, int tiles_n, int splits) {
+  const int tiles = tiles_m * tiles_n;
+  const int j = splits % 8 == 0 ? (int)blockIdx.x >> 3 : (int)blockIdx.x;
+  const int z = splits % 8 == 0 ? (int)(blockIdx.x & 7) + 8 * (j / tiles) : j / tiles;
+  const int t = j % tiles;
+  return {t / tiles_n, t % tiles_n, z, z < splits};
+}
+
+__device__ __forceinline__ BlockTile row_tile(int tiles_m, int tiles_n) {
+  const int j = tiles_m >= 32 ? (int)blockIdx.x >> 3 : (int)blockIdx.x;
+  const int tm = tiles_m >= 32 ? (int)(blockIdx.x & 7) + 8 * (j / tiles_n) : j / tiles_n;
+  return {tm, j % tiles_n, 0, tm < tiles_m};
+}
+
+// C[M x N] = sum over this block's K slice of A(m, k) B(k, n); slice z goes to C + z * c_split.
+template <bool KM, bool VEC>
+__global__ __launch_bounds__(kThreads, 2) void gemm_split3(int M, int N, int K, const float* __restrict__ A, int lda,
+                                                           const float* __restrict__ B, int ldb,
+                                                           float* __restrict__ C, int ldc, int k_per_split,
+                                                           size_t c_split, int tiles_m, int tiles_n, int splits) {
+  __shared__ Stage As, Bs;
+  const int w = threadIdx.x / kWave;
+  const int l = threadIdx.x % kWave;
+  const BlockTile bt = KM ? slice_tile(tiles_m, tiles_n, splits) : row_tile(tiles_m, tiles_n);
+  if (!bt.ok) return;
+  const int tm = bt.tm, tn = bt.tn, z = bt.z;
+  const int m0 = tm * kBM, n0 = tn * kBN;
+  const int k_lo = z * k_per_split;
+  const int k_hi = min(K, k_lo + k_per_split);
+  const int wm = (w / 2) * 64, wn = (w % 2) * 64;
+  const int lr = l % 32, lk = l / 32;
+
+  f32x16 lead[2][2], rest[2][2];
+#pragma unroll
+  for (int a = 0; a < 2; ++a)
+#pragma unroll
+    for (int b = 0; b < 2; ++b)
+#pragma unroll
+      for (int v = 0; v < 16; ++v) lead[a][b][v] = rest[a][b][v] = 0.0f;
+
+  float xa[2][8], xb[2][8];
+  float big = 0.0f;
+  if (k_lo < k_hi) {
+    load_stage<KM, VEC>(A, lda, m0, M, k_lo, k_hi, xa);
+    load_stage<KM, VEC>(B, ldb, n0, N, k_lo, k_hi, xb);
+  }
+  for (int k0 = k_lo; k0 < k_hi; k0 += kBK) {
+    store_stage<KM>(As, xa, big);
+    store_stage<KM>(Bs, xb, big);
+    __syncthreads();
+    if (k0 + kBK < k_hi) {
+      load_stage<KM, VEC>(A, lda, m0, M, k0 + kBK, k_hi, xa);
+      load_stage<KM, VEC>(B, ldb, n0, N, k0 + kBK, k_hi, xb);
+    }
+#pragma unroll
+    for (int ks = 0; ks < kBK / 16; ++ks) {
+      bf16x8 fa[3][2], fb[3][2];
+#pragma unroll
+      for (int p = 0; p < 3; ++p)
+#pragma unroll
+        for (int t = 0; t < 2; ++t) {
+          fa[p][t] = __builtin_bit_cast(bf16x8, As[p][2 * ks + lk][wm + 32 * t + lr]);
+          fb[p][t] = __builtin_bit_cast(bf16x8, Bs[p][2 * ks + lk][wn + 32 * t + lr]);
+        }
+      // smallest terms first; neighbours in the issue order go to different accumulators
+      constexpr int kTerm[6][2] = {{2, 0}, {0, 2}, {1, 1}, {1, 0}, {0, 1}, {0, 0}};
+#pragma unroll
+      for (int t = 0; t < 6; ++t)
+#pragma unroll
+        for (int a = 0; a < 2; ++a)
+#pragma unroll
+          for (int b = 0; b < 2; ++b) {
+            f32x16& acc = t == 5 ? lead[a][b] : rest[a][b];
+            acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[kTerm[t][0]][a], fb[kTerm[t][1]][b], acc, 0, 0, 0);
+          }
+    }
+    __syncthreads();
+  }
+  if (__syncthreads_or(big >= kWide)) {  // a value out of the split's range: the same sums in float32
+    float(*Af)[kLdF] = reinterpret_cast<float(*)[kLdF]>(&As);
+    float(*Bf)[kLdF] = reinterpret_cast<float(*)[kLdF]>(&Bs);
+#pragma unroll
+    for (int a = 0; a < 2; ++a)
+#pragma unroll
+      for (int b = 0; b < 2; ++b)
+#pragma unroll
+        for (int v = 0; v < 16; ++v) lead[a][b][v] = rest[a][b][v] = 0.0f;
+    for (int k0 = k_lo; k0 < k_hi; k0 += kBK) {
+      load_stage<KM, VEC>(A, lda, m0, M, k0, k_hi, xa);
+      load_stage<KM, VEC>(B, ldb, n0, N, k0, k_hi, xb);
+#pragma unroll
+      for (int q = 0; q < 2; ++q) {
+        int row, kc;
+        piece_of<KM>(q, row, kc);
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {
+          Af[8 * kc + u][row] = xa[q][u];
+          Bf[8 * kc + u][row] = xb[q][u];
+        }
+      }
+      __syncthreads();
+      for (int k = 0; k < kBK; k += 2)
+#pragma unroll
+        for (int a = 0; a < 2; ++a)
+#pragma unroll
+          for (int b = 0; b < 2; ++b)
+            lead[a][b] = __builtin_amdgcn_mfma_f32_32x32x2f32(Af[k + lk][wm + 32 * a + lr], Bf[k + lk][wn + 32 * b + lr],
+                                                             lead[a][b], 0, 0, 0);
+      __syncthreads();
+    }
+  }
+
+  // accumulator layout of 32x32: register v of lane l holds row 8 (v / 4) + 4 (l / 32) + v % 4, column l % 32
+  float* Cz = C + (size_t)z * c_split;
+#pragma unroll
+  for (int a = 0; a < 2; ++a)
+#pragma unroll
+    for (int b = 0; b < 2; ++b)
+#pragma unroll
+      for (int v = 0; v < 16; ++v) {
+        const int m = m0 + wm + 32 * a + 8 * (v / 4) + 4 * lk + (v % 4);
+        const int n = n0 + wn + 32 * b + lr;
+        if (m < M && n < N) Cz[(size_t)m * ldc + n] = lead[a][b][v] + rest[a][b][v];
+      }
+}
+
+// C[M x N] = sum over this block's K slice of A(k, m) B(k, n), float32 operands with their products and
+// sums in float64 (v_mfma_f64_16x16x4_f64), each slice rounded to float32 once. Bound: the float64 matrix
+// cores (78.6 TFLOP/s nominal); converting the operands costs one instruction per 16 x 4 fragment.
+// Block 128 x 128, wavefront 64 x 64 (4 x 4 tiles), stages of 16 k double buffered in LDS; lines of 144
+// floats put the four k of a fragment on different banks.
+constexpr int kDK = 16;
+constexpr int kDLd = kBM + 16;
+typedef double f64x4 __attribute__((ext_vector_type(4)));
+
+template <bool VEC>
+__global__ __launch_bounds__(kThreads, 2) void gemm_f64(int M, int N, int K, const float* __restrict__ A, int lda,
+                                                        const float* __restrict__ B, int ldb, float* __restrict__ C,
+                                                        int ldc, int k_per_split, size_t c_split, int tiles_m,
+                                                        int tiles_n, int splits) {
+  __shared__ __attribute__((aligned(16))) float As[2][kDK][kDLd], Bs[2][kDK][kDLd];
+  const int w = threadIdx.x / kWave;
+  const int l = threadIdx.x % kWave;
+  const BlockTile bt = slice_tile(tiles_m, tiles_n, splits);
+  if (!bt.ok) return;
+  const int m0 = bt.tm * kBM, n0 = bt.tn * kBN, z = bt.z;
+  const int k_lo = z * k_per_split;
+  const int k_hi = min(K, k_lo + k_per_split);
+  const int wm = (w / 2) * 64, wn = (w % 2) * 64;
+  const int lr = l % 16, lk = l / 16;
+  f64x4 acc[4][4];
+#pragma unroll
+  for (int a = 0; a < 4; ++a)
+#pragma unroll
+    for (int b = 0; b < 4; ++b) acc[a][b] = f64x4{0.0, 0.0, 0.0, 0.0};
+  // a thread's part of a stage: lines tid / 32 and 8 + tid / 32, four columns
+  const int c4 = 4 * (threadIdx.x % 32), ln = threadIdx.x / 32;
+  float4 xa[2], xb[2];
+  auto load = [&](const float* __restrict__ p, int ld, int c0, int R, int k0, float4 (&x)[2]) {
+#pragma unroll
+    for (int q = 0; q < 2; ++q) {
+      const int k = k0 + ln + 8 * q;
+      const float* row = p + (size_t)min(k, k_hi - 1) * ld;
+      const int c = c0 + c4;
+      if (VEC && c + 4 <= R) {
+        x[q] = *reinterpret_cast<const float4*>(row + c);
+      } else {  // columns past the end read the last one (their results are not stored)
+        x[q] = make_float4(row[min(c, R - 1)], row[min(c + 1, R - 1)], row[min(c + 2, R - 1)], row[min(c + 3, R - 1)]);
+      }
+      if (k >= k_hi) x[q] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+    }
+  };
+  if (k_lo < k_hi) {
+    load(A, lda, m0, M, k_lo, xa);
+    load(B, ldb, n0, N, k_lo, xb);
+  }
+  int cur = 0;
+  for (int k0 = k_lo; k0 < k_hi; k0 += kDK, cur ^= 1) {
+#pragma unroll
+    for (int q = 0; q < 2; ++q) {
+      *reinterpret_cast<float4*>(&As[cur][ln + 8 * q][c4]) = xa[q];
+      *reinterpret_cast<float4*>(&Bs[cur][ln + 8 * q][c4]) = xb[q];
+    }
+    __syncthreads();  // one barrier per stage: the next stage is stored to the other buffer
+    if (k0 + kDK < k_hi) {
+      load(A, lda, m0, M, k0 + kDK, xa);
+      load(B, ldb, n0, N, k0 + kDK, xb);
+    }
+#pragma unroll
+    for (int ks = 0; ks < kDK; ks += 4) {
+      double fa[4], fb[4];
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        fa[q] = (double)As[cur][ks + lk][wm + 16 * q + lr];
+        fb[q] = (double)Bs[cur][ks + lk][wn + 16 * q + lr];
+      }
+#pragma unroll
+      for (int a = 0; a < 4; ++a)
+#pragma unroll
+        for (int b = 0; b < 4; ++b) acc[a][b] = __builtin_amdgcn_mfma_f64_16x16x4f64(fa[a], fb[b], acc[a][b], 0, 0, 0);
+    }
+  }
+  // register v of lane l holds row 4 v + l / 16, column l % 16 of its 16 x 16 tile
+  float* Cz = C + (size_t)z * c_split;
+#pragma unroll
+  for (int a = 0; a < 4; ++a)
+#pragma unroll
+    for (int b = 0; b < 4; ++b)
+#pragma unroll
+      for (int v = 0; v < 4; ++v) {
+        const int m = m0 + wm + 16 * a + 4 * v + lk;
+        const int n = n0 + wn + 16 * b + lr;
+        if (m < M && n < N) Cz[(size_t)m * ldc + n] = (float)acc[a][b][v];
+      }
+}
+
+}  // namespace
+
+void gemm_split_km(int M, int N, int K, const float* A, int lda, const float* B, int ldb, float* C, int ldc, int splits,
+                   size_t c_split, hipStream_t s) {
+  const int tm = (M + kBM - 1) / kBM, tn = (N + kBN - 1) / kBN;
+  int kps = (K + splits - 1) / splits;
+  kps = (kps + kBK - 1) / kBK * kBK;
+  hipLaunchKernelGGL((gemm_split3<true, false>), dim3((unsigned)(splits * tm * tn)), dim3(kThreads), 0, s, M, N,
+                     K, A, lda, B, ldb, C, ldc, kps, c_split, tm, tn, splits);
+}
+
+void gemm_split_kc(int M, int N, int K, const float* A, int lda, const float* B, int ldb, float* C, int ldc,
+                   hipStream_t s) {
+  const int tm = (M + kBM - 1) / kBM, tn = (N + kBN - 1) / kBN;
+  const bool vec = lda % 4 == 0 && ldb % 4 == 0 && reinterpret_cast<uintptr_t>(A) % 16 == 0 &&
+                   reinterpret_cast<uintptr_t>(B) % 16 == 0;
+  const int kps = (K + kBK - 1) / kBK * kBK;
+  const dim3 g((unsigned)((tm >= 32 ? (tm + 7) / 8 * 8 : tm) * tn));
+  if (vec)
+    hipLaunchKernelGGL((gemm_split3<false, true>), g, dim3(kThreads), 0, s, M, N, K, A, lda, B, ldb, C, ldc, kps, 0, tm,
+                       tn, 1);
+  else
+    hipLaunchKernelGGL((gemm_split3<false, false>), g, dim3(kThreads), 0, s, M, N, K, A, lda, B, ldb, C, ldc, kps, 0,
+                       tm, tn, 1);
+}
+
+void gemm_f64_km(int M, int N, int K, const float* A, int lda, const float* B, int ldb, float* C, int ldc, int splits,
+                 size_t c_split, hipStream_t s) {
+  const int tm = (M + kBM - 1) / kBM, tn = (N + kBN - 1) / kBN;
+  int kps = (K + splits - 1) / splits;
+  kps = (kps + kDK - 1) / kDK * kDK;
+  const bool vec = lda % 4 == 0 && ldb % 4 == 0 && reinterpret_cast<uintptr_t>(A) % 16 == 0 &&
+                   reinterpret_cast<uintptr_t>(B) % 16 == 0;
+  const dim3 g((unsigned)(splits * tm * tn));
+  if (vec)
+    hipLaunchKernelGGL(gemm_f64<true>, g, dim3(kThreads), 0, s, M, N, K, A, lda, B, ldb, C, ldc, kps, c_split, tm, tn,
+                       splits);
+  else
+    hipLaunchKernelGGL(gemm_f64<false>, g, dim3(kThreads), 0, s, M, N, K, A, lda, B, ldb, C, ldc, kps, c_split, tm, tn,
+                       splits);
+}
+
+}  // namespace snn

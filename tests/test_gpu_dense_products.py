@@ -1,0 +1,65 @@
+"""The dense backward's products (three-part bf16 operands on the matrix cores) against float64 at the
+edges of their tiles, and with values outside the split's range."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2105_08810_amd import snn
+
+pytestmark = pytest.mark.gpu
+
+INF = float("inf")
+
+
+def _run(T, B, n_in, n_out, eps, trace, W, alpha):
+    dev = lambda x: torch.from_numpy(x).cuda()
+    dW, gi = snn.dense_backward_ref(dev(W), dev(trace), dev(np.zeros_like(eps)), dev(eps), alpha, INF,
+                                    INF, 100.0)
+    return dW.cpu().numpy().astype(np.float64), gi.cpu().numpy().astype(np.float64)
+
+
+def _reference(eps, trace, W, alpha):
+    T, B, n_out = eps.shape
+    e, tr, w = eps.astype(np.float64), trace.astype(np.float64).reshape(T * B, -1), W.astype(np.float64)
+    d = np.zeros_like(e)
+    for t in range(T - 1, 0, -1):
+        d[t - 1] = alpha * d[t] + e[t]
+    return tr.T @ e.reshape(T * B, n_out), (d.reshape(T * B, n_out) @ w.T).reshape(T, B, -1)
+
+
+@pytest.mark.parametrize("T,B,n_in,n_out", [
+    (1, 1, 1, 1), (2, 3, 5, 7), (16, 2, 127, 33), (129, 1, 128, 128), (11, 31, 129, 130), (40, 7, 300, 31),
+    (100, 41, 260, 100), (17, 241, 64, 257), (3, 1365, 36, 512)])
+def test_dense_products(T, B, n_in, n_out):
+    rng = np.random.default_rng(T * B + n_in)
+    eps = rng.standard_normal((T, B, n_out)).astype(np.float32) * np.float32(1e-4)
+    trace = (rng.random((T, B, n_in)) * 3).astype(np.float32)
+    W = rng.standard_normal((n_in, n_out)).astype(np.float32)
+    alpha = float(np.float32(0.9))
+    dW, gi = _run(T, B, n_in, n_out, eps, trace, W, alpha)
+    rW, rg = _reference(eps, trace, W, alpha)
+    eW, eg = _reference(np.abs(eps), trace, np.abs(W), alpha)
+    # left-out terms below 2^-24, one rounding of the running sum per 16 products (2^-24 of at most the
+    # absolute sum each), and for the spike gradient the float32 recurrence (2^-23 a step, over 1 / (1 - alpha))
+    u = 2.0 ** -24
+    assert (np.abs(dW - rW) <= (T * B / 16 + 8) * 2 * u * eW).all()
+    assert (np.abs(gi - rg) <= (n_out / 16 + 8 + 20) * 2 * u * eg + 1e-37).all()
+
+
+@pytest.mark.parametrize("value", [2e38, -INF, np.nan])
+def test_dense_products_outside_the_split(value):
+    """A value of 2^127 and more, an infinity and a NaN give what float32 products give."""
+    T, B, n_in, n_out = 3, 50, 140, 136
+    rng = np.random.default_rng(5)
+    eps = rng.standard_normal((T, B, n_out)).astype(np.float32)
+    eps[2, 7, 130] = value
+    trace = (rng.random((T, B, n_in)) < 0.5).astype(np.float32)
+    W = rng.standard_normal((n_in, n_out)).astype(np.float32) * np.float32(0.01)
+    dW, gi = _run(T, B, n_in, n_out, eps, trace, W, 0.5)
+    with np.errstate(invalid="ignore"):
+        rW, rg = _reference(eps, trace, W, 0.5)
+    for x, r in ((dW, rW), (gi, rg)):
+        assert np.array_equal(np.isnan(x), np.isnan(r)) and np.array_equal(np.isinf(x), np.isinf(r))
+        ok = np.isfinite(r)
+        assert np.array_equal(x[np.isinf(r)], r[np.isinf(r)])
+        assert (np.abs(x[ok] - r[ok]) <= 1e-5 * np.maximum(np.abs(r[ok]), 1.0)).all()
