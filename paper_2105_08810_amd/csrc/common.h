@@ -64,6 +64,22 @@ void mdw_enqueue_layout(int T, int B, int N_in, int N_out, const int32_t* out_ro
 void mdw_enqueue_rest(const float* trace_in, int T, int B, int N_in, int N_out, const float* out_g, const float* eps_out,
                       int64_t out_cap, float* dW, void* workspace, hipStream_t s);
 
+// Device-side choice between two ways to do a call's work, both enqueued: a kernel with a gate runs iff the
+// CSR holds at least `least` entries (or, with below, fewer). end NULL: it always runs. The entry arrays'
+// allocated length is only an upper bound of the entries, and reading the count back would wait for the GPU.
+struct Gate {
+  const int32_t* end = nullptr;  // row_ptr[T * B]
+  int64_t cap = 0;               // allocated entries
+  int64_t least = 0;
+  bool below = false;
+};
+
+__device__ __forceinline__ bool gate_open(const Gate& g) {
+  if (!g.end) return true;
+  const int64_t n = *g.end;
+  return ((n > g.cap ? g.cap : n) >= g.least) != g.below;
+}
+
 // Dense float32 products (gemm.hip). K slice z of `splits` goes to C + z * c_split.
 //   gemm_split_km  C = sum_k A[k, m] B[k, n], operands in three bf16 parts, float32 sums
 //   gemm_split_kc  C = sum_k A[m, k] B[n, k], the same
@@ -73,13 +89,13 @@ void gemm_split_km(int M, int N, int K, const float* A, int lda, const float* B,
 void gemm_split_kc(int M, int N, int K, const float* A, int lda, const float* B, int ldb, float* C, int ldc,
                    hipStream_t s);
 void gemm_f64_km(int M, int N, int K, const float* A, int lda, const float* B, int ldb, float* C, int ldc, int splits,
-                 size_t c_split, hipStream_t s);
+                 size_t c_split, const Gate& gate, hipStream_t s);
 
 // Exclusive scan of counts[0..n) into out[0..n] (out[n] = total) and *total64 = total.
 // temp must hold scan_temp_elems(n) int32 values.
 size_t scan_temp_elems(int n);
 void launch_exclusive_scan(const int32_t* counts, int n, int32_t* out, int64_t* total64, int32_t* temp,
-                           hipStream_t stream);
+                           hipStream_t stream, const Gate& gate = Gate{});
 
 // ------------------------------------------------------------------ device helpers
 

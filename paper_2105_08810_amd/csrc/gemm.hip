@@ -251,7 +251,8 @@ __global__ __launch_bounds__(kThreads, 2) void gemm_split3(int M, int N, int K, 
 
 // C[M x N] = sum over this block's K slice of A(k, m) B(k, n), float32 operands with their products and
 // sums in float64 (v_mfma_f64_16x16x4_f64), each slice rounded to float32 once. Bound: the float64 matrix
-// cores (78.6 TFLOP/s nominal); converting the operands costs one instruction per 16 x 4 fragment.
+// cores (78.6 TFLOP/s nominal; 1024 x 1024 x 128000 takes 4.23 ms, 63 TFLOP/s, the library's 4096^3 product
+// 68); converting the operands costs one instruction per 16 x 4 fragment.
 // Block 128 x 128, wavefront 64 x 64 (4 x 4 tiles), stages of 16 k double buffered in LDS; lines of 144
 // floats put the four k of a fragment on different banks.
 constexpr int kDK = 16;
@@ -262,7 +263,8 @@ template <bool VEC>
 __global__ __launch_bounds__(kThreads, 2) void gemm_f64(int M, int N, int K, const float* __restrict__ A, int lda,
                                                         const float* __restrict__ B, int ldb, float* __restrict__ C,
                                                         int ldc, int k_per_split, size_t c_split, int tiles_m,
-                                                        int tiles_n, int splits) {
+                                                        int tiles_n, int splits, Gate gate) {
+  if (!gate_open(gate)) return;
   __shared__ __attribute__((aligned(16))) float As[2][kDK][kDLd], Bs[2][kDK][kDLd];
   const int w = threadIdx.x / kWave;
   const int l = threadIdx.x % kWave;
@@ -366,7 +368,7 @@ void gemm_split_kc(int M, int N, int K, const float* A, int lda, const float* B,
 }
 
 void gemm_f64_km(int M, int N, int K, const float* A, int lda, const float* B, int ldb, float* C, int ldc, int splits,
-                 size_t c_split, hipStream_t s) {
+                 size_t c_split, const Gate& gate, hipStream_t s) {
   const int tm = (M + kBM - 1) / kBM, tn = (N + kBN - 1) / kBN;
   int kps = (K + splits - 1) / splits;
   kps = (kps + kDK - 1) / kDK * kDK;
@@ -375,10 +377,10 @@ void gemm_f64_km(int M, int N, int K, const float* A, int lda, const float* B, i
   const dim3 g((unsigned)(splits * tm * tn));
   if (vec)
     hipLaunchKernelGGL(gemm_f64<true>, g, dim3(kThreads), 0, s, M, N, K, A, lda, B, ldb, C, ldc, kps, c_split, tm, tn,
-                       splits);
+                       splits, gate);
   else
     hipLaunchKernelGGL(gemm_f64<false>, g, dim3(kThreads), 0, s, M, N, K, A, lda, B, ldb, C, ldc, kps, c_split, tm, tn,
-                       splits);
+                       splits, gate);
 }
 
 }  // namespace snn

@@ -83,7 +83,8 @@ __device__ __forceinline__ void load_tile(const int32_t* counts, int n, int base
   }
 }
 
-__global__ __launch_bounds__(kScanThreads) void scan_tile_sums(const int32_t* counts, int n, int32_t* sums) {
+__global__ __launch_bounds__(kScanThreads) void scan_tile_sums(const int32_t* counts, int n, int32_t* sums, Gate gate) {
+  if (!gate_open(gate)) return;
   int x[kScanPerThread];
   load_tile(counts, n, blockIdx.x * kScanTile + threadIdx.x * kScanPerThread, x);
   int s = 0;
@@ -95,7 +96,8 @@ __global__ __launch_bounds__(kScanThreads) void scan_tile_sums(const int32_t* co
 }
 
 // One block scans the tile sums in place (exclusive).
-__global__ __launch_bounds__(kScanThreads) void scan_sums(int32_t* sums, int nb) {
+__global__ __launch_bounds__(kScanThreads) void scan_sums(int32_t* sums, int nb, Gate gate) {
+  if (!gate_open(gate)) return;
   int carry = 0;
   for (int base = 0; base < nb; base += kScanTile) {
     int x[kScanPerThread];
@@ -119,7 +121,9 @@ __global__ __launch_bounds__(kScanThreads) void scan_sums(int32_t* sums, int nb)
 // Each tile's offset is sums[tile] (scanned by scan_sums), or, with own_prefix, the sum of the
 // earlier tiles' totals formed by the block itself (few tiles: one kernel less on the chain).
 __global__ __launch_bounds__(kScanThreads) void scan_apply(const int32_t* counts, int n, const int32_t* sums,
-                                                           int nb, int32_t* out, int64_t* total64, int own_prefix) {
+                                                           int nb, int32_t* out, int64_t* total64, int own_prefix,
+                                                           Gate gate) {
+  if (!gate_open(gate)) return;
   int x[kScanPerThread];
   const int base = blockIdx.x * kScanTile + threadIdx.x * kScanPerThread;
   load_tile(counts, n, base, x);
@@ -155,15 +159,15 @@ __global__ __launch_bounds__(kScanThreads) void scan_apply(const int32_t* counts
 size_t scan_temp_elems(int n) { return (size_t)((n + kScanTile - 1) / kScanTile) + 1; }
 
 void launch_exclusive_scan(const int32_t* counts, int n, int32_t* out, int64_t* total64, int32_t* temp,
-                           hipStream_t stream) {
+                           hipStream_t stream, const Gate& gate) {
   const int nb = (n + kScanTile - 1) / kScanTile;
   // up to kOwnPrefixTiles tiles each block adds the earlier tiles' totals itself (two kernels);
   // beyond, one block scans the tile totals first (three kernels)
   const bool own = nb <= kOwnPrefixTiles;
-  hipLaunchKernelGGL(scan_tile_sums, dim3(nb), dim3(kScanThreads), 0, stream, counts, n, temp);
-  if (!own) hipLaunchKernelGGL(scan_sums, dim3(1), dim3(kScanThreads), 0, stream, temp, nb);
+  hipLaunchKernelGGL(scan_tile_sums, dim3(nb), dim3(kScanThreads), 0, stream, counts, n, temp, gate);
+  if (!own) hipLaunchKernelGGL(scan_sums, dim3(1), dim3(kScanThreads), 0, stream, temp, nb, gate);
   hipLaunchKernelGGL(scan_apply, dim3(nb), dim3(kScanThreads), 0, stream, counts, n, temp, nb, out, total64,
-                     own ? 1 : 0);
+                     own ? 1 : 0, gate);
 }
 
 }  // namespace snn

@@ -182,7 +182,8 @@ __device__ __forceinline__ EntryKey entry_key(int ee, int E1, int rp, int nr, in
 __global__ __launch_bounds__(kRowWaves * kWave) void slab_count(int TB, int N_out, int n_slabs, int slab, int R,
                                                                 const int32_t* __restrict__ row_ptr,
                                                                 const int32_t* __restrict__ col_idx, int64_t cap,
-                                                                int32_t* __restrict__ cnt) {
+                                                                int32_t* __restrict__ cnt, Gate gate) {
+  if (!gate_open(gate)) return;
   __shared__ int tot[kRowWaves][kWave];
   const int w = threadIdx.x / kWave;
   const int l = lane_id();
@@ -208,7 +209,8 @@ __global__ __launch_bounds__(kRowWaves * kWave) void slab_fill(int TB, int N_out
                                                                const float* __restrict__ g,
                                                                const float* __restrict__ eps, int64_t cap,
                                                                const int32_t* __restrict__ sp, int64_t nrec,
-                                                               SlabRec* __restrict__ rec) {
+                                                               SlabRec* __restrict__ rec, Gate gate) {
+  if (!gate_open(gate)) return;
   __shared__ int done[kRowWaves][kWave];
   const int w = threadIdx.x / kWave;
   const int l = lane_id();
@@ -247,8 +249,9 @@ __global__ __launch_bounds__(kDwThreads) void dw_slab_kernel(const float* __rest
                                                              int N_out, const int32_t* __restrict__ sp,
                                                              const SlabRec* __restrict__ rec, int64_t nrec,
                                                              float* __restrict__ out, int n_chunks,
-                                                             int n_itiles, int n_slabs, int slab) {
+                                                             int n_itiles, int n_slabs, int slab, Gate gate) {
   extern __shared__ double acc[];  // [slab][kLd]
+  if (!gate_open(gate)) return;
   int id = blockIdx.x;
   const int nb = gridDim.x;
   if ((nb & 7) == 0) id = (id & 7) * (nb >> 3) + (id >> 3);
@@ -367,8 +370,9 @@ __global__ __launch_bounds__(kDwThreads) void dw_rows_kernel(const float* __rest
                                                              const float* __restrict__ g,
                                                              const float* __restrict__ eps, int64_t cap,
                                                              float* __restrict__ out, int n_chunks,
-                                                             int n_itiles) {
+                                                             int n_itiles, Gate gate) {
   extern __shared__ double acc[];  // [N_out][kRowsLd]
+  if (!gate_open(gate)) return;
   int id = blockIdx.x;
   const int nb = gridDim.x;
   if ((nb & 7) == 0) id = (id & 7) * (nb >> 3) + (id >> 3);
@@ -630,7 +634,9 @@ __global__ void fill_zero(float* __restrict__ p, size_t n) {
   for (size_t k = blockIdx.x * (size_t)blockDim.x + threadIdx.x; k < n; k += (size_t)gridDim.x * blockDim.x) p[k] = 0.0f;
 }
 
-__global__ void reduce_chunks(const float* __restrict__ part, int n_chunks, size_t n, float* __restrict__ out) {
+__global__ void reduce_chunks(const float* __restrict__ part, int n_chunks, size_t n, float* __restrict__ out,
+                              Gate gate) {
+  if (!gate_open(gate)) return;
   constexpr int kAhead = 8;  // partials loaded before any is added (the adds keep chunk order)
   for (size_t k = blockIdx.x * (size_t)blockDim.x + threadIdx.x; k < n; k += (size_t)gridDim.x * blockDim.x) {
     double s = 0.0;  // fixed order, rounded once
@@ -645,6 +651,72 @@ __global__ void reduce_chunks(const float* __restrict__ part, int n_chunks, size
     for (; c < n_chunks; ++c) s += (double)part[(size_t)c * n + k];
     out[k] = (float)s;
   }
+}
+
+// ------------------------------------------------------------------ wide bands
+//
+// With many active entries dW is a dense product: G written densely (zeros included) and
+// dW = trace^T G on the float64 matrix cores (gemm_f64_km), the accumulation of the kernels above.
+// A wavefront per row builds the row in LDS and writes it once (HBM-bound: 12 bytes per entry read,
+// 4 per slot written).
+constexpr int kDenseWaves = 4;
+
+__global__ __launch_bounds__(kDenseWaves * kWave) void csr_dense_g(int TB, int N_out, const int32_t* __restrict__ rp,
+                                                                   const int32_t* __restrict__ col,
+                                                                   const float* __restrict__ g,
+                                                                   const float* __restrict__ eps, int64_t cap,
+                                                                   float* __restrict__ Gd, Gate gate) {
+  extern __shared__ float row_lds[];  // [kDenseWaves][N_out rounded up to whole float4]
+  if (!gate_open(gate)) return;
+  const int w = threadIdx.x / kWave;
+  const int l = lane_id();
+  const int r = blockIdx.x * kDenseWaves + w;
+  if (r >= TB) return;
+  const int ld = (N_out + 3) & ~3;
+  float* x = row_lds + (size_t)w * ld;
+  float4* x4 = reinterpret_cast<float4*>(x);
+  for (int j = l; 4 * j < ld; j += kWave) x4[j] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+  __builtin_amdgcn_wave_barrier();
+  const int e0 = clamp_entry(rp[r], cap), e1 = clamp_entry(rp[r + 1], cap);
+  for (int e = e0 + l; e < e1; e += kWave) {
+    const int j = col[e];
+    const float v = eps[e] * (g ? g[e] : 1.0f);
+    if ((unsigned)j < (unsigned)N_out) x[j] = v;
+  }
+  __builtin_amdgcn_wave_barrier();
+  float* dst = Gd + (size_t)r * N_out;
+  if (N_out % 4 == 0) {
+    for (int j = l; 4 * j < N_out; j += kWave) reinterpret_cast<float4*>(dst)[j] = x4[j];
+  } else {
+    for (int j = l; j < N_out; j += kWave) dst[j] = x[j];
+  }
+}
+
+// The dense product's plan and the number of entries from which it is the faster way. Per multiply-add
+// the entry kernels run at the rate of their float64 LDS atomics, measured 3.8e12 a second (1024 -> 1024,
+// 27% active: 9.6 ms), the product at 31.7e12 (padded to 128 x 128 tiles: 4.2 ms), plus about 2 ps per slot
+// for writing and reading G and 15 us of launches; entries cost more than the product from about 13%.
+struct DenseDwPlan {
+  int splits;
+  int64_t least;
+};
+
+DenseDwPlan plan_dw_dense(int T, int B, int N_in, int N_out) {
+  DenseDwPlan p{};
+  const double TB = (double)T * B;
+  const int tm = (N_in + 127) / 128, tn = (N_out + 127) / 128;
+  int s = (2 * cu_count() + tm * tn - 1) / (tm * tn);
+  s = std::min(s, std::max(1, T * B / 256));
+  s = std::max(1, std::min(s, 64));
+  p.splits = s >= 8 ? s / 8 * 8 : s;
+  const double dense_s = TB * (128.0 * tm) * (128.0 * tn) / 31.7e12 + TB * N_out * 2e-12 + 15e-6;
+  p.least = (int64_t)(1.1 * dense_s * 3.8e12 / (double)N_in) + 1;
+  return p;
+}
+
+// Whether a layer with out_cap entry slots may hold enough of them for the dense product.
+bool dw_dense_possible(int T, int B, int N_in, int N_out, int64_t out_cap) {
+  return N_out > 32 && out_cap >= plan_dw_dense(T, B, N_in, N_out).least;
 }
 
 // ------------------------------------------------------------------ narrow layers
@@ -1326,9 +1398,17 @@ size_t dw_workspace(int T, int B, int N_in, int N_out, int64_t out_cap) {
     return c.off;
   }
   if (mdw_eligible(T, B, N_in, N_out, out_cap)) return mdw_workspace(T, B, N_in, N_out, out_cap);
+  size_t dense = 0;  // the dense product's G and partials, in the same place (one of the two ways runs)
+  if (dw_dense_possible(T, B, N_in, N_out, out_cap)) {
+    Carve c(nullptr);
+    c.take<float>((size_t)T * B * N_out);
+    const int splits = plan_dw_dense(T, B, N_in, N_out).splits;
+    if (splits > 1) c.take<float>((size_t)splits * N_in * N_out);
+    dense = c.off;
+  }
   if (dw_rows_eligible(N_in, N_out)) {  // the chunk partials only
     const DwPlan p = plan_dw_rows(T, B, N_in, N_out);
-    return p.n_chunks > 1 ? (size_t)p.n_chunks * N_in * N_out * sizeof(float) : 256;
+    return std::max(dense, p.n_chunks > 1 ? (size_t)p.n_chunks * N_in * N_out * sizeof(float) : 256);
   }
   const DwPlan p = plan_dw_interleaved(T, B, N_in, N_out);
   const int nsp = p.n_slabs * T * B;
@@ -1338,7 +1418,7 @@ size_t dw_workspace(int T, int B, int N_in, int N_out, int64_t out_cap) {
   c.take<int32_t>((size_t)nsp);
   c.take<int32_t>(scan_temp_elems(nsp));
   c.take<SlabRec>((size_t)std::max<int64_t>(out_cap, 1));
-  return c.off;
+  return std::max(dense, c.off);
 }
 
 size_t gin_workspace(int T, int B, int N_out) {
@@ -1420,6 +1500,30 @@ void enqueue_dw(const float* trace_in, int T, int B, int N_in, int N_out, const 
     if (rest) mdw_enqueue_rest(trace_in, T, B, N_in, N_out, out_g, eps_out, out_cap, dW, workspace, s);
     return;
   }
+  // Entry by entry below p.least active entries, a dense product from there on; which, the kernels decide
+  // by the CSR's own count (out_cap is an upper bound of it), so both are enqueued where both are possible.
+  Gate few{}, many{};
+  DenseDwPlan dense{};
+  const bool maybe_dense = dw_dense_possible(T, B, N_in, N_out, out_cap);
+  if (maybe_dense) {
+    dense = plan_dw_dense(T, B, N_in, N_out);
+    few = Gate{out_row_ptr + (size_t)T * B, out_cap, dense.least, true};
+    many = Gate{out_row_ptr + (size_t)T * B, out_cap, dense.least, false};
+  }
+  const auto enqueue_dense = [&]() {
+    Carve ws(workspace);
+    float* Gd = ws.take<float>((size_t)T * B * N_out);
+    float* part = dense.splits > 1 ? ws.take<float>((size_t)dense.splits * N_in * N_out) : dW;
+    const size_t lds = (size_t)kDenseWaves * ((N_out + 3) & ~3) * sizeof(float);
+    hipLaunchKernelGGL(csr_dense_g, dim3((unsigned)((T * B + kDenseWaves - 1) / kDenseWaves)),
+                       dim3(kDenseWaves * kWave), lds, s, T * B, N_out, out_row_ptr, out_col_idx, out_g, eps_out,
+                       out_cap, Gd, many);
+    const size_t n = (size_t)N_in * N_out;
+    gemm_f64_km(N_in, N_out, T * B, trace_in, N_in, Gd, N_out, part, N_out, dense.splits, n, many, s);
+    if (dense.splits > 1)
+      hipLaunchKernelGGL(reduce_chunks, dim3((unsigned)std::min<size_t>((n + 255) / 256, 4096)), dim3(256), 0, s, part,
+                         dense.splits, n, dW, many);
+  };
   if (dw_rows_eligible(N_in, N_out)) {  // straight from the CSR: no layout pass
     if (!rest) return;
     const DwPlan p = plan_dw_rows(T, B, N_in, N_out);
@@ -1428,17 +1532,18 @@ void enqueue_dw(const float* trace_in, int T, int B, int N_in, int N_out, const 
     if (out_g) {
       ensure_dynamic_lds((const void*)dw_rows_kernel<true>, (int)p.lds);
       hipLaunchKernelGGL(dw_rows_kernel<true>, grid, dim3(kDwThreads), p.lds, s, trace_in, T * B, N_in, N_out,
-                         out_row_ptr, out_col_idx, out_g, eps_out, out_cap, part, p.n_chunks, p.n_itiles);
+                         out_row_ptr, out_col_idx, out_g, eps_out, out_cap, part, p.n_chunks, p.n_itiles, few);
     } else {
       ensure_dynamic_lds((const void*)dw_rows_kernel<false>, (int)p.lds);
       hipLaunchKernelGGL(dw_rows_kernel<false>, grid, dim3(kDwThreads), p.lds, s, trace_in, T * B, N_in, N_out,
-                         out_row_ptr, out_col_idx, out_g, eps_out, out_cap, part, p.n_chunks, p.n_itiles);
+                         out_row_ptr, out_col_idx, out_g, eps_out, out_cap, part, p.n_chunks, p.n_itiles, few);
     }
     if (p.n_chunks > 1) {
       const size_t n = (size_t)N_in * N_out;
       const unsigned blocks = (unsigned)std::min<size_t>((n + 255) / 256, 4096);
-      hipLaunchKernelGGL(reduce_chunks, dim3(blocks), dim3(256), 0, s, part, p.n_chunks, n, dW);
+      hipLaunchKernelGGL(reduce_chunks, dim3(blocks), dim3(256), 0, s, part, p.n_chunks, n, dW, few);
     }
+    if (maybe_dense) enqueue_dense();
     return;
   }
   const int TB = T * B;
@@ -1458,25 +1563,26 @@ void enqueue_dw(const float* trace_in, int T, int B, int N_in, int N_out, const 
   const int64_t nrec = std::max<int64_t>(out_cap, 1);
   if (layout) {
     hipLaunchKernelGGL(slab_count, rgrid, rblock, 0, s, TB, N_out, p.n_slabs, p.slab, R, out_row_ptr, out_col_idx,
-                       out_cap, scnt);
-    launch_exclusive_scan(scnt, nsp, sp, nullptr, stmp, s);
+                       out_cap, scnt, few);
+    launch_exclusive_scan(scnt, nsp, sp, nullptr, stmp, s, few);
   }
   if (!rest) return;
   if (out_g)
     hipLaunchKernelGGL(slab_fill<true>, rgrid, rblock, 0, s, TB, N_out, p.n_slabs, p.slab, R, out_row_ptr,
-                       out_col_idx, out_g, eps_out, out_cap, sp, nrec, rec);
+                       out_col_idx, out_g, eps_out, out_cap, sp, nrec, rec, few);
   else
     hipLaunchKernelGGL(slab_fill<false>, rgrid, rblock, 0, s, TB, N_out, p.n_slabs, p.slab, R, out_row_ptr,
-                       out_col_idx, out_g, eps_out, out_cap, sp, nrec, rec);
+                       out_col_idx, out_g, eps_out, out_cap, sp, nrec, rec, few);
   const dim3 dgrid((unsigned)(p.n_itiles * p.n_slabs * p.n_chunks));
   ensure_dynamic_lds((const void*)dw_slab_kernel, (int)p.lds);
   hipLaunchKernelGGL(dw_slab_kernel, dgrid, dim3(kDwThreads), p.lds, s, trace_in, TB, N_in, N_out, sp, rec, nrec,
-                     part, p.n_chunks, p.n_itiles, p.n_slabs, p.slab);
+                     part, p.n_chunks, p.n_itiles, p.n_slabs, p.slab, few);
   if (p.n_chunks > 1) {
     const size_t n = (size_t)N_in * N_out;
     const unsigned blocks = (unsigned)std::min<size_t>((n + 255) / 256, 4096);
-    hipLaunchKernelGGL(reduce_chunks, dim3(blocks), dim3(256), 0, s, part, p.n_chunks, n, dW);
+    hipLaunchKernelGGL(reduce_chunks, dim3(blocks), dim3(256), 0, s, part, p.n_chunks, n, dW, few);
   }
+  if (maybe_dense) enqueue_dense();
 }
 
 // Chunks of the trace-recompute dW: 128 samples x tlen steps (tlen a multiple of K), about as
@@ -1534,14 +1640,14 @@ void enqueue_dw_spikes(const uint8_t* s_in, const float* ck, int K, float alpha,
   const dim3 rblock(kRowWaves * kWave);
   const int64_t nrec = std::max<int64_t>(out_cap, 1);
   hipLaunchKernelGGL(slab_count, rgrid, rblock, 0, s, TB, N_out, p.n_slabs, p.slab, R, out_row_ptr, out_col_idx,
-                     out_cap, scnt);
+                     out_cap, scnt, Gate{});
   launch_exclusive_scan(scnt, nsp, sp, nullptr, stmp, s);
   if (out_g)
     hipLaunchKernelGGL(slab_fill<true>, rgrid, rblock, 0, s, TB, N_out, p.n_slabs, p.slab, R, out_row_ptr,
-                       out_col_idx, out_g, eps_out, out_cap, sp, nrec, rec);
+                       out_col_idx, out_g, eps_out, out_cap, sp, nrec, rec, Gate{});
   else
     hipLaunchKernelGGL(slab_fill<false>, rgrid, rblock, 0, s, TB, N_out, p.n_slabs, p.slab, R, out_row_ptr,
-                       out_col_idx, out_g, eps_out, out_cap, sp, nrec, rec);
+                       out_col_idx, out_g, eps_out, out_cap, sp, nrec, rec, Gate{});
   const dim3 dgrid((unsigned)(p.n_itiles * p.n_slabs * q.n_chunks));
   ensure_dynamic_lds((const void*)dw_slab_spikes_kernel, (int)p.lds);
   hipLaunchKernelGGL(dw_slab_spikes_kernel, dgrid, dim3(kDwThreads), p.lds, s, s_in, ck, K, alpha, T, B, N_in, N_out,
@@ -1549,7 +1655,7 @@ void enqueue_dw_spikes(const uint8_t* s_in, const float* ck, int K, float alpha,
   if (q.n_chunks > 1) {
     const size_t n = (size_t)N_in * N_out;
     const unsigned blocks = (unsigned)std::min<size_t>((n + 255) / 256, 4096);
-    hipLaunchKernelGGL(reduce_chunks, dim3(blocks), dim3(256), 0, s, part, q.n_chunks, n, dW);
+    hipLaunchKernelGGL(reduce_chunks, dim3(blocks), dim3(256), 0, s, part, q.n_chunks, n, dW, Gate{});
   }
 }
 
