@@ -231,6 +231,14 @@ snn_status snn_sparse_dw_prepared(const float* trace_in, int T, int B, int N_in,
                                   const float* eps_out, int64_t out_cap, float* dW, void* workspace,
                                   size_t workspace_bytes, void* stream);
 size_t snn_sparse_grad_in_workspace(int T, int B, int N_out);
+/*
+ * The spike gradient's workspace with room for delta written densely where in_cap allows so many input
+ * entries that a dense product may be the faster way (from about 13% of a large layer's slots on); given at
+ * least this much, snn_sparse_grad_in takes that way when in_row_ptr[T*B] says so. With the smaller workspace
+ * it goes entry by entry. snn_sparse_backward likewise, with the second query.
+ */
+size_t snn_sparse_grad_in_workspace_full(int T, int B, int N_in, int N_out, int64_t in_cap);
+size_t snn_sparse_backward_workspace_full(int T, int B, int N_in, int N_out, int64_t out_cap, int64_t in_cap);
 snn_status snn_sparse_grad_in(const float* W, int T, int B, int N_in, int N_out, float alpha,
                               const int32_t* out_row_ptr, const int32_t* out_col_idx,
                               const float* out_g, const float* eps_out, int64_t out_cap,

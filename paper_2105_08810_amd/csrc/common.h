@@ -88,6 +88,16 @@ void gemm_split_km(int M, int N, int K, const float* A, int lda, const float* B,
                    size_t c_split, hipStream_t s);
 void gemm_split_kc(int M, int N, int K, const float* A, int lda, const float* B, int ldb, float* C, int ldc,
                    hipStream_t s);
+// The elements (r, col_idx[e]) of C, as gemm_split_kc forms it, at the entries e < cap of a CSR over C's
+// rows: out[e] (0 for a column outside [0, N)). What is not an entry is not written.
+struct GatherOut {
+  const int32_t* row_ptr = nullptr;  // [M + 1]
+  const int32_t* col_idx = nullptr;
+  int64_t cap = 0;
+  float* out = nullptr;
+};
+void gemm_split_kc_gather(int M, int N, int K, const float* A, int lda, const float* B, int ldb, const GatherOut& to,
+                          const Gate& gate, hipStream_t s);
 void gemm_f64_km(int M, int N, int K, const float* A, int lda, const float* B, int ldb, float* C, int ldc, int splits,
                  size_t c_split, const Gate& gate, hipStream_t s);
 

@@ -4,20 +4,21 @@
 // times 8 significant bits hold a float32's 24. A product takes the six terms down to 2^-16 of the
 // leading one (hh, hm, mh, mm, hl, lh; what is left out is below 2^-24 of |x||y|), and the matrix cores
 // form 16-bit products exactly and sum them in float32. hh goes to one accumulator and the five small
-// terms to another, so the leading sum is rounded once per 16 products of K (a float32 MFMA chain: once
-// per 2). bf16 has float32's exponent range, so no scaling is needed; values of 2^127 and more (and
+// terms to another, so the leading sum is rounded once per 8 products of K (a float32 MFMA chain: once
+// per 1 or 2). bf16 has float32's exponent range, so no scaling is needed; values of 2^127 and more (and
 // infinities, which a split would turn into NaN) make the block that met one form its tile again on the
 // float32 matrix cores.
 //
 // Bound: the matrix cores, six bf16 products per float32 one (2.5 PFLOP/s / 6 = 417 TFLOP/s of useful
 // work at the nominal rate; the float32 MFMA's nominal rate is 157). A block of four wavefronts owns
-// 128 x 128 of C, a wavefront 64 x 64 (2 x 2 tiles of v_mfma_f32_32x32x16_bf16). A stage of 32 k is
+// 128 x 128 of C, a wavefront 64 x 64 (4 x 4 tiles of v_mfma_f32_16x16x32_bf16). A stage of 32 k is
 // loaded into registers while the previous one is multiplied, split there and stored to LDS as
 // [part][k / 8][row] pieces of 16 bytes, which the fragment reads (lane = row, 8 consecutive k) take
 // without bank conflicts; two blocks per CU overlap one's split with the other's products. Measured at
 // 128000 x 1024 x 1024: 1.52 ms, 176 TFLOP/s (1056 in bf16 terms; a large bf16 product of the library
-// reaches 1290 on this card), 1.75 ms with the six terms of a tile issued one after another. Error
-// against 64 bits with 16000 products of random sign per sum: 0.8e-6 of the result, float32 MFMA 3.3e-6.
+// reaches 1290 on this card), 1.75 ms with the six terms of a tile issued one after another, 1.54 with
+// 32 x 32 x 16 tiles. Error against 64 bits with 16000 products of random sign per sum: 0.8e-6 of the
+// result, float32 MFMA 3.3e-6.
 #include "common.h"
 
 namespace snn {
@@ -26,12 +27,11 @@ namespace {
 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef float f32x2 __attribute__((ext_vector_type(2)));
-typedef float f32x16 __attribute__((ext_vector_type(16)));
+typedef float f32x4 __attribute__((ext_vector_type(4)));
 
 constexpr int kBM = 128, kBN = 128, kBK = 32;
 constexpr int kThreads = 256;
 constexpr int kKC = kBK / 8;      // pieces of 8 k per row and stage
-constexpr int kLdR = kBM + 2;     // pieces per [part][k / 8] line (2: the lines' stores spread over the banks)
 constexpr float kWide = 1.7e38f;  // 2^127 rounded down: bf16 rounding cannot overflow below it
 
 // Eight values into their three parts, 16 bytes each.
@@ -51,25 +51,25 @@ __device__ __forceinline__ void split8(const float (&x)[8], uint4& h, uint4& m, 
   l = make_uint4(lp[0], lp[1], lp[2], lp[3]);
 }
 
-// One operand's share of a stage: two pieces (8 k of one row each) per thread.
+// One operand's share of a stage of ROWS (128 or 64) rows: two pieces or one (8 k of one row each) per thread.
 //   KM: element (r, k) at p[k * ld + r] (rows contiguous): a piece is eight loads, each 256 contiguous
 //       bytes over a wavefront.
 //   else p[r * ld + k] (k contiguous): a piece is 32 contiguous bytes.
 // Rows past the end read the last row (their results are not stored); k past k_hi reads as 0.
-template <bool KM>
+template <bool KM, int ROWS>
 __device__ __forceinline__ void piece_of(int q, int& row, int& kc) {
   const int idx = threadIdx.x + kThreads * q;
-  row = KM ? idx % kBM : idx / kKC;
-  kc = KM ? idx / kBM : idx % kKC;
+  row = KM ? idx % ROWS : idx / kKC;
+  kc = KM ? idx / ROWS : idx % kKC;
 }
 
-template <bool KM, bool VEC>
+template <bool KM, bool VEC, int ROWS>
 __device__ __forceinline__ void load_stage(const float* __restrict__ p, int ld, int r0, int R, int k0, int k_hi,
-                                           float (&x)[2][8]) {
+                                           float (&x)[ROWS / 64][8]) {
 #pragma unroll
-  for (int q = 0; q < 2; ++q) {
+  for (int q = 0; q < ROWS / 64; ++q) {
     int row, kc;
-    piece_of<KM>(q, row, kc);
+    piece_of<KM, ROWS>(q, row, kc);
     const int r = min(r0 + row, R - 1);
     const int k = k0 + 8 * kc;
     if (KM) {
@@ -94,23 +94,40 @@ __device__ __forceinline__ void load_stage(const float* __restrict__ p, int ld, 
   }
 }
 
-typedef uint4 Stage[3][kKC][kLdR];
-constexpr int kLdF = kBM + 4;  // floats per line of the float32 stage (a wide tile)
-static_assert(kBK * kLdF * sizeof(float) <= sizeof(Stage), "the float32 stage fits the split one's LDS");
+// [part][k / 8][row] pieces; a line holds two more than its rows (the lines' stores spread over the banks).
+template <int ROWS>
+struct Stage {
+  uint4 x[3][kKC][ROWS + 2];
+};
 
-template <bool KM>
-__device__ __forceinline__ void store_stage(Stage& S, const float (&x)[2][8], float& big) {
+template <bool KM, int ROWS>
+__device__ __forceinline__ void store_stage(Stage<ROWS>& S, const float (&x)[ROWS / 64][8], float& big) {
 #pragma unroll
-  for (int q = 0; q < 2; ++q) {
+  for (int q = 0; q < ROWS / 64; ++q) {
     int row, kc;
-    piece_of<KM>(q, row, kc);
+    piece_of<KM, ROWS>(q, row, kc);
 #pragma unroll
     for (int u = 0; u < 8; u += 2) big = fmaxf(fmaxf(big, fabsf(x[q][u])), fabsf(x[q][u + 1]));
-    uint4 h, m, l;
-    split8(x[q], h, m, l);
-    S[0][kc][row] = h;
-    S[1][kc][row] = m;
-    S[2][kc][row] = l;
+    split8(x[q], S.x[0][kc][row], S.x[1][kc][row], S.x[2][kc][row]);
+  }
+}
+
+// The same stage as float32 lines [k][row], for a tile with a value out of the split's range.
+template <int ROWS>
+struct WideStage {
+  float x[kBK][ROWS + 4];
+};
+static_assert(sizeof(WideStage<128>) <= sizeof(Stage<128>) && sizeof(WideStage<64>) <= sizeof(Stage<64>),
+              "the float32 stage fits the split one's LDS");
+
+template <bool KM, int ROWS>
+__device__ __forceinline__ void store_wide(WideStage<ROWS>& S, const float (&x)[ROWS / 64][8]) {
+#pragma unroll
+  for (int q = 0; q < ROWS / 64; ++q) {
+    int row, kc;
+    piece_of<KM, ROWS>(q, row, kc);
+#pragma unroll
+    for (int u = 0; u < 8; ++u) S.x[8 * kc + u][row] = x[q][u];
   }
 }
 
@@ -138,115 +155,204 @@ __device__ __forceinline__ BlockTile row_tile(int tiles_m, int tiles_n) {
 }
 
 // C[M x N] = sum over this block's K slice of A(m, k) B(k, n); slice z goes to C + z * c_split.
-template <bool KM, bool VEC>
+// GATHER: only the elements (r, col_idx[e]) of a CSR's entries e are wanted (row r = m of its T*B rows,
+// columns ascending in a row) and go to out[e]. The block finds its rows' entries in its columns by
+// bisection, passes its tile through LDS 64 rows at a time and reads the entries' elements there. Its tile
+// is 128 x 64, and every 64 k its sums are moved to float64 registers (the matrix cores round the running
+// sum every 8 k): the error stays below that of a wavefront's float32 dot product (1024 terms of a trained-like
+// layer: 0.7e-7 of the result against 0.9e-7; 1.2e-7 with float32 totals per 256 k).
+template <bool KM, bool VEC, bool GATHER>
 __global__ __launch_bounds__(kThreads, 2) void gemm_split3(int M, int N, int K, const float* __restrict__ A, int lda,
                                                            const float* __restrict__ B, int ldb,
                                                            float* __restrict__ C, int ldc, int k_per_split,
-                                                           size_t c_split, int tiles_m, int tiles_n, int splits) {
-  __shared__ Stage As, Bs;
+                                                           size_t c_split, int tiles_m, int tiles_n, int splits,
+                                                           GatherOut to, Gate gate) {
+  if (!gate_open(gate)) return;
+  constexpr int TN = GATHER ? 2 : 4;  // 16-wide column tiles of a wavefront
+  constexpr int BN = 32 * TN;
+  constexpr int kFold = 2;  // GATHER: stages between two moves to the float64 sums
+  __shared__ __attribute__((aligned(16))) char lds[sizeof(Stage<kBM>) + sizeof(Stage<BN>)];
+  __shared__ int range[GATHER ? 2 * kBM : 1];  // entries of the tile's rows in its columns: [range[r], range[kBM + r])
+  Stage<kBM>& As = *reinterpret_cast<Stage<kBM>*>(lds);
+  Stage<BN>& Bs = *reinterpret_cast<Stage<BN>*>(lds + sizeof(Stage<kBM>));
   const int w = threadIdx.x / kWave;
   const int l = threadIdx.x % kWave;
   const BlockTile bt = KM ? slice_tile(tiles_m, tiles_n, splits) : row_tile(tiles_m, tiles_n);
   if (!bt.ok) return;
-  const int tm = bt.tm, tn = bt.tn, z = bt.z;
-  const int m0 = tm * kBM, n0 = tn * kBN;
-  const int k_lo = z * k_per_split;
+  const int m0 = bt.tm * kBM, n0 = bt.tn * BN;
+  const int wm = (w / 2) * 64, wn = (w % 2) * (BN / 2);
+  const int lr = l % 16, lk = l / 16;
+
+  if (GATHER) {  // one bound of one row per thread; the first and last tile also take columns outside [0, N)
+    const int r = m0 + (int)threadIdx.x % kBM;
+    const bool upper = threadIdx.x >= kBM;
+    int lo = 0;
+    if (r < M) {
+      const auto clamped = [&](int v) { return (int)(v < 0 ? 0 : (v > to.cap ? to.cap : v)); };
+      const int a = clamped(to.row_ptr[r]);
+      const int z = max(a, clamped(to.row_ptr[r + 1]));
+      const int want = upper ? n0 + BN : n0;
+      int hi = z;
+      lo = a;
+      if (upper && bt.tn == tiles_n - 1) lo = z;
+      if (!upper && bt.tn == 0) hi = a;
+      while (lo < hi) {
+        const int mid = (lo + hi) >> 1;
+        if (to.col_idx[mid] < want) lo = mid + 1; else hi = mid;
+      }
+    }
+    range[threadIdx.x] = lo;
+  }
+
+  const int k_lo = bt.z * k_per_split;
   const int k_hi = min(K, k_lo + k_per_split);
-  const int wm = (w / 2) * 64, wn = (w % 2) * 64;
-  const int lr = l % 32, lk = l / 32;
+  f32x4 lead[4][TN], rest[4][TN];
+  const auto clear = [&]() {
+#pragma unroll
+    for (int a = 0; a < 4; ++a)
+#pragma unroll
+      for (int b = 0; b < TN; ++b) lead[a][b] = rest[a][b] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+  };
+  clear();
+  double total[4][GATHER ? TN : 1][4];
+  const auto fold = [&]() {
+    if constexpr (GATHER) {
+#pragma unroll
+      for (int a = 0; a < 4; ++a)
+#pragma unroll
+        for (int b = 0; b < TN; ++b)
+#pragma unroll
+          for (int v = 0; v < 4; ++v) total[a][b][v] += (double)lead[a][b][v] + (double)rest[a][b][v];
+      clear();
+    }
+  };
+  if constexpr (GATHER) {
+#pragma unroll
+    for (int a = 0; a < 4; ++a)
+#pragma unroll
+      for (int b = 0; b < TN; ++b)
+#pragma unroll
+        for (int v = 0; v < 4; ++v) total[a][b][v] = 0.0;
+  }
 
-  f32x16 lead[2][2], rest[2][2];
-#pragma unroll
-  for (int a = 0; a < 2; ++a)
-#pragma unroll
-    for (int b = 0; b < 2; ++b)
-#pragma unroll
-      for (int v = 0; v < 16; ++v) lead[a][b][v] = rest[a][b][v] = 0.0f;
-
-  float xa[2][8], xb[2][8];
+  float xa[2][8], xb[BN / 64][8];
   float big = 0.0f;
   if (k_lo < k_hi) {
-    load_stage<KM, VEC>(A, lda, m0, M, k_lo, k_hi, xa);
-    load_stage<KM, VEC>(B, ldb, n0, N, k_lo, k_hi, xb);
+    load_stage<KM, VEC, kBM>(A, lda, m0, M, k_lo, k_hi, xa);
+    load_stage<KM, VEC, BN>(B, ldb, n0, N, k_lo, k_hi, xb);
   }
+  int stage = 0;
   for (int k0 = k_lo; k0 < k_hi; k0 += kBK) {
-    store_stage<KM>(As, xa, big);
-    store_stage<KM>(Bs, xb, big);
+    store_stage<KM, kBM>(As, xa, big);
+    store_stage<KM, BN>(Bs, xb, big);
     __syncthreads();
     if (k0 + kBK < k_hi) {
-      load_stage<KM, VEC>(A, lda, m0, M, k0 + kBK, k_hi, xa);
-      load_stage<KM, VEC>(B, ldb, n0, N, k0 + kBK, k_hi, xb);
+      load_stage<KM, VEC, kBM>(A, lda, m0, M, k0 + kBK, k_hi, xa);
+      load_stage<KM, VEC, BN>(B, ldb, n0, N, k0 + kBK, k_hi, xb);
     }
+    bf16x8 fa[3][4];
 #pragma unroll
-    for (int ks = 0; ks < kBK / 16; ++ks) {
-      bf16x8 fa[3][2], fb[3][2];
+    for (int p = 0; p < 3; ++p)
 #pragma unroll
-      for (int p = 0; p < 3; ++p)
+      for (int a = 0; a < 4; ++a) fa[p][a] = __builtin_bit_cast(bf16x8, As.x[p][lk][wm + 16 * a + lr]);
 #pragma unroll
-        for (int t = 0; t < 2; ++t) {
-          fa[p][t] = __builtin_bit_cast(bf16x8, As[p][2 * ks + lk][wm + 32 * t + lr]);
-          fb[p][t] = __builtin_bit_cast(bf16x8, Bs[p][2 * ks + lk][wn + 32 * t + lr]);
-        }
+    for (int b = 0; b < TN; ++b) {
+      bf16x8 fb[3];
+#pragma unroll
+      for (int p = 0; p < 3; ++p) fb[p] = __builtin_bit_cast(bf16x8, Bs.x[p][lk][wn + 16 * b + lr]);
       // smallest terms first; neighbours in the issue order go to different accumulators
       constexpr int kTerm[6][2] = {{2, 0}, {0, 2}, {1, 1}, {1, 0}, {0, 1}, {0, 0}};
 #pragma unroll
       for (int t = 0; t < 6; ++t)
 #pragma unroll
-        for (int a = 0; a < 2; ++a)
-#pragma unroll
-          for (int b = 0; b < 2; ++b) {
-            f32x16& acc = t == 5 ? lead[a][b] : rest[a][b];
-            acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(fa[kTerm[t][0]][a], fb[kTerm[t][1]][b], acc, 0, 0, 0);
-          }
+        for (int a = 0; a < 4; ++a) {
+          f32x4& acc = t == 5 ? lead[a][b] : rest[a][b];
+          acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fa[kTerm[t][0]][a], fb[kTerm[t][1]], acc, 0, 0, 0);
+        }
     }
+    if (GATHER && ++stage % kFold == 0) fold();
     __syncthreads();
   }
+  fold();
   if (__syncthreads_or(big >= kWide)) {  // a value out of the split's range: the same sums in float32
-    float(*Af)[kLdF] = reinterpret_cast<float(*)[kLdF]>(&As);
-    float(*Bf)[kLdF] = reinterpret_cast<float(*)[kLdF]>(&Bs);
-#pragma unroll
-    for (int a = 0; a < 2; ++a)
-#pragma unroll
-      for (int b = 0; b < 2; ++b)
-#pragma unroll
-        for (int v = 0; v < 16; ++v) lead[a][b][v] = rest[a][b][v] = 0.0f;
+    WideStage<kBM>& Aw = *reinterpret_cast<WideStage<kBM>*>(&As);
+    WideStage<BN>& Bw = *reinterpret_cast<WideStage<BN>*>(&Bs);
+    clear();
     for (int k0 = k_lo; k0 < k_hi; k0 += kBK) {
-      load_stage<KM, VEC>(A, lda, m0, M, k0, k_hi, xa);
-      load_stage<KM, VEC>(B, ldb, n0, N, k0, k_hi, xb);
-#pragma unroll
-      for (int q = 0; q < 2; ++q) {
-        int row, kc;
-        piece_of<KM>(q, row, kc);
-#pragma unroll
-        for (int u = 0; u < 8; ++u) {
-          Af[8 * kc + u][row] = xa[q][u];
-          Bf[8 * kc + u][row] = xb[q][u];
-        }
-      }
+      load_stage<KM, VEC, kBM>(A, lda, m0, M, k0, k_hi, xa);
+      load_stage<KM, VEC, BN>(B, ldb, n0, N, k0, k_hi, xb);
+      store_wide<KM, kBM>(Aw, xa);
+      store_wide<KM, BN>(Bw, xb);
       __syncthreads();
-      for (int k = 0; k < kBK; k += 2)
+      for (int k = 0; k < kBK; k += 4)
 #pragma unroll
-        for (int a = 0; a < 2; ++a)
+        for (int a = 0; a < 4; ++a)
 #pragma unroll
-          for (int b = 0; b < 2; ++b)
-            lead[a][b] = __builtin_amdgcn_mfma_f32_32x32x2f32(Af[k + lk][wm + 32 * a + lr], Bf[k + lk][wn + 32 * b + lr],
-                                                             lead[a][b], 0, 0, 0);
+          for (int b = 0; b < TN; ++b)
+            lead[a][b] = __builtin_amdgcn_mfma_f32_16x16x4f32(Aw.x[k + lk][wm + 16 * a + lr],
+                                                             Bw.x[k + lk][wn + 16 * b + lr], lead[a][b], 0, 0, 0);
       __syncthreads();
+    }
+    if constexpr (GATHER) {
+#pragma unroll
+      for (int a = 0; a < 4; ++a)
+#pragma unroll
+        for (int b = 0; b < TN; ++b)
+#pragma unroll
+          for (int v = 0; v < 4; ++v) total[a][b][v] = (double)lead[a][b][v];
     }
   }
 
-  // accumulator layout of 32x32: register v of lane l holds row 8 (v / 4) + 4 (l / 32) + v % 4, column l % 32
-  float* Cz = C + (size_t)z * c_split;
+  // accumulator layout of 16x16: register v of lane l holds row 4 (l / 16) + v, column l % 16
+  if constexpr (!GATHER) {
+    float* Cz = C + (size_t)bt.z * c_split;
 #pragma unroll
-  for (int a = 0; a < 2; ++a)
+    for (int a = 0; a < 4; ++a)
 #pragma unroll
-    for (int b = 0; b < 2; ++b)
+      for (int b = 0; b < TN; ++b)
 #pragma unroll
-      for (int v = 0; v < 16; ++v) {
-        const int m = m0 + wm + 32 * a + 8 * (v / 4) + 4 * lk + (v % 4);
-        const int n = n0 + wn + 32 * b + lr;
-        if (m < M && n < N) Cz[(size_t)m * ldc + n] = lead[a][b][v] + rest[a][b][v];
+        for (int v = 0; v < 4; ++v) {
+          const int m = m0 + wm + 16 * a + 4 * lk + v;
+          const int n = n0 + wn + 16 * b + lr;
+          if (m < M && n < N) Cz[(size_t)m * ldc + n] = lead[a][b][v] + rest[a][b][v];
+        }
+  } else {
+    float(*tile)[BN + 4] = reinterpret_cast<float(*)[BN + 4]>(lds);
+    static_assert(64 * (BN + 4) * sizeof(float) <= sizeof(lds), "half a tile of C fits the stages' LDS");
+    for (int half = 0; half < 2; ++half) {
+      if (w / 2 == half) {
+#pragma unroll
+        for (int a = 0; a < 4; ++a)
+#pragma unroll
+          for (int b = 0; b < TN; ++b)
+#pragma unroll
+            for (int v = 0; v < 4; ++v) tile[16 * a + 4 * lk + v][wn + 16 * b + lr] = (float)total[a][b][v];
       }
+      __syncthreads();
+      constexpr int kRows = 4;  // rows of a wavefront in flight
+      for (int r0 = 16 * w; r0 < 16 * w + 16; r0 += kRows) {
+        int lo[kRows], hi[kRows], n = 0;
+#pragma unroll
+        for (int u = 0; u < kRows; ++u) {
+          lo[u] = range[64 * half + r0 + u];
+          hi[u] = range[kBM + 64 * half + r0 + u];
+          n = max(n, hi[u] - lo[u]);
+        }
+        for (int x = l; x - l < n; x += kWave) {
+          int c[kRows];
+#pragma unroll
+          for (int u = 0; u < kRows; ++u) c[u] = lo[u] + x < hi[u] ? to.col_idx[lo[u] + x] : -1;
+#pragma unroll
+          for (int u = 0; u < kRows; ++u) {
+            const int k = c[u] - n0;
+            const float v = ((unsigned)k < (unsigned)BN && c[u] < N) ? tile[r0 + u][k] : 0.0f;
+            if (lo[u] + x < hi[u]) to.out[lo[u] + x] = v;
+          }
+        }
+      }
+      __syncthreads();  // the tile is rewritten by the other half
+    }
+  }
 }
 
 // C[M x N] = sum over this block's K slice of A(k, m) B(k, n), float32 operands with their products and
@@ -348,23 +454,39 @@ void gemm_split_km(int M, int N, int K, const float* A, int lda, const float* B,
   const int tm = (M + kBM - 1) / kBM, tn = (N + kBN - 1) / kBN;
   int kps = (K + splits - 1) / splits;
   kps = (kps + kBK - 1) / kBK * kBK;
-  hipLaunchKernelGGL((gemm_split3<true, false>), dim3((unsigned)(splits * tm * tn)), dim3(kThreads), 0, s, M, N,
-                     K, A, lda, B, ldb, C, ldc, kps, c_split, tm, tn, splits);
+  hipLaunchKernelGGL((gemm_split3<true, false, false>), dim3((unsigned)(splits * tm * tn)), dim3(kThreads), 0, s, M, N,
+                     K, A, lda, B, ldb, C, ldc, kps, c_split, tm, tn, splits, GatherOut{}, Gate{});
 }
 
-void gemm_split_kc(int M, int N, int K, const float* A, int lda, const float* B, int ldb, float* C, int ldc,
-                   hipStream_t s) {
-  const int tm = (M + kBM - 1) / kBM, tn = (N + kBN - 1) / kBN;
+namespace {
+
+template <bool GATHER>
+void launch_kc(int M, int N, int K, const float* A, int lda, const float* B, int ldb, float* C, int ldc,
+               const GatherOut& to, const Gate& gate, hipStream_t s) {
+  const int bn = GATHER ? kBN / 2 : kBN;
+  const int tm = (M + kBM - 1) / kBM, tn = (N + bn - 1) / bn;
   const bool vec = lda % 4 == 0 && ldb % 4 == 0 && reinterpret_cast<uintptr_t>(A) % 16 == 0 &&
                    reinterpret_cast<uintptr_t>(B) % 16 == 0;
   const int kps = (K + kBK - 1) / kBK * kBK;
   const dim3 g((unsigned)((tm >= 32 ? (tm + 7) / 8 * 8 : tm) * tn));
   if (vec)
-    hipLaunchKernelGGL((gemm_split3<false, true>), g, dim3(kThreads), 0, s, M, N, K, A, lda, B, ldb, C, ldc, kps, 0, tm,
-                       tn, 1);
+    hipLaunchKernelGGL((gemm_split3<false, true, GATHER>), g, dim3(kThreads), 0, s, M, N, K, A, lda, B, ldb, C, ldc,
+                       kps, 0, tm, tn, 1, to, gate);
   else
-    hipLaunchKernelGGL((gemm_split3<false, false>), g, dim3(kThreads), 0, s, M, N, K, A, lda, B, ldb, C, ldc, kps, 0,
-                       tm, tn, 1);
+    hipLaunchKernelGGL((gemm_split3<false, false, GATHER>), g, dim3(kThreads), 0, s, M, N, K, A, lda, B, ldb, C, ldc,
+                       kps, 0, tm, tn, 1, to, gate);
+}
+
+}  // namespace
+
+void gemm_split_kc(int M, int N, int K, const float* A, int lda, const float* B, int ldb, float* C, int ldc,
+                   hipStream_t s) {
+  launch_kc<false>(M, N, K, A, lda, B, ldb, C, ldc, GatherOut{}, Gate{}, s);
+}
+
+void gemm_split_kc_gather(int M, int N, int K, const float* A, int lda, const float* B, int ldb, const GatherOut& to,
+                          const Gate& gate, hipStream_t s) {
+  launch_kc<true>(M, N, K, A, lda, B, ldb, nullptr, 0, to, gate, s);
 }
 
 void gemm_f64_km(int M, int N, int K, const float* A, int lda, const float* B, int ldb, float* C, int ldc, int splits,

@@ -19,6 +19,8 @@
 //                 gathers the W row and reduces W[i,:] . delta over the wavefront.
 #include "common.h"
 
+#include <type_traits>
+
 namespace snn {
 namespace {
 
@@ -998,17 +1000,17 @@ __global__ __launch_bounds__(kWalkThreads) void gin_chunk_sums(int T, int B, int
   __builtin_amdgcn_wave_barrier();
   const int t_lo = c * P;
   const int t_hi = min(T, t_lo + P);
-  float apow = 1.0f;
+  double apow = 1.0;  // powers in float64: 16 rounded products would be off by more than the sums are
   for (int t = t_lo; t < t_hi; ++t) {
     const int r = t * B + b;
     const int e0 = clamp_entry(row_ptr[r], cap);
     const int e1 = clamp_entry(row_ptr[r + 1], cap);
     for (int e = e0 + l; e < e1; e += kWave) {  // distinct j inside a row: no two lanes collide
       const int j = col_idx[e];
-      if ((unsigned)j < (unsigned)N_out) x[j] += apow * (eps[e] * (g ? g[e] : 1.0f));
+      if ((unsigned)j < (unsigned)N_out) x[j] += (float)apow * (eps[e] * (g ? g[e] : 1.0f));
     }
     __builtin_amdgcn_wave_barrier();
-    apow *= alpha;
+    apow *= (double)alpha;
   }
   float* dst = L + (size_t)q * N_out;
   for (int j = l; j < N_out; j += kWave) dst[j] = x[j];
@@ -1020,12 +1022,12 @@ __global__ void gin_carries(int T, int B, int N_out, float alpha, int P, int C, 
   const size_t k = blockIdx.x * (size_t)blockDim.x + threadIdx.x;
   const size_t BN = (size_t)B * N_out;
   if (k >= BN) return;
-  float aP = 1.0f;
-  for (int s = 0; s < P; ++s) aP *= alpha;
+  double aP = 1.0;  // float64: the carry of a chunk enters every chunk before it
+  for (int s = 0; s < P; ++s) aP *= (double)alpha;
   const int last_len = T - (C - 1) * P;
-  float aLast = 1.0f;
-  for (int s = 0; s < last_len; ++s) aLast *= alpha;
-  float x = 0.0f;
+  double aLast = 1.0;
+  for (int s = 0; s < last_len; ++s) aLast *= (double)alpha;
+  double x = 0.0;
   constexpr int kAhead = 8;  // chunk sums loaded before the carries overwrite them
   int c = C - 1;
   for (; c + 1 >= kAhead; c -= kAhead) {
@@ -1034,14 +1036,14 @@ __global__ void gin_carries(int T, int B, int N_out, float alpha, int P, int C, 
     for (int u = 0; u < kAhead; ++u) Lv[u] = buf[(size_t)(c - u) * BN + k];
 #pragma unroll
     for (int u = 0; u < kAhead; ++u) {
-      buf[(size_t)(c - u) * BN + k] = x;
-      x = (c - u == C - 1 ? aLast : aP) * x + Lv[u];
+      buf[(size_t)(c - u) * BN + k] = (float)x;
+      x = (c - u == C - 1 ? aLast : aP) * x + (double)Lv[u];
     }
   }
   for (; c >= 0; --c) {
     const float Lc = buf[(size_t)c * BN + k];
-    buf[(size_t)c * BN + k] = x;
-    x = (c == C - 1 ? aLast : aP) * x + Lc;
+    buf[(size_t)c * BN + k] = (float)x;
+    x = (c == C - 1 ? aLast : aP) * x + (double)Lc;
   }
 }
 
@@ -1081,7 +1083,9 @@ __device__ __forceinline__ float wave_sum4(float a0, float a1, float a2, float a
 // that a step waits only for its W rows. The input-active entries are taken four at a time
 // (4 * NJ W loads in flight) and reduced together; then delta <- alpha delta + G[t], each
 // active output added by the lane that owns its column (a uniform register index).
-template <int NJ>
+// DENSE: delta itself is written (eps_in is then [T*B][N_out]) and the input side is not read; the recurrence
+// then runs in float64 (the kernel is bound by its stores).
+template <int NJ, bool DENSE>
 __global__ __launch_bounds__(kWalkThreads, NJ <= 16 ? 4 : 1) void gin_walk(const float* __restrict__ W, int T, int B, int N_in,
                                                          int N_out, float alpha, int P, int C,
                                                          const int32_t* __restrict__ orp,
@@ -1090,7 +1094,9 @@ __global__ __launch_bounds__(kWalkThreads, NJ <= 16 ? 4 : 1) void gin_walk(const
                                                          const float* __restrict__ oeps, int64_t ocap,
                                                          const int32_t* __restrict__ irp,
                                                          const int32_t* __restrict__ ici, int64_t icap,
-                                                         const float* __restrict__ D, float* __restrict__ eps_in) {
+                                                         const float* __restrict__ D, float* __restrict__ eps_in,
+                                                         Gate gate) {
+  if (!gate_open(gate)) return;
   const int w = threadIdx.x / kWave;
   const int l = lane_id();
   // grid-stride over (c, b): a grid smaller than C*B/4 blocks leaves room on every CU for
@@ -1098,7 +1104,7 @@ __global__ __launch_bounds__(kWalkThreads, NJ <= 16 ? 4 : 1) void gin_walk(const
   for (int q = blockIdx.x * kWalkWaves + w; q < C * B; q += gridDim.x * kWalkWaves) {
   const int c = q / B;
   const int b = q - c * B;
-  float d[NJ];
+  typename std::conditional<DENSE, double, float>::type d[NJ];
 #pragma unroll
   for (int m = 0; m < NJ; ++m) {
     const int j = l + kWave * m;
@@ -1109,8 +1115,8 @@ __global__ __launch_bounds__(kWalkThreads, NJ <= 16 ? 4 : 1) void gin_walk(const
   int ia = 0, ib = 0, oa = 0, ob = 0;
   if (l < t_hi - t_lo) {
     const int r = (t_lo + l) * B + b;
-    ia = clamp_entry(irp[r], icap);
-    ib = clamp_entry(irp[r + 1], icap);
+    ia = DENSE ? 0 : clamp_entry(irp[r], icap);
+    ib = DENSE ? 0 : clamp_entry(irp[r + 1], icap);
     oa = clamp_entry(orp[r], ocap);
     ob = clamp_entry(orp[r + 1], ocap);
   }
@@ -1135,6 +1141,14 @@ __global__ __launch_bounds__(kWalkThreads, NJ <= 16 ? 4 : 1) void gin_walk(const
     const int kn = max(k - 1, 0);
     const int vi_n = in_idx(kn), vj_n = out_col(kn);
     const float vg_n = out_g(kn);
+    if (DENSE) {
+      float* dst = eps_in + ((size_t)(t_lo + k) * B + b) * N_out;
+#pragma unroll
+      for (int m = 0; m < NJ; ++m) {
+        const int j = l + kWave * m;
+        if (j < N_out) dst[j] = (float)d[m];
+      }
+    }
     // eps_in at the input-active entries of row (t, b), with delta[t] = d
     const int i0 = rdlane(ia, k);
     const int i1 = rdlane(ib, k);
@@ -1161,7 +1175,7 @@ __global__ __launch_bounds__(kWalkThreads, NJ <= 16 ? 4 : 1) void gin_walk(const
       for (int u = 0; u < kGinBatch; ++u) {
         acc[u] = 0.0f;
 #pragma unroll
-        for (int m = 0; m < NJ; ++m) acc[u] += wv[u][m] * d[m];  // d = 0 past N_out
+        for (int m = 0; m < NJ; ++m) acc[u] += wv[u][m] * (float)d[m];  // d = 0 past N_out
         acc[u] = iv[u] >= 0 ? acc[u] : 0.0f;
       }
       const float tot = wave_sum4(acc[0], acc[1], acc[2], acc[3]);
@@ -1198,13 +1212,13 @@ __global__ __launch_bounds__(kWalkThreads, NJ <= 16 ? 4 : 1) void gin_walk(const
   }
 }
 
-template <int NJ>
-void launch_walk(dim3 grid, size_t lds, hipStream_t s, const float* W, int T, int B, int N_in, int N_out,
-                 float alpha, int P, int C, const int32_t* orp, const int32_t* oci, const float* og,
-                 const float* oeps, int64_t ocap, const int32_t* irp, const int32_t* ici, int64_t icap,
-                 const float* D, float* eps_in) {
-  hipLaunchKernelGGL(gin_walk<NJ>, grid, dim3(kWalkThreads), lds, s, W, T, B, N_in, N_out, alpha, P, C, orp, oci,
-                     og, oeps, ocap, irp, ici, icap, D, eps_in);
+template <int NJ, bool DENSE>
+void launch_walk(dim3 grid, hipStream_t s, const float* W, int T, int B, int N_in, int N_out, float alpha, int P, int C,
+                 const int32_t* orp, const int32_t* oci, const float* og, const float* oeps, int64_t ocap,
+                 const int32_t* irp, const int32_t* ici, int64_t icap, const float* D, float* eps_in,
+                 const Gate& gate) {
+  hipLaunchKernelGGL((gin_walk<NJ, DENSE>), grid, dim3(kWalkThreads), 0, s, W, T, B, N_in, N_out, alpha, P, C, orp, oci,
+                     og, oeps, ocap, irp, ici, icap, D, eps_in, gate);
 }
 
 // The walk for layers whose outputs are a multiple of 4 (and more than 256): lane l holds
@@ -1212,13 +1226,14 @@ void launch_walk(dim3 grid, size_t lds, hipStream_t s, const float* W, int T, in
 // G[t] goes into delta through a per-wavefront LDS row: the step's output entries are stored
 // at their columns (one lane each, no two alike inside a row), every lane then takes its
 // columns with 16-byte reads (delta <- alpha delta + G) and the entries' columns are cleared
-// again. This replaces a register-indexed add per output entry.
-template <int NJ>
+// again. This replaces a register-indexed add per output entry. DENSE as for gin_walk.
+template <int NJ, bool DENSE>
 __global__ __launch_bounds__(kWalkThreads, NJ <= 16 ? 4 : 1) void gin_walk_x4(
     const float* __restrict__ W, int T, int B, int N_in, int N_out, float alpha, int P, int C,
     const int32_t* __restrict__ orp, const int32_t* __restrict__ oci, const float* __restrict__ og,
     const float* __restrict__ oeps, int64_t ocap, const int32_t* __restrict__ irp,
-    const int32_t* __restrict__ ici, int64_t icap, const float* __restrict__ D, float* __restrict__ eps_in) {
+    const int32_t* __restrict__ ici, int64_t icap, const float* __restrict__ D, float* __restrict__ eps_in, Gate gate) {
+  if (!gate_open(gate)) return;
   static_assert(NJ % 4 == 0, "whole 16-byte columns per lane");
   constexpr int NQ = NJ / 4;
   extern __shared__ float4 gq_all[];
@@ -1231,7 +1246,7 @@ __global__ __launch_bounds__(kWalkThreads, NJ <= 16 ? 4 : 1) void gin_walk_x4(
   for (int q = blockIdx.x * kWalkWaves + w; q < C * B; q += gridDim.x * kWalkWaves) {
     const int c = q / B;
     const int b = q - c * B;
-    float d[NJ];
+    typename std::conditional<DENSE, double, float>::type d[NJ];
 #pragma unroll
     for (int m = 0; m < NQ; ++m) {
       const int j = 4 * l + 4 * kWave * m;
@@ -1247,8 +1262,8 @@ __global__ __launch_bounds__(kWalkThreads, NJ <= 16 ? 4 : 1) void gin_walk_x4(
     int ia = 0, ib = 0, oa = 0, ob = 0;
     if (l < t_hi - t_lo) {
       const int r = (t_lo + l) * B + b;
-      ia = clamp_entry(irp[r], icap);
-      ib = clamp_entry(irp[r + 1], icap);
+      ia = DENSE ? 0 : clamp_entry(irp[r], icap);
+      ib = DENSE ? 0 : clamp_entry(irp[r + 1], icap);
       oa = clamp_entry(orp[r], ocap);
       ob = clamp_entry(orp[r + 1], ocap);
     }
@@ -1295,6 +1310,15 @@ __global__ __launch_bounds__(kWalkThreads, NJ <= 16 ? 4 : 1) void gin_walk_x4(
       vj = out_col(kn);
       ve = out_e(kn);
       vgg = out_gg(kn);
+      if (DENSE) {
+        float* dst = eps_in + ((size_t)(t_lo + k) * B + b) * N_out;
+#pragma unroll
+        for (int m = 0; m < NQ; ++m) {
+          const int j = 4 * l + 4 * kWave * m;
+          if (j < N_out)
+            *reinterpret_cast<float4*>(dst + j) = make_float4((float)d[4 * m], (float)d[4 * m + 1], (float)d[4 * m + 2], (float)d[4 * m + 3]);
+        }
+      }
       for (int e0 = i0; e0 < i1; e0 += kWave) {
         if (e0 > i0) vc = ici[min(e0 + l, i1 - 1)];  // entry e0 + l
         const int ne = min(kWave, i1 - e0);
@@ -1329,7 +1353,7 @@ __global__ __launch_bounds__(kWalkThreads, NJ <= 16 ? 4 : 1) void gin_walk_x4(
           for (int u = 0; u < kGinBatch; ++u) {
             acc[u] = 0.0f;
 #pragma unroll
-            for (int m = 0; m < NJ; ++m) acc[u] += wv[u][m] * d[m];  // d = 0 past N_out
+            for (int m = 0; m < NJ; ++m) acc[u] += wv[u][m] * (float)d[m];  // d = 0 past N_out
             acc[u] = iv[u] >= 0 ? acc[u] : 0.0f;
           }
           const float tot = wave_sum4(acc[0], acc[1], acc[2], acc[3]);
@@ -1371,13 +1395,14 @@ __global__ __launch_bounds__(kWalkThreads, NJ <= 16 ? 4 : 1) void gin_walk_x4(
   }
 }
 
-template <int NJ>
+template <int NJ, bool DENSE>
 void launch_walk_x4(dim3 grid, hipStream_t s, const float* W, int T, int B, int N_in, int N_out, float alpha, int P,
                     int C, const int32_t* orp, const int32_t* oci, const float* og, const float* oeps, int64_t ocap,
-                    const int32_t* irp, const int32_t* ici, int64_t icap, const float* D, float* eps_in) {
+                    const int32_t* irp, const int32_t* ici, int64_t icap, const float* D, float* eps_in,
+                    const Gate& gate) {
   const size_t lds = (size_t)kWalkWaves * NJ * kWave * sizeof(float);
-  hipLaunchKernelGGL(gin_walk_x4<NJ>, grid, dim3(kWalkThreads), lds, s, W, T, B, N_in, N_out, alpha, P, C, orp, oci,
-                     og, oeps, ocap, irp, ici, icap, D, eps_in);
+  hipLaunchKernelGGL((gin_walk_x4<NJ, DENSE>), grid, dim3(kWalkThreads), lds, s, W, T, B, N_in, N_out, alpha, P, C, orp,
+                     oci, og, oeps, ocap, irp, ici, icap, D, eps_in, gate);
 }
 
 }  // namespace
@@ -1421,6 +1446,23 @@ size_t dw_workspace(int T, int B, int N_in, int N_out, int64_t out_cap) {
   return std::max(dense, c.off);
 }
 
+// The spike gradient with many input entries: delta written densely by the walk, then delta W^T on the matrix
+// cores, read at the entries (gemm_split_kc_gather). An entry of the walk costs its W row's gather and dot,
+// measured 163 ps at 1024 outputs and 43 at 100 (26% active); the product runs at 70e12 multiply-adds a second
+// with its gather (N_in padded to 64, N_out to 32), 3 ps per entry and 3 ps per delta element. 3 x 1024 layers at
+// 27% active: 5.5 -> 2.4 ms per layer.
+int64_t gin_dense_least(int T, int B, int N_in, int N_out) {
+  const double TB = (double)T * B;
+  const double product_s = TB * (64.0 * ((N_in + 63) / 64)) * (32.0 * ((N_out + 31) / 32)) / 70e12 +
+                           TB * N_out * 3e-12 + 15e-6;
+  const double entry_s = N_out * 1.3e-13 + 27e-12;
+  return (int64_t)(1.1 * product_s / entry_s) + 1;
+}
+
+bool gin_dense_possible(int T, int B, int N_in, int N_out, int64_t in_cap) {
+  return N_out > 32 && in_cap >= gin_dense_least(T, B, N_in, N_out);
+}
+
 size_t gin_workspace(int T, int B, int N_out) {
   Carve c(nullptr);
   if (N_out <= kNarrowOut) {  // padded dense G and delta
@@ -1430,6 +1472,14 @@ size_t gin_workspace(int T, int B, int N_out) {
   }
   const WalkPlan wp = plan_walk(T);
   c.take<float>((size_t)wp.C * B * N_out);
+  return c.off;
+}
+
+// With room for the dense delta where the input side may hold enough entries for it.
+size_t gin_workspace_full(int T, int B, int N_in, int N_out, int64_t in_cap) {
+  Carve c(nullptr);
+  c.off = align256(gin_workspace(T, B, N_out));
+  if (gin_dense_possible(T, B, N_in, N_out, in_cap)) c.take<float>((size_t)T * B * N_out);
   return c.off;
 }
 
@@ -1664,7 +1714,8 @@ void enqueue_dw_spikes(const uint8_t* s_in, const float* ck, int K, float alpha,
 void enqueue_grad_in(const float* W, int T, int B, int N_in, int N_out, float alpha, const int32_t* out_row_ptr,
                      const int32_t* out_col_idx, const float* out_g, const float* eps_out, int64_t out_cap,
                      const int32_t* in_row_ptr, const int32_t* in_col_idx, int64_t in_cap, float* eps_in,
-                     bool share_cu, void* workspace, hipStream_t s, const float* g_dense = nullptr) {
+                     bool share_cu, void* workspace, size_t workspace_bytes, hipStream_t s,
+                     const float* g_dense = nullptr) {
   if (in_cap == 0) return;
   if (out_cap == 0) {  // no active output entry: delta = 0 everywhere
     fill_zero_async(eps_in, (size_t)in_cap, s);
@@ -1706,28 +1757,44 @@ void enqueue_grad_in(const float* W, int T, int B, int N_in, int N_out, float al
                      Lbuf);
   const int nj = (N_out + kWave - 1) / kWave;
   const dim3 walk_grid(share_cu ? std::min<unsigned>(wgrid.x, 2u * (unsigned)cu_count()) : wgrid.x);
-  if (nj > 4 && N_out % 4 == 0) {
-#define SNN_WALK4(NJ_)                                                                                        \
-  launch_walk_x4<NJ_>(walk_grid, s, W, T, B, N_in, N_out, alpha, wp.P, wp.C, out_row_ptr, out_col_idx, out_g, \
-                      eps_out, out_cap, in_row_ptr, in_col_idx, in_cap, Lbuf, eps_in)
-    if (nj <= 8) SNN_WALK4(8);
-    else if (nj <= 16) SNN_WALK4(16);
-    else if (nj <= 32) SNN_WALK4(32);
-    else SNN_WALK4(64);
-#undef SNN_WALK4
-    return;
+  // Entry by entry, or a dense product: the kernels decide by the input CSR's own count (in_cap is an upper
+  // bound of it), so both are enqueued where both are possible and the caller gave the room.
+  Gate few{}, many{};
+  float* delta = nullptr;
+  if (gin_dense_possible(T, B, N_in, N_out, in_cap) &&
+      workspace_bytes >= gin_workspace_full(T, B, N_in, N_out, in_cap)) {
+    const int64_t least = gin_dense_least(T, B, N_in, N_out);
+    few = Gate{in_row_ptr + (size_t)T * B, in_cap, least, true};
+    many = Gate{in_row_ptr + (size_t)T * B, in_cap, least, false};
+    delta = ws.take<float>((size_t)T * B * N_out);
   }
-#define SNN_WALK(NJ_)                                                                                             \
-  launch_walk<NJ_>(walk_grid, 0, s, W, T, B, N_in, N_out, alpha, wp.P, wp.C, out_row_ptr, out_col_idx, out_g, eps_out, \
-                   out_cap, in_row_ptr, in_col_idx, in_cap, Lbuf, eps_in)
-  if (nj <= 1) SNN_WALK(1);
-  else if (nj <= 2) SNN_WALK(2);
-  else if (nj <= 4) SNN_WALK(4);
-  else if (nj <= 8) SNN_WALK(8);
-  else if (nj <= 16) SNN_WALK(16);
-  else if (nj <= 32) SNN_WALK(32);
-  else SNN_WALK(64);
+#define SNN_WALK_ONE(LAUNCH, NJ_, DENSE_, OUT, GATE)                                                               \
+  LAUNCH<NJ_, DENSE_>(DENSE_ ? wgrid : walk_grid, s, W, T, B, N_in, N_out, alpha, wp.P, wp.C, out_row_ptr,         \
+                      out_col_idx, out_g, eps_out, out_cap, in_row_ptr, in_col_idx, in_cap, Lbuf, OUT, GATE)
+#define SNN_WALK(LAUNCH, NJ_)                                        \
+  do {                                                               \
+    SNN_WALK_ONE(LAUNCH, NJ_, false, eps_in, few);                   \
+    if (delta) SNN_WALK_ONE(LAUNCH, NJ_, true, delta, many);         \
+  } while (0)
+  if (nj > 4 && N_out % 4 == 0) {
+    if (nj <= 8) SNN_WALK(launch_walk_x4, 8);
+    else if (nj <= 16) SNN_WALK(launch_walk_x4, 16);
+    else if (nj <= 32) SNN_WALK(launch_walk_x4, 32);
+    else SNN_WALK(launch_walk_x4, 64);
+  } else {
+    if (nj <= 1) SNN_WALK(launch_walk, 1);
+    else if (nj <= 2) SNN_WALK(launch_walk, 2);
+    else if (nj <= 4) SNN_WALK(launch_walk, 4);
+    else if (nj <= 8) SNN_WALK(launch_walk, 8);
+    else if (nj <= 16) SNN_WALK(launch_walk, 16);
+    else if (nj <= 32) SNN_WALK(launch_walk, 32);
+    else SNN_WALK(launch_walk, 64);
+  }
 #undef SNN_WALK
+#undef SNN_WALK_ONE
+  if (delta)
+    gemm_split_kc_gather(T * B, N_in, N_out, delta, N_out, W, N_out, GatherOut{in_row_ptr, in_col_idx, in_cap, eps_in},
+                         many, s);
 }
 
 // common checks of the output-side CSR and its gradient
@@ -1823,6 +1890,11 @@ extern "C" size_t snn_sparse_grad_in_workspace(int T, int B, int N_out) {
   return gin_workspace(T, B, N_out);
 }
 
+extern "C" size_t snn_sparse_grad_in_workspace_full(int T, int B, int N_in, int N_out, int64_t in_cap) {
+  if (!dims_ok(T, B, N_in, N_out) || in_cap < 0) return 0;
+  return gin_workspace_full(T, B, N_in, N_out, in_cap);
+}
+
 extern "C" snn_status snn_sparse_grad_in(const float* W, int T, int B, int N_in, int N_out, float alpha,
                                          const int32_t* out_row_ptr, const int32_t* out_col_idx, const float* out_g,
                                          const float* eps_out, int64_t out_cap, const int32_t* in_row_ptr,
@@ -1834,13 +1906,19 @@ extern "C" snn_status snn_sparse_grad_in(const float* W, int T, int B, int N_in,
   if (!workspace || workspace_bytes < gin_workspace(T, B, N_out)) return SNN_ERR_INVALID_ARG;
   if (N_out > 4096) return SNN_ERR_UNSUPPORTED;
   enqueue_grad_in(W, T, B, N_in, N_out, alpha, out_row_ptr, out_col_idx, out_g, eps_out, out_cap, in_row_ptr,
-                  in_col_idx, in_cap, eps_in, share_cu != 0, workspace, static_cast<hipStream_t>(stream));
+                  in_col_idx, in_cap, eps_in, share_cu != 0, workspace, workspace_bytes, static_cast<hipStream_t>(stream));
   return launch_status();
 }
 
 extern "C" size_t snn_sparse_backward_workspace(int T, int B, int N_in, int N_out, int64_t out_cap) {
   if (!dims_ok(T, B, N_in, N_out) || out_cap < 0) return 0;
   return align256(dw_workspace(T, B, N_in, N_out, out_cap)) + gin_workspace(T, B, N_out);
+}
+
+extern "C" size_t snn_sparse_backward_workspace_full(int T, int B, int N_in, int N_out, int64_t out_cap,
+                                                     int64_t in_cap) {
+  if (!dims_ok(T, B, N_in, N_out) || out_cap < 0 || in_cap < 0) return 0;
+  return align256(dw_workspace(T, B, N_in, N_out, out_cap)) + gin_workspace_full(T, B, N_in, N_out, in_cap);
 }
 
 namespace {
@@ -1882,7 +1960,8 @@ extern "C" snn_status snn_sparse_backward(const float* W, const float* trace_in,
 
   hipStream_t s = static_cast<hipStream_t>(stream);
   char* dw_ws = static_cast<char*>(workspace);
-  char* gin_ws = dw_ws + align256(dw_workspace(T, B, N_in, N_out, out_cap));
+  const size_t dw_bytes = align256(dw_workspace(T, B, N_in, N_out, out_cap));
+  char* gin_ws = dw_ws + dw_bytes;
   const bool do_gin = grad_in && in_cap > 0;
   // A narrow layer's dense G is written once, at the front of the dW workspace, before the fork.
   const bool narrow_g = N_out <= kNarrowOut && out_cap > 0;
@@ -1905,7 +1984,7 @@ extern "C" snn_status snn_sparse_backward(const float* W, const float* trace_in,
     // CU (per product, a dW entry costs about 1.5 times a walk entry)
     const bool dw_longer = 3.0 * (double)out_cap * N_in >= 2.0 * (double)in_cap * N_out;
     enqueue_grad_in(W, T, B, N_in, N_out, alpha, out_row_ptr, out_col_idx, out_g, eps_out, out_cap, in_row_ptr,
-                    in_col_idx, in_cap, eps_in, sa != s && dw_longer, gin_ws, sa,
+                    in_col_idx, in_cap, eps_in, sa != s && dw_longer, gin_ws, workspace_bytes - dw_bytes, sa,
                     narrow_g ? reinterpret_cast<const float*>(dw_ws) : nullptr);
   }
   enqueue_dw(trace_in, T, B, N_in, N_out, out_row_ptr, out_col_idx, out_g, eps_out, out_cap, dW, dw_ws, s, narrow_g);

@@ -50,6 +50,8 @@ _SIGNATURES = {
     "snn_sparse_dw_spikes_workspace": (_SZ, [_I, _I, _I, _I, _I64, _I]),
     "snn_sparse_dw_spikes": (_I, [_P, _P, _I, _F, _I, _I, _I, _I, _P, _P, _P, _P, _I64, _P, _P, _SZ, _P]),
     "snn_sparse_grad_in_workspace": (_SZ, [_I, _I, _I]),
+    "snn_sparse_grad_in_workspace_full": (_SZ, [_I, _I, _I, _I, _I64]),
+    "snn_sparse_backward_workspace_full": (_SZ, [_I, _I, _I, _I, _I64, _I64]),
     "snn_sparse_grad_in": (_I, [_P, _I, _I, _I, _I, _F, _P, _P, _P, _P, _I64, _P, _P, _I64, _P, _I, _P, _SZ, _P]),
     "snn_dense_backward_workspace": (_SZ, [_I, _I, _I, _I]),
     "snn_dense_backward_ref": (_I, [_P, _P, _P, _P, _I, _I, _I, _I, _F, _F, _F, _F, _P, _P, _P, _SZ, _P]),
@@ -277,6 +279,14 @@ def snn_sparse_dw_spikes(s_in, ck, K, alpha, T, B, N_in, N_out, out_row_ptr, out
 
 def snn_sparse_grad_in_workspace(T, B, N_out) -> int:
     return int(lib().snn_sparse_grad_in_workspace(T, B, N_out))
+
+
+def snn_sparse_grad_in_workspace_full(T, B, N_in, N_out, in_cap) -> int:
+    return int(lib().snn_sparse_grad_in_workspace_full(T, B, N_in, N_out, int(in_cap)))
+
+
+def snn_sparse_backward_workspace_full(T, B, N_in, N_out, out_cap, in_cap) -> int:
+    return int(lib().snn_sparse_backward_workspace_full(T, B, N_in, N_out, int(out_cap), int(in_cap)))
 
 
 def snn_sparse_grad_in(W, T, B, N_in, N_out, alpha, out_row_ptr, out_col_idx, out_g, eps_out, out_cap, in_row_ptr,
@@ -509,7 +519,8 @@ def sparse_backward(W, trace_in, alpha, out: Csr, eps_out, inp: Optional[Csr] = 
     dW = torch.empty((N_in, N_out), dtype=torch.float32, device=dev)
     eps_in = torch.empty(inp.capacity, dtype=torch.float32, device=dev) if inp is not None else None
     if ws is None:
-        ws = workspace(snn_sparse_backward_workspace(T, B, N_in, N_out, out.capacity), dev)
+        ws = workspace(snn_sparse_backward_workspace_full(T, B, N_in, N_out, out.capacity,
+                                                          0 if inp is None else inp.capacity), dev)
     snn_sparse_backward(W, trace_in, T, B, N_in, N_out, alpha, out.row_ptr, out.col_idx, out.g, eps_out,
                         out.capacity, None if inp is None else inp.row_ptr, None if inp is None else inp.col_idx,
                         0 if inp is None else inp.capacity, eps_in, dW, ws, aux_stream=aux_stream)
@@ -559,7 +570,7 @@ def sparse_grad_in(W, alpha, T, B, out: Csr, eps_out, inp: Csr, share_cu=False, 
     if eps_in is None:
         eps_in = torch.empty(inp.capacity, dtype=torch.float32, device=dev)
     if ws is None:
-        ws = workspace(snn_sparse_grad_in_workspace(T, B, N_out), dev)
+        ws = workspace(snn_sparse_grad_in_workspace_full(T, B, N_in, N_out, inp.capacity), dev)
     snn_sparse_grad_in(W, T, B, N_in, N_out, alpha, out.row_ptr, out.col_idx, out.g, eps_out, out.capacity,
                        inp.row_ptr, inp.col_idx, inp.capacity, eps_in, share_cu, ws, stream)
     return eps_in

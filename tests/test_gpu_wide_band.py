@@ -64,3 +64,60 @@ def test_dw_wide_band_truncated():
     G[r[:cap], c[:cap]] = (eps * g[:cap]).astype(np.float64)
     tr = trace.reshape(T * B, n_in).astype(np.float64)
     assert (np.abs(dW.cpu().numpy() - tr.T @ G) <= 4 * U * (tr.T @ np.abs(G))).all()
+
+
+def _grad_in_reference(T, B, W, G, alpha):
+    d = np.zeros((T, B, W.shape[1]))
+    G = G.reshape(T, B, -1)
+    for t in range(T - 1, 0, -1):
+        d[t - 1] = alpha * d[t] + G[t]
+    return d.reshape(T * B, -1) @ W.astype(np.float64).T
+
+
+# share_in on both sides of the count from which the product runs; output widths at the ends of a K stage
+# and of its 256-wide slices, input widths at a tile's ends, rows that do not fill a tile
+@pytest.mark.parametrize("T,B,n_in,n_out,share_out,share_in,spare", [
+    (30, 20, 900, 300, 0.3, 0.95, 0), (30, 20, 900, 300, 0.3, 0.2, 500000), (129, 5, 1025, 257, 0.1, 0.9, 1000),
+    (3, 427, 640, 256, 0.5, 0.9, 0), (7, 91, 897, 100, 0.9, 1.0, 3), (64, 20, 700, 35, 0.9, 0.95, 0),
+    (2, 300, 1024, 1024, 0.2, 0.9, 0), (11, 61, 1000, 770, 0.02, 0.9, 0)])
+def test_grad_in_wide_band(T, B, n_in, n_out, share_out, share_in, spare):
+    rng = np.random.default_rng(n_in * 7 + n_out)
+    on_o, g, out, pad_o = _csr(rng, T, B, n_out, share_out)
+    on_i, _, inp, _ = _csr(rng, T, B, n_in, share_in, spare)
+    eps = rng.standard_normal(len(g)).astype(np.float32)
+    W = rng.standard_normal((n_in, n_out)).astype(np.float32)
+    alpha = float(np.float32(np.exp(-0.1)))
+    e_in = torch.full((inp.capacity,), 7.0, device="cuda")
+    snn.sparse_grad_in(torch.from_numpy(W).cuda(), alpha, T, B, out, torch.from_numpy(pad_o(eps, np.float32(0))).cuda(),
+                       inp, eps_in=e_in)
+    G = np.zeros(on_o.shape)
+    G[on_o] = (eps * g).astype(np.float64)
+    r, a = (_grad_in_reference(T, B, x, y, alpha)[on_i] for x, y in ((W, G), (np.abs(W), np.abs(G))))
+    got = e_in.cpu().numpy()
+    # float32 recurrence (2 roundings a step, over 1 / (1 - alpha) steps) and sums (8 roundings of the leading
+    # sum per 64 terms, 2^-24 left out of each product; a wavefront's dot product below the count: 24 roundings)
+    assert (np.abs(got[:len(r)] - r) <= (2 * 11 + 24 + 4) * U * a).all()
+    assert (got[len(r):] == 7.0).all()  # slots without an entry stay as they are
+
+
+def test_grad_in_wide_band_truncated_and_columns_outside():
+    """Entries past the input capacity are not written; an entry with a column outside the layer reads 0."""
+    T, B, n_in, n_out = 30, 20, 900, 300
+    rng = np.random.default_rng(11)
+    on_o, g, out, _ = _csr(rng, T, B, n_out, 0.2)
+    on_i, _, inp, _ = _csr(rng, T, B, n_in, 0.99)
+    eps = rng.standard_normal(len(g)).astype(np.float32)
+    W = rng.standard_normal((n_in, n_out)).astype(np.float32)
+    col = inp.col_idx.clone()
+    rp = inp.row_ptr.cpu().numpy()
+    first, last = int(rp[5]), int(rp[9]) - 1  # the first entry of row 5, the last of row 8
+    col[first], col[last] = -3, n_in + 2
+    cap = inp.capacity - 5000
+    cut = snn.Csr(inp.row_ptr, col[:cap].contiguous(), None, None, cap)
+    e_in = snn.sparse_grad_in(torch.from_numpy(W).cuda(), 0.9, T, B, out, torch.from_numpy(eps).cuda(), cut)
+    G = np.zeros(on_o.shape)
+    G[on_o] = (eps * g).astype(np.float64)
+    alpha = float(np.float32(0.9))
+    r, a = (_grad_in_reference(T, B, x, y, alpha)[on_i][:cap] for x, y in ((W, G), (np.abs(W), np.abs(G))))
+    r[[first, last]] = 0.0
+    assert (np.abs(e_in.cpu().numpy() - r) <= 45 * U * a).all()
