@@ -121,3 +121,32 @@ def test_grad_in_wide_band_truncated_and_columns_outside():
     r, a = (_grad_in_reference(T, B, x, y, alpha)[on_i][:cap] for x, y in ((W, G), (np.abs(W), np.abs(G))))
     r[[first, last]] = 0.0
     assert (np.abs(e_in.cpu().numpy() - r) <= 45 * U * a).all()
+
+
+# many bits per window (placed a lane per column) and few, rows of part windows, of 64 windows and of more,
+# tiles that mix both, a capacity in the middle
+@pytest.mark.parametrize("T,B,N,share,cut", [
+    (7, 5, 33, 0.9, 0), (40, 30, 64, 0.5, 0), (50, 26, 200, 0.3, 0), (20, 33, 300, 0.95, 100), (9, 11, 1024, 1.0, 0),
+    (3, 7, 4096, 0.3, 0), (3, 5, 4500, 0.4, 5000), (60, 40, 130, -1.0, 0), (1, 1, 1, 1.0, 0)])
+def test_compact_bits_wide_band(T, B, N, share, cut):
+    rng = np.random.default_rng(N)
+    V = rng.random((T, B, N)).astype(np.float32)
+    if share < 0:  # activity that changes along time: tiles of either kind
+        on = rng.random((T, B, N)) < np.linspace(0, 1, T)[:, None, None]
+    else:
+        on = rng.random((T, B, N)) < share
+    W64 = (B * N + 63) // 64
+    pad = np.zeros((T, W64 * 64), np.uint8)
+    pad[:, :B * N] = on.reshape(T, -1)
+    words = np.packbits(pad, axis=1, bitorder="little").view(np.int64).reshape(-1)
+    n = int(on.sum())
+    cap = max(n - cut, 1)
+    csr = snn.active_compact_bits(torch.from_numpy(words.copy()).cuda(), torch.from_numpy(V).cuda(), 1.0, 100.0, cap)
+    flat = on.reshape(T * B, N)
+    assert csr.nnz() == n
+    assert np.array_equal(csr.row_ptr.cpu().numpy(), np.concatenate([[0], np.cumsum(flat.sum(1))]))
+    m = min(n, cap)
+    assert np.array_equal(csr.col_idx.cpu().numpy()[:m], np.nonzero(flat)[1][:m])
+    d = np.abs(V[on][:m] - np.float32(1.0))
+    x = np.float32(100.0) * d + np.float32(1.0)
+    assert (np.abs(csr.g.cpu().numpy()[:m] - 1.0 / (x * x)) <= 4 * U / (x * x)).all()
