@@ -384,6 +384,17 @@ snn_status snn_maxpool_spikes(const uint8_t* S, int T, int B, int H, int W, int 
                               void* stream);
 
 /*
+ * snn_conv_lif_forward and snn_maxpool_spikes in one call (H, W even), with the trace of the pooled spikes that a
+ * layer on them reads as its input trace: trace_pool [T,B,(H/2)*(W/2)*F] float32 (written unless NULL),
+ * trace_pool[0] = 0, trace_pool[t+1] = alpha_next*trace_pool[t] + P[t], bit-identical to the trace_in that a
+ * forward of that layer writes; alpha_next in (0,1], checked only with trace_pool. All outputs as the two calls'.
+ */
+snn_status snn_conv_lif_forward_pool(const uint8_t* s_in, const float* Wc, int T, int B, int H, int W, int C, int F,
+                                     float alpha, float theta, float b_th, float* V, uint8_t* s_out,
+                                     float* trace_in, uint64_t* active_bits, uint8_t* P, uint8_t* arg,
+                                     float* trace_pool, float alpha_next, void* stream);
+
+/*
  * The pooled layer's share of the active set: pooled neuron (t, b, np) is active iff the conv
  * neuron its pooling picked (arg) is active in conv_bits. Both bitsets in the layout of
  * snn_lif_forward_active (N = H*W*F for conv_bits, (H/2)*(W/2)*F for pool_bits, written).

@@ -185,6 +185,116 @@ __global__ __launch_bounds__(kGatherWaves * kWave) void lif_gather(const uint8_t
   }
 }
 
+// lif_gather for layers of at most 32 outputs (readouts): a wavefront takes 64 / L rows, L lanes each (lane =
+// column), so that one W load serves 64 / L rows; with a row per wavefront most lanes have no column. The L lanes
+// of a row read LB of its bytes each, place the spiking inputs in the row's list by a scan over the lanes, and
+// the lists are summed (ascending, kNarrowKb rows of W in flight) when one may overflow and at the end. Same
+// sums in the same order as lif_gather. Bound: latency of the W rows, a list's length over kNarrowKb round
+// trips. 12544 -> 10, T = 100, B = 256 (2349
+// spikes in the longest row): 461 -> 150 us.
+constexpr int kNarrowCols = 32;
+constexpr int kNarrowFull = 512;  // entries from which a row's list is summed before more inputs are read
+constexpr int kNarrowKb = 16;
+
+template <int LB>
+struct Bytes;
+template <>
+struct Bytes<4> { typedef uint32_t type; };
+template <>
+struct Bytes<8> { typedef uint2 type; };
+template <>
+struct Bytes<16> { typedef uint4 type; };
+
+template <int LB, int L>
+__global__ __launch_bounds__(kGatherWaves * kWave) void lif_gather_narrow(const uint8_t* __restrict__ s_in,
+                                                                          const float* __restrict__ W, int T, int B,
+                                                                          int N_in, int N_out, float* __restrict__ V) {
+  constexpr int kRowsPerWave = kWave / L;
+  constexpr int kCap = kNarrowFull + L * LB;
+  constexpr int kAheadLoads = 4;
+  static_assert(kCap % kNarrowKb == 0 && kNarrowKb % 8 == 0, "lists of whole batches, batches of whole 16-byte reads");
+  __shared__ __attribute__((aligned(16))) uint16_t lists[kGatherWaves * kRowsPerWave][kCap];
+  const int w = threadIdx.x / kWave;
+  const int l = lane_id();
+  const int g = l / L, li = l % L;
+  const long rows = (long)(T - 1) * B;
+  // a wavefront's rows lie a quarter (half) of the rows apart: activity clusters in time, and a wavefront takes as
+  // long as its longest list
+  const long wave_rows = (long)gridDim.x * kGatherWaves;
+  const long r = (long)g * wave_rows + (long)blockIdx.x * kGatherWaves + w;
+  const bool live = r < rows;
+  const uint8_t* row = s_in + (size_t)(live ? r : 0) * N_in;
+  uint16_t* lst = lists[w * kRowsPerWave + g];
+  const int col = min(li, N_out - 1);
+  float acc = 0.0f;
+  int cnt = 0;  // entries in the row's list
+  auto sum_list = [&]() {
+    __builtin_amdgcn_wave_barrier();
+    for (int k = 0; __ballot(k < cnt); k += kNarrowKb) {
+      // eight entries a read (past the list: anything, clamped into W and not added)
+      uint16_t i[kNarrowKb];
+      const uint4* e = reinterpret_cast<const uint4*>(lst + min(k, kCap - kNarrowKb));
+#pragma unroll
+      for (int u = 0; u < kNarrowKb / 8; ++u) {
+        const uint4 x = e[u];
+        __builtin_memcpy(i + 8 * u, &x, sizeof(x));
+      }
+      float wv[kNarrowKb];
+#pragma unroll
+      for (int u = 0; u < kNarrowKb; ++u) wv[u] = W[(size_t)min((int)i[u], N_in - 1) * N_out + col];
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int u = 0; u < kNarrowKb; ++u) acc = k + u < cnt ? __fadd_rn(acc, wv[u]) : acc;
+    }
+    cnt = 0;
+    __builtin_amdgcn_wave_barrier();
+  };
+  typedef typename Bytes<LB>::type Piece;
+  for (int i0 = 0; i0 < N_in; i0 += kAheadLoads * L * LB) {
+    uint32_t x[kAheadLoads][LB / 4];
+#pragma unroll
+    for (int u = 0; u < kAheadLoads; ++u) {
+      const int i = i0 + (u * L + li) * LB;  // N_in is a multiple of LB: a piece is in the row or past it
+      const bool in = live && i < N_in;
+      const Piece p = *reinterpret_cast<const Piece*>(row + (in ? i : 0));
+      __builtin_memcpy(x[u], &p, LB);
+#pragma unroll
+      for (int q = 0; q < LB / 4; ++q) x[u][q] = in ? x[u][q] : 0u;
+    }
+#pragma unroll
+    for (int u = 0; u < kAheadLoads; ++u) {
+      uint32_t mask = 0;  // bit k: byte k of the piece is a spike
+#pragma unroll
+      for (int q = 0; q < LB / 4; ++q) {
+        const uint32_t y = x[u][q];
+        const uint32_t high = ((((y & 0x7f7f7f7fu) + 0x7f7f7f7fu) | y) >> 7) & 0x01010101u;
+        mask |= ((high * 0x01020408u) >> 24 & 0xfu) << (4 * q);
+      }
+      if (__ballot(mask != 0) == 0) continue;
+      const int n = __popc(mask);
+      int incl = n;  // inclusive scan over the row's lanes
+      incl += __builtin_amdgcn_update_dpp(0, incl, 0x111, 0xf, 0xf, true);  // row_shr:1
+      incl += __builtin_amdgcn_update_dpp(0, incl, 0x112, 0xf, 0xf, true);  // row_shr:2
+      incl += __builtin_amdgcn_update_dpp(0, incl, 0x114, 0xf, 0xf, true);  // row_shr:4
+      incl += __builtin_amdgcn_update_dpp(0, incl, 0x118, 0xf, 0xf, true);  // row_shr:8
+      if (L == 32) {
+        const int low = __shfl(incl, (l & ~31) + 15, kWave);
+        incl += li >= 16 ? low : 0;
+      }
+      int pos = cnt + incl - n;
+      const int ib = i0 + (u * L + li) * LB;
+      while (mask) {
+        lst[pos++] = (uint16_t)(ib + __builtin_ctz(mask));
+        mask &= mask - 1u;
+      }
+      cnt += __shfl(incl, (l & ~(L - 1)) + L - 1, kWave);
+      if (__ballot(cnt > kNarrowFull)) sum_list();
+    }
+  }
+  sum_list();
+  if (live && li < N_out) V[(size_t)(r + B) * N_out + li] = acc;
+}
+
 // The input trace of input k = b * N_in + i over the whole time axis: trace[0] = 0,
 // trace[t+1] = alpha trace[t] + S_in[t] (loads kScanAhead steps ahead). One input per lane, not
 // four: four times the wavefronts for the same bytes, so that more of them overlap their load and
@@ -645,6 +755,215 @@ __global__ __launch_bounds__(kScanThreads) void conv_scan(const uint8_t* __restr
   if (valid) s_out[(size_t)(T - 1) * step + k] = (uint8_t)(v > theta);
 }
 
+// The convolutional layer a 2x2 pooling window at a time, for F a multiple of 64, C in {1, 2, 4} and even H, W: a
+// wavefront owns a window's four pixels x 64 filters, lane = (pixel column dx, filter pair), the two pixel rows in
+// registers. Same operations in the same order as conv_scan. A step's 4 x 4 x C patch serves all four pixels (one
+// ballot per 64 bytes, the next kPoolSteps steps' bytes in flight), the filters are read from LDS, V leaves in
+// 512-byte and the spikes in 128-byte runs. With P != NULL the window's pooled spikes, picks and (with trace_pool)
+// the pooled spikes' trace with leak alpha_next are written from the spikes in registers, so that pooling and
+// trace read nothing back: the ballot of (row dy, filter parity q) holds the spikes of both pixel columns, and
+// lane l takes pooled filter l. Bound: HBM stores (28 x 28 x 64, T = 100, B = 256: 8.4 GB).
+// Whole forward there 3.43 -> 1.88 ms: conv_scan 2.18, pooling 0.39 and the pooled trace 0.33 ms before, this
+// kernel 1.72 (2.33 with blocks in launch order and plain stores, 1.97 with the XCD order, 1.78 with V and the
+// trace streamed past L2).
+constexpr int kPoolSteps = 8;
+typedef float Pair __attribute__((ext_vector_type(2)));
+constexpr size_t kPoolLds = 32 * 1024;
+
+// Every bit of a uniform word twice: bit i goes to bits 2 i and 2 i + 1.
+__device__ __forceinline__ uint64_t twice(uint32_t x) {
+  uint64_t r;
+  asm("s_bitreplicate_b64_b32 %0, %1" : "=s"(r) : "s"(x));
+  return r;
+}
+
+template <int C>
+__global__ __launch_bounds__(kScanThreads) void conv_pool_scan(
+    const uint8_t* __restrict__ s_in, const float* __restrict__ Wc, int T, int B, int H, int W, int F, int n_waves,
+    float alpha, float theta, float b_th, float* __restrict__ V, uint8_t* __restrict__ s_out,
+    uint64_t* __restrict__ bits, uint8_t* __restrict__ P, uint8_t* __restrict__ arg, float* __restrict__ trace_pool,
+    float alpha_next) {
+  extern __shared__ __attribute__((aligned(16))) float wl[];  // [9 C][F]
+  for (int k = threadIdx.x; k < 9 * C * F; k += kScanThreads) wl[k] = Wc[k];
+  __syncthreads();
+  constexpr int kPatch = 16 * C;                         // bytes of a step's patch
+  constexpr int kWords = kPoolSteps * kPatch / kWave;    // ballots per group of steps
+  // Blocks are dealt to the 8 XCDs in turn: each XCD takes one contiguous eighth of the windows, so that lines
+  // shared by neighbouring windows (bitset words, pooled spikes) fill up in one L2.
+  const int nb = gridDim.x;
+  const int block = nb % 8 == 0 ? (int)(blockIdx.x & 7) * (nb / 8) + (int)(blockIdx.x >> 3) : (int)blockIdx.x;
+  const int wave = __builtin_amdgcn_readfirstlane(block * (kScanThreads / kWave) + threadIdx.x / kWave);
+  if (wave >= n_waves) return;
+  const int l = lane_id();
+  const int fgs = F / kWave, hw = W / 2;
+  const int fg = wave % fgs;
+  const int win = wave / fgs;  // (b * H/2 + py) * W/2 + px
+  const int px = win % hw;
+  const int py = (win / hw) % (H / 2);
+  const int b = win / (hw * (H / 2));
+  const int dx = l >> 5, pair = l & 31;
+  const int f0 = fg * kWave + 2 * pair;
+  const size_t N = (size_t)H * W * F, step = (size_t)B * N, pstep = step / 4;
+  const size_t W64 = step / kWave;  // F is a multiple of 64: whole words per pixel
+  // offsets inside a step: the lane's neurons of row dy, its pooled neuron, the word of pixel (l >> 1, l & 1)
+  const size_t pix0 = (size_t)b * H * W + (size_t)(2 * py) * W + 2 * px;
+  const size_t base = pix0 * F;
+  const int off0 = dx * F + f0, off1 = off0 + W * F;
+  const size_t pbase = (size_t)win * F + fg * kWave;
+  const size_t word0 = pix0 * fgs + fg;
+  const int woff = ((l >> 1) & 1) * W * fgs + (l & 1) * fgs;
+  const size_t in_step = (size_t)B * H * W * C;
+  const uint8_t* xb = s_in + (size_t)b * H * W * C;
+  // byte of word i that this lane loads: step and place in the patch
+  int lstep[kWords], loff[kWords];
+  bool lin[kWords];
+#pragma unroll
+  for (int i = 0; i < kWords; ++i) {
+    const int id = i * kWave + l;
+    lstep[i] = id / kPatch;
+    const int q = id % kPatch;
+    const int yy = 2 * py - 1 + q / (4 * C), xx = 2 * px - 1 + (q / C) % 4;
+    lin[i] = yy >= 0 && yy < H && xx >= 0 && xx < W;
+    loff[i] = lin[i] ? (yy * W + xx) * C + q % C : 0;
+  }
+  auto load = [&](uint32_t (&x)[kWords], int t0) {
+#pragma unroll
+    for (int i = 0; i < kWords; ++i) {
+      const int t = t0 + lstep[i];
+      x[i] = (lin[i] && t < T - 1) ? xb[(size_t)t * in_step + loff[i]] : 0u;
+    }
+  };
+  float v[2][2] = {{0.0f, 0.0f}, {0.0f, 0.0f}};
+  float tr = 0.0f;
+  auto put_v = [&](int t) {
+    float* Vt = V + (size_t)t * step + base;
+    // V and the trace are not read again soon and need not take the place of the other lines in L2
+    __builtin_nontemporal_store(Pair{v[0][0], v[0][1]}, reinterpret_cast<Pair*>(Vt + off0));
+    __builtin_nontemporal_store(Pair{v[1][0], v[1][1]}, reinterpret_cast<Pair*>(Vt + off1));
+    if (bits) {
+      uint64_t word[4];  // pixel (dy, dx): bit 2 pair + q from lane (dx, pair) of ballot (dy, q)
+#pragma unroll
+      for (int dy = 0; dy < 2; ++dy) {
+        const uint64_t a0 = __ballot(fabsf(v[dy][0] - theta) < b_th), a1 = __ballot(fabsf(v[dy][1] - theta) < b_th);
+#pragma unroll
+        for (int x = 0; x < 2; ++x)
+          word[2 * dy + x] =
+              (twice((uint32_t)(a0 >> (32 * x))) & 0x5555555555555555ull) |
+              (twice((uint32_t)(a1 >> (32 * x))) & 0xAAAAAAAAAAAAAAAAull);
+      }
+      const uint64_t mine = l == 0 ? word[0] : (l == 1 ? word[1] : (l == 2 ? word[2] : word[3]));
+      if (l < 4) bits[(size_t)t * W64 + word0 + woff] = mine;
+    }
+  };
+  // spikes of step t (and what pooling makes of them); returns them for the recurrence
+  auto put_spikes = [&](int t, bool (&sp)[2][2]) {
+#pragma unroll
+    for (int dy = 0; dy < 2; ++dy)
+#pragma unroll
+      for (int q = 0; q < 2; ++q) sp[dy][q] = v[dy][q] > theta;
+    uint8_t* St = s_out + (size_t)t * step + base;
+    __builtin_nontemporal_store((uint16_t)((sp[0][0] ? 1 : 0) | (sp[0][1] ? 256 : 0)), reinterpret_cast<uint16_t*>(St + off0));
+    __builtin_nontemporal_store((uint16_t)((sp[1][0] ? 1 : 0) | (sp[1][1] ? 256 : 0)), reinterpret_cast<uint16_t*>(St + off1));
+    if (P) {
+      const uint64_t m00 = __ballot(sp[0][0]), m01 = __ballot(sp[0][1]);
+      const uint64_t m10 = __ballot(sp[1][0]), m11 = __ballot(sp[1][1]);
+      const uint64_t r0 = l & 1 ? m01 : m00, r1 = l & 1 ? m11 : m10;
+      const int k = l >> 1;  // pooled filter l: parity l % 2, pair l / 2
+      const bool s0 = ((uint32_t)r0 >> k) & 1u, s1 = ((uint32_t)(r0 >> 32) >> k) & 1u;
+      const bool s2 = ((uint32_t)r1 >> k) & 1u, s3 = ((uint32_t)(r1 >> 32) >> k) & 1u;
+      const bool any = s0 || s1 || s2 || s3;
+      P[(size_t)t * pstep + pbase + l] = (uint8_t)any;
+      arg[(size_t)t * pstep + pbase + l] = (uint8_t)(s0 ? 0 : (s1 ? 1 : (s2 ? 2 : (s3 ? 3 : 0))));
+      if (trace_pool && t + 1 < T) {
+        tr = __fadd_rn(__fmul_rn(alpha_next, tr), any ? 1.0f : 0.0f);
+        __builtin_nontemporal_store(tr, trace_pool + (size_t)(t + 1) * pstep + pbase + l);
+      }
+    }
+  };
+  put_v(0);
+  if (P && trace_pool) trace_pool[pbase + l] = 0.0f;
+  uint32_t cur[kWords], nxt[kWords];
+  load(cur, 0);
+  for (int t0 = 0; t0 < T - 1; t0 += kPoolSteps) {
+    load(nxt, t0 + kPoolSteps);
+    uint64_t m[kWords];
+#pragma unroll
+    for (int i = 0; i < kWords; ++i) m[i] = __ballot(cur[i] != 0);
+#pragma unroll
+    for (int s = 0; s < kPoolSteps; ++s) {
+      const int t = t0 + s;
+      if (t < T - 1) {
+        const uint64_t patch = kPatch == 64 ? m[s * kPatch / kWave]
+                                            : (m[s * kPatch / kWave] >> (s * kPatch % kWave)) & ((1ull << (kPatch % 64)) - 1ull);
+        float in[2][2] = {{0.0f, 0.0f}, {0.0f, 0.0f}};
+        if (patch) {  // uniform: most steps of a window see no spike
+          uint64_t taps[2];
+#pragma unroll
+          for (int dy = 0; dy < 2; ++dy) {
+            taps[dy] = 0;
+#pragma unroll
+            for (int r = 0; r < 3; ++r)
+              taps[dy] |= ((patch >> (((dy + r) * 4 + dx) * C)) & ((1ull << (3 * C)) - 1ull)) << (3 * C * r);
+          }
+          while (__ballot((taps[0] | taps[1]) != 0)) {
+#pragma unroll
+            for (int dy = 0; dy < 2; ++dy) {
+              if (taps[dy]) {
+                const float2 wv = *reinterpret_cast<const float2*>(wl + (int)__builtin_ctzll(taps[dy]) * F + f0);
+                in[dy][0] = __fadd_rn(in[dy][0], wv.x);
+                in[dy][1] = __fadd_rn(in[dy][1], wv.y);
+                taps[dy] &= taps[dy] - 1ull;
+              }
+            }
+          }
+        }
+        bool sp[2][2];
+        put_spikes(t, sp);
+#pragma unroll
+        for (int dy = 0; dy < 2; ++dy)
+#pragma unroll
+          for (int q = 0; q < 2; ++q)
+            v[dy][q] = __fadd_rn(__fadd_rn(__fmul_rn(alpha, v[dy][q]), in[dy][q]), sp[dy][q] ? -1.0f : -0.0f);
+        put_v(t + 1);
+      }
+    }
+#pragma unroll
+    for (int i = 0; i < kWords; ++i) cur[i] = nxt[i];
+  }
+  bool sp[2][2];
+  put_spikes(T - 1, sp);
+}
+
+// Whether conv_pool_scan takes the layer (its V and spike stores are 8 and 2 bytes wide).
+bool conv_pool_ok(int H, int W, int C, int F, const float* V, const uint8_t* s_out) {
+  return F % kWave == 0 && (C == 1 || C == 2 || C == 4) && H % 2 == 0 && W % 2 == 0 &&
+         (size_t)9 * C * F * sizeof(float) <= kPoolLds && reinterpret_cast<uintptr_t>(V) % 8 == 0 &&
+         reinterpret_cast<uintptr_t>(s_out) % 2 == 0;
+}
+
+void launch_conv_pool(const uint8_t* s_in, const float* Wc, int T, int B, int H, int W, int C, int F, float alpha,
+                      float theta, float b_th, float* V, uint8_t* s_out, uint64_t* bits, uint8_t* P, uint8_t* arg,
+                      float* trace_pool, float alpha_next, hipStream_t s) {
+  const int waves = B * (H / 2) * (W / 2) * (F / kWave);
+  const int blocks = (waves + kScanThreads / kWave - 1) / (kScanThreads / kWave);
+  const dim3 g((unsigned)(blocks >= 64 ? (blocks + 7) / 8 * 8 : blocks));  // whole eighths (see the kernel)
+  const size_t lds = (size_t)9 * C * F * sizeof(float);
+#define SNN_CP(C_)                                                                                                \
+  hipLaunchKernelGGL(conv_pool_scan<C_>, g, dim3(kScanThreads), lds, s, s_in, Wc, T, B, H, W, F, waves, alpha, theta, \
+                     b_th, V, s_out, bits, P, arg, trace_pool, alpha_next)
+  if (C == 1) SNN_CP(1);
+  else if (C == 2) SNN_CP(2);
+  else SNN_CP(4);
+#undef SNN_CP
+}
+
+// The trace of spikes [T,B,N] alone (lif_scan's trace blocks).
+void launch_trace(const uint8_t* s_in, int T, int B, int N, float alpha, float* trace, hipStream_t s) {
+  const int nt = (int)(((size_t)B * N + kScanThreads - 1) / kScanThreads);
+  hipLaunchKernelGGL(lif_scan, dim3((unsigned)nt), dim3(kScanThreads), 0, s, s_in, T, B, N, 1, alpha, 0.0f, 0.0f,
+                     nullptr, nullptr, trace, nullptr, 1.0f, nullptr, 0);
+}
+
 snn_status lif_forward_impl(const uint8_t* s_in, const float* W, int T, int B, int N_in, int N_out, float alpha,
                             float theta, float b_th, float* V, uint8_t* s_out, float* trace_in, float* trace_out,
                             float alpha_next, uint64_t* bits, void* stream) {
@@ -696,7 +1015,22 @@ snn_status lif_forward_impl(const uint8_t* s_in, const float* W, int T, int B, i
                    (reinterpret_cast<uintptr_t>(V) % 16) == 0;
   const int NQ = (N_out + 4 * kWave - 1) / (4 * kWave);
   const long rows = (long)(T - 1) * B;
-  if (rows > 0) {
+  const auto multiple = [&](int b) { return N_in % b == 0 && reinterpret_cast<uintptr_t>(s_in) % b == 0; };
+  if (rows > 0 && N_out <= kNarrowCols && multiple(4) && N_in <= 65536) {
+    const int lanes = N_out <= 16 ? 16 : 32;
+    const int per_block = kGatherWaves * (kWave / lanes);
+    const dim3 g((unsigned)((rows + per_block - 1) / per_block));
+#define SNN_GN(LB, L)                                                                                             \
+  hipLaunchKernelGGL((lif_gather_narrow<LB, L>), g, dim3(kGatherWaves * kWave), 0, s, s_in, W, T, B, N_in, N_out, V)
+    if (multiple(16)) {
+      if (lanes == 16) SNN_GN(16, 16); else SNN_GN(16, 32);
+    } else if (multiple(8)) {
+      if (lanes == 16) SNN_GN(8, 16); else SNN_GN(8, 32);
+    } else {
+      if (lanes == 16) SNN_GN(4, 16); else SNN_GN(4, 32);
+    }
+#undef SNN_GN
+  } else if (rows > 0) {
     const dim3 g((unsigned)((rows + kGatherWaves - 1) / kGatherWaves));
     if (al && vec) launch_gather<true, true>(NQ, g, s, s_in, W, T, B, N_in, N_out, V);
     else if (al) launch_gather<true, false>(NQ, g, s, s_in, W, T, B, N_in, N_out, V);
@@ -740,9 +1074,12 @@ extern "C" snn_status snn_lif_forward_traces(const uint8_t* s_in, const float* W
                           active_bits, stream);
 }
 
-extern "C" snn_status snn_conv_lif_forward(const uint8_t* s_in, const float* Wc, int T, int B, int H, int W, int C,
-                                           int F, float alpha, float theta, float b_th, float* V, uint8_t* s_out,
-                                           float* trace_in, uint64_t* active_bits, void* stream) {
+namespace {
+
+// snn_conv_lif_forward, and with P the pooling and the pooled trace.
+snn_status conv_forward_impl(const uint8_t* s_in, const float* Wc, int T, int B, int H, int W, int C, int F, float alpha,
+                             float theta, float b_th, float* V, uint8_t* s_out, float* trace_in, uint64_t* active_bits,
+                             uint8_t* P, uint8_t* arg, float* trace_pool, float alpha_next, void* stream) {
   if (!s_in || !Wc || !V || !s_out) return SNN_ERR_INVALID_ARG;
   if (bad_dim(T) || bad_dim(B) || bad_dim(H) || bad_dim(W) || bad_dim(C) || bad_dim(F)) return SNN_ERR_INVALID_ARG;
   if ((int64_t)H * W * F >= ((int64_t)1 << 31) || (int64_t)H * W * C >= ((int64_t)1 << 31)) return SNN_ERR_INVALID_ARG;
@@ -750,18 +1087,43 @@ extern "C" snn_status snn_conv_lif_forward(const uint8_t* s_in, const float* Wc,
   if (bad_alpha(alpha) || isnan(theta)) return SNN_ERR_INVALID_ARG;
   if (active_bits && (isnan(b_th) || b_th < 0.0f)) return SNN_ERR_INVALID_ARG;
   hipStream_t s = static_cast<hipStream_t>(stream);
-  const int nv = (int)(((size_t)B * H * W * F + kScanThreads - 1) / kScanThreads);
-  if (F % kWave == 0 && 9 * C <= kWave)  // a wavefront's lanes are the filters of one pixel
-    hipLaunchKernelGGL(conv_scan<true>, dim3((unsigned)nv), dim3(kScanThreads), 0, s, s_in, Wc, T, B, H, W, C, F, alpha,
-                       theta, b_th, V, s_out, active_bits);
-  else
-    hipLaunchKernelGGL(conv_scan<false>, dim3((unsigned)nv), dim3(kScanThreads), 0, s, s_in, Wc, T, B, H, W, C, F,
-                       alpha, theta, b_th, V, s_out, active_bits);
-  if (trace_in) {  // the input trace: lif_scan's trace blocks alone
-    const int N_in = H * W * C;
-    const int nt = (int)(((size_t)B * N_in + kScanThreads - 1) / kScanThreads);
-    hipLaunchKernelGGL(lif_scan, dim3((unsigned)nt), dim3(kScanThreads), 0, s, s_in, T, B, N_in, 1, alpha, theta,
-                       b_th, nullptr, nullptr, trace_in, nullptr, 1.0f, nullptr, 0);
+  const bool fused = conv_pool_ok(H, W, C, F, V, s_out);
+  if (fused) {
+    launch_conv_pool(s_in, Wc, T, B, H, W, C, F, alpha, theta, b_th, V, s_out, active_bits, P, arg, trace_pool,
+                     alpha_next, s);
+  } else {
+    const int nv = (int)(((size_t)B * H * W * F + kScanThreads - 1) / kScanThreads);
+    if (F % kWave == 0 && 9 * C <= kWave)  // a wavefront's lanes are the filters of one pixel
+      hipLaunchKernelGGL(conv_scan<true>, dim3((unsigned)nv), dim3(kScanThreads), 0, s, s_in, Wc, T, B, H, W, C, F,
+                         alpha, theta, b_th, V, s_out, active_bits);
+    else
+      hipLaunchKernelGGL(conv_scan<false>, dim3((unsigned)nv), dim3(kScanThreads), 0, s, s_in, Wc, T, B, H, W, C, F,
+                         alpha, theta, b_th, V, s_out, active_bits);
+  }
+  if (trace_in) launch_trace(s_in, T, B, H * W * C, alpha, trace_in, s);
+  if (P && !fused) {
+    const snn_status st = snn_maxpool_spikes(s_out, T, B, H, W, F, P, arg, stream);
+    if (st != SNN_OK) return st;
+    if (trace_pool) launch_trace(P, T, B, (H / 2) * (W / 2) * F, alpha_next, trace_pool, s);
   }
   return launch_status();
+}
+
+}  // namespace
+
+extern "C" snn_status snn_conv_lif_forward(const uint8_t* s_in, const float* Wc, int T, int B, int H, int W, int C,
+                                           int F, float alpha, float theta, float b_th, float* V, uint8_t* s_out,
+                                           float* trace_in, uint64_t* active_bits, void* stream) {
+  return conv_forward_impl(s_in, Wc, T, B, H, W, C, F, alpha, theta, b_th, V, s_out, trace_in, active_bits, nullptr,
+                           nullptr, nullptr, 1.0f, stream);
+}
+
+extern "C" snn_status snn_conv_lif_forward_pool(const uint8_t* s_in, const float* Wc, int T, int B, int H, int W,
+                                                int C, int F, float alpha, float theta, float b_th, float* V,
+                                                uint8_t* s_out, float* trace_in, uint64_t* active_bits, uint8_t* P,
+                                                uint8_t* arg, float* trace_pool, float alpha_next, void* stream) {
+  if (!P || !arg || H % 2 != 0 || W % 2 != 0) return SNN_ERR_INVALID_ARG;
+  if (trace_pool && bad_alpha(alpha_next)) return SNN_ERR_INVALID_ARG;
+  return conv_forward_impl(s_in, Wc, T, B, H, W, C, F, alpha, theta, b_th, V, s_out, trace_in, active_bits, P, arg,
+                           trace_pool, alpha_next, stream);
 }

@@ -373,13 +373,13 @@ class ConvNetwork:
         if self.V is None:
             self.allocate()
         T, B, H, W, C, F = self.dims
-        snn.snn_conv_lif_forward(self.X, self.Wc, T, B, H, W, C, F, self.alpha, self.theta,
-                                 0.0 if b_th is None else b_th, self.V, self.S, self.trace,
-                                 None if b_th is None else self.bits)
+        snn.snn_conv_lif_forward_pool(self.X, self.Wc, T, B, H, W, C, F, self.alpha, self.theta,
+                                      0.0 if b_th is None else b_th, self.V, self.S, self.trace,
+                                      None if b_th is None else self.bits, self.P, self.arg, self.trace_out,
+                                      self.alpha_out)
         self.bits_bth = b_th
-        snn.snn_maxpool_spikes(self.S, T, B, H, W, F, self.P, self.arg)
         snn.snn_lif_forward(self.P, self.W_out, T, B, self.Np, self.W_out.shape[1], self.alpha_out, INF, self.V_out,
-                            self.S_out, self.trace_out)
+                            self.S_out, None)
         return self
 
     def readout(self, dense=False):

@@ -62,6 +62,7 @@ _SIGNATURES = {
     "snn_activity_reg_grad": (_I, [_P, _I, _I, _I, _P, _P, _I64, _P, _P]),
     "snn_adam_step": (_I, [_P, _P, _P, _P, _I64, _F, _F, _F, _F, _I, _P]),
     "snn_conv_lif_forward": (_I, [_P, _P, _I, _I, _I, _I, _I, _I, _F, _F, _F, _P, _P, _P, _P, _P]),
+    "snn_conv_lif_forward_pool": (_I, [_P, _P, _I, _I, _I, _I, _I, _I, _F, _F, _F, _P, _P, _P, _P, _P, _P, _P, _F, _P]),
     "snn_maxpool_spikes": (_I, [_P, _I, _I, _I, _I, _I, _P, _P, _P]),
     "snn_pool_route_bits": (_I, [_P, _P, _I, _I, _I, _I, _I, _P, _P]),
     "snn_pool_scatter_eps": (_I, [_I, _I, _I, _I, _I, _P, _P, _I64, _P, _P, _P, _P, _I64, _P, _P]),
@@ -359,6 +360,16 @@ def snn_conv_lif_forward(s_in, Wc, T, B, H, W, C, F, alpha, theta, b_th, V, s_ou
         _ptr(s_in, torch.uint8, "s_in"), _ptr(Wc, torch.float32, "Wc"), T, B, H, W, C, F, float(alpha), float(theta),
         float(b_th), _ptr(V, torch.float32, "V"), _ptr(s_out, torch.uint8, "s_out"),
         _ptr(trace_in, torch.float32, "trace_in"), _ptr(active_bits, torch.int64, "active_bits"), _stream(stream)))
+
+
+def snn_conv_lif_forward_pool(s_in, Wc, T, B, H, W, C, F, alpha, theta, b_th, V, s_out, trace_in, active_bits, P, arg,
+                              trace_pool=None, alpha_next=1.0, stream=None):
+    _check("snn_conv_lif_forward_pool", lib().snn_conv_lif_forward_pool(
+        _ptr(s_in, torch.uint8, "s_in"), _ptr(Wc, torch.float32, "Wc"), T, B, H, W, C, F, float(alpha), float(theta),
+        float(b_th), _ptr(V, torch.float32, "V"), _ptr(s_out, torch.uint8, "s_out"),
+        _ptr(trace_in, torch.float32, "trace_in"), _ptr(active_bits, torch.int64, "active_bits"),
+        _ptr(P, torch.uint8, "P"), _ptr(arg, torch.uint8, "arg"), _ptr(trace_pool, torch.float32, "trace_pool"),
+        float(alpha_next), _stream(stream)))
 
 
 def snn_maxpool_spikes(S, T, B, H, W, F, P, arg, stream=None):
