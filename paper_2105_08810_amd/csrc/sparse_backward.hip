@@ -695,9 +695,9 @@ __global__ __launch_bounds__(kDenseWaves * kWave) void csr_dense_g(int TB, int N
 }
 
 // The dense product's plan and the number of entries from which it is the faster way. Per multiply-add
-// the entry kernels run at the rate of their float64 LDS atomics, measured 3.8e12 a second (1024 -> 1024,
-// 27% active: 9.6 ms), the product at 31.7e12 (padded to 128 x 128 tiles: 4.2 ms), plus about 2 ps per slot
-// for writing and reading G and 15 us of launches; entries cost more than the product from about 13%.
+// the entry kernels run at the rate of their float64 LDS atomics, measured 3.05e12 a second (1024 -> 1024,
+// 12% active: 5.3 ms; 2312 -> 200, 12%: 1.43), the product at 31e12 (padded to 128 x 128 tiles: 4.3 ms), plus
+// 1.3 ps per slot for writing G and 15 us of launches; entries cost more than the product from about 11%.
 struct DenseDwPlan {
   int splits;
   int64_t least;
@@ -711,8 +711,8 @@ DenseDwPlan plan_dw_dense(int T, int B, int N_in, int N_out) {
   s = std::min(s, std::max(1, T * B / 256));
   s = std::max(1, std::min(s, 64));
   p.splits = s >= 8 ? s / 8 * 8 : s;
-  const double dense_s = TB * (128.0 * tm) * (128.0 * tn) / 31.7e12 + TB * N_out * 2e-12 + 15e-6;
-  p.least = (int64_t)(1.1 * dense_s * 3.8e12 / (double)N_in) + 1;
+  const double dense_s = TB * (128.0 * tm) * (128.0 * tn) / 31e12 + TB * N_out * 1.3e-12 + 15e-6;
+  p.least = (int64_t)(1.03 * dense_s * 3.05e12 / (double)N_in) + 1;
   return p;
 }
 
