@@ -134,6 +134,15 @@ snn_status snn_active_compact_bits(const uint64_t* active_bits, const float* V, 
                                    size_t workspace_bytes, void* stream);
 
 /*
+ * The entries alone, for a caller that sizes the entry arrays by the count: after a call of
+ * snn_active_compact_bits with capacity 0 (row pointers and nnz), row_ptr as that call wrote it from the same
+ * bitset, writes col_idx and g_act as snn_active_compact_bits does. No workspace.
+ */
+snn_status snn_active_compact_bits_place(const uint64_t* active_bits, const float* V, int T, int B, int N,
+                                         float theta, float beta, const int32_t* row_ptr, int32_t* col_idx,
+                                         float* g_act, int64_t capacity, void* stream);
+
+/*
  * snn_active_compact_bits without a workspace argument and without any allocation, for callers
  * that cannot allocate device memory (code under HIP graph capture, tight serving loops,
  * harnesses that forbid hipMalloc). Same arguments (minus workspace) and results. The row

@@ -310,6 +310,8 @@ constexpr int kGroupBits = 10;
 // tr <= kTileThreads * kMaxPerThread rows per tile.
 constexpr int kMaxPerThread = 8;
 
+// ROWS: the row pointers are there already (an earlier call's, over the same bitset) and only the entries are placed.
+template <bool ROWS>
 __global__ __launch_bounds__(kTileThreads) void bits_fill(const uint64_t* __restrict__ bits, const float* __restrict__ V,
                                                           int T, int B, int N, int tr, int rpw, float theta, float beta,
                                                           const int32_t* __restrict__ counts,
@@ -324,6 +326,12 @@ __global__ __launch_bounds__(kTileThreads) void bits_fill(const uint64_t* __rest
   const int wv = threadIdx.x / kWave;
   const int rows = T * B;
   const int t0 = blockIdx.x * tr, t1 = min(rows, t0 + tr);
+  int all = 0;
+  if (ROWS) {
+    for (int k = threadIdx.x; k <= t1 - t0; k += kTileThreads) rp_tile[k] = row_ptr[t0 + k];
+    __syncthreads();
+    all = rp_tile[t1 - t0] - rp_tile[0];
+  } else {
   // the totals of the tiles before this one (fixed order: per thread, then the wavefronts in order)
   int p = 0;
   for (int k = threadIdx.x; k < (int)blockIdx.x; k += kTileThreads) p += tile_sum[k];
@@ -351,7 +359,7 @@ __global__ __launch_bounds__(kTileThreads) void bits_fill(const uint64_t* __rest
   __syncthreads();  // red is reused
   if (l == kWave - 1) red[wv] = incl;
   __syncthreads();
-  int before = 0, all = 0;
+  int before = 0;
 #pragma unroll
   for (int k = 0; k < kTileWaves; ++k) {
     const int v = red[k];
@@ -374,6 +382,7 @@ __global__ __launch_bounds__(kTileThreads) void bits_fill(const uint64_t* __rest
       row_ptr[rows] = base + all;
       *nnz = (int64_t)base + all;
     }
+  }
   }
   __syncthreads();
   if (cap <= 0) return;
@@ -507,8 +516,8 @@ snn_status enqueue_compact_bits(const uint64_t* active_bits, const float* V, int
   int32_t* tsum = ws.take<int32_t>(p.n_tiles);
   hipLaunchKernelGGL(bits_count, dim3((unsigned)p.n_tiles), dim3(kTileThreads), 0, s, active_bits, T, B, N, p.tr, p.rpw,
                      counts, tsum);
-  hipLaunchKernelGGL(bits_fill, dim3((unsigned)p.n_tiles), dim3(kTileThreads), (size_t)(p.tr + 1) * sizeof(int), s,
-                     active_bits, V, T, B, N, p.tr, p.rpw, theta, beta, counts, tsum, row_ptr, nnz_dev, col_idx, g_act,
+  hipLaunchKernelGGL(bits_fill<false>, dim3((unsigned)p.n_tiles), dim3(kTileThreads), (size_t)(p.tr + 1) * sizeof(int),
+                     s, active_bits, V, T, B, N, p.tr, p.rpw, theta, beta, counts, tsum, row_ptr, nnz_dev, col_idx, g_act,
                      capacity);
   return launch_status();
 }
@@ -526,6 +535,21 @@ extern "C" snn_status snn_active_compact_bits(const uint64_t* active_bits, const
   if (workspace_bytes < snn_active_compact_bits_workspace(T, B, N)) return SNN_ERR_INVALID_ARG;
   return enqueue_compact_bits(active_bits, V, T, B, N, theta, beta, row_ptr, col_idx, g_act, capacity, nnz_dev,
                               workspace, static_cast<hipStream_t>(stream));
+}
+
+extern "C" snn_status snn_active_compact_bits_place(const uint64_t* active_bits, const float* V, int T, int B, int N,
+                                                    float theta, float beta, const int32_t* row_ptr,
+                                                    int32_t* col_idx, float* g_act, int64_t capacity, void* stream) {
+  int64_t unused = 0;
+  if (!compact_bits_args_ok(active_bits, V, T, B, N, theta, beta, row_ptr, col_idx, g_act, capacity, &unused))
+    return SNN_ERR_INVALID_ARG;
+  const TilePlan p = plan_tiles(T * B, N);
+  if (p.tr > kTileThreads * kMaxPerThread) return SNN_ERR_UNSUPPORTED;
+  if (capacity == 0) return SNN_OK;
+  hipLaunchKernelGGL(bits_fill<true>, dim3((unsigned)p.n_tiles), dim3(kTileThreads), (size_t)(p.tr + 1) * sizeof(int),
+                     static_cast<hipStream_t>(stream), active_bits, V, T, B, N, p.tr, p.rpw, theta, beta, nullptr,
+                     nullptr, const_cast<int32_t*>(row_ptr), nullptr, col_idx, g_act, capacity);
+  return launch_status();
 }
 
 // ------------------------------------------------------------------ allocation-free form

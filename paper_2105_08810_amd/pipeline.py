@@ -115,6 +115,9 @@ class Network:
         """CSR of every LIF layer's active set: from the forward's bitsets when they were marked
         with this b_th, else from V."""
         caps = capacities or [None] * self.L
+        if self.bits and self.bits_bth == b_th and all(c is None for c in caps):  # one host sync for every layer
+            return snn.active_compact_bits_counted([(self.bits[l], self.V[l], self.V[l].shape) for l in range(self.L)],
+                                                   self.theta, self.beta)
         return [self.compact_layer(l, b_th, caps[l]) for l in range(self.L)]
 
     def compact_layer(self, l, b_th, capacity: Optional[int] = None) -> snn.Csr:
@@ -281,7 +284,10 @@ class Network:
         grads = list(dWs) + [dW_out]
         opt.step(grads)
         mark(5)
-        pen = sum(a[1] for a in acts) if acts else torch.zeros(1, device=self.X.device)
+        if acts:
+            pen = acts[0][1] if len(acts) == 1 else torch.cat([a[1] for a in acts]).sum(0, keepdim=True)
+        else:
+            pen = torch.zeros(1, device=self.X.device)
         return {"ce": ro[2], "penalty": pen, "grads": grads, "nnz": nnz}
 
 
@@ -392,6 +398,10 @@ class ConvNetwork:
             raise ValueError("compact(b_th): run forward(b_th) first")
         T, B, H, W, C, F = self.dims
         caps = capacities or [None, None]
+        if caps[0] is None and caps[1] is None:  # one host sync for both counts
+            snn.snn_pool_route_bits(self.bits, self.arg, T, B, H, W, F, self.pbits)
+            return snn.active_compact_bits_counted(
+                [(self.bits, self.V, self.V.shape), (self.pbits, None, (T, B, self.Np))], self.theta, self.beta)
         conv = snn.active_compact_bits(self.bits, self.V, self.theta, self.beta, caps[0])
         snn.snn_pool_route_bits(self.bits, self.arg, T, B, H, W, F, self.pbits)
         pool = snn.active_compact_bits(self.pbits, None, self.theta, self.beta, caps[1], with_g=False,

@@ -40,6 +40,7 @@ _SIGNATURES = {
     "snn_lif_forward_traces": (_I, [_P, _P, _I, _I, _I, _I, _F, _F, _F, _P, _P, _P, _P, _F, _P, _P]),
     "snn_active_compact_bits_workspace": (_SZ, [_I, _I, _I]),
     "snn_active_compact_bits": (_I, [_P, _P, _I, _I, _I, _F, _F, _P, _P, _P, _I64, _P, _P, _SZ, _P]),
+    "snn_active_compact_bits_place": (_I, [_P, _P, _I, _I, _I, _F, _F, _P, _P, _P, _I64, _P]),
     "snn_active_compact_bits_noalloc": (_I, [_P, _P, _I, _I, _I, _F, _F, _P, _P, _P, _I64, _P, _P]),
     "snn_sparse_dw_workspace": (_SZ, [_I, _I, _I, _I, _I64]),
     "snn_sparse_dw": (_I, [_P, _I, _I, _I, _I, _P, _P, _P, _P, _I64, _P, _P, _SZ, _P]),
@@ -116,8 +117,11 @@ def _ptr(t: Optional[torch.Tensor], dtype=None, name="tensor") -> Optional[int]:
 
 
 def _stream(stream=None) -> int:
-    s = torch.cuda.current_stream() if stream is None else stream
-    return s.cuda_stream
+    """The handle of `stream`, or of torch's current stream on the current device (asked for as a plain
+    integer: building a torch.cuda.Stream object for every call costs several microseconds)."""
+    if stream is None:
+        return torch._C._cuda_getCurrentRawStream(torch._C._cuda_getDevice())
+    return stream.cuda_stream
 
 
 def _check(fn: str, status: int):
@@ -171,6 +175,13 @@ def snn_active_compact_bits(active_bits, V, T, B, N, theta, beta, row_ptr, col_i
         float(beta), _ptr(row_ptr, torch.int32, "row_ptr"), _ptr(col_idx, torch.int32, "col_idx"),
         _ptr(g_act, torch.float32, "g_act"), int(capacity), _ptr(nnz_dev, torch.int64, "nnz"),
         _ptr(ws, None, "workspace"), 0 if ws is None else ws.numel() * ws.element_size(), _stream(stream)))
+
+
+def snn_active_compact_bits_place(active_bits, V, T, B, N, theta, beta, row_ptr, col_idx, g_act, capacity, stream=None):
+    _check("snn_active_compact_bits_place", lib().snn_active_compact_bits_place(
+        _ptr(active_bits, torch.int64, "active_bits"), _ptr(V, torch.float32, "V"), T, B, N, float(theta),
+        float(beta), _ptr(row_ptr, torch.int32, "row_ptr"), _ptr(col_idx, torch.int32, "col_idx"),
+        _ptr(g_act, torch.float32, "g_act"), int(capacity), _stream(stream)))
 
 
 def snn_active_compact_bits_noalloc(active_bits, V, T, B, N, theta, beta, row_ptr, col_idx, g_act, capacity,
@@ -491,19 +502,41 @@ def active_compact_bits(bits: torch.Tensor, V: Optional[torch.Tensor], theta, be
                         with_g=True, shape=None) -> Csr:
     """Allocate and run snn_active_compact_bits. Without a capacity it first counts (one host sync).
     shape = (T, B, N) when V is None (then with_g must be False)."""
+    if with_g and V is None:
+        _check("snn_active_compact_bits", SNN_ERR_INVALID_ARG)
+    if capacity is None:
+        return active_compact_bits_counted([(bits, V, V.shape if V is not None else shape)], theta, beta, with_g)[0]
     T, B, N = V.shape if V is not None else shape
     dev = bits.device
     ws = workspace(snn_active_compact_bits_workspace(T, B, N), dev)
     row_ptr = torch.empty(T * B + 1, dtype=torch.int32, device=dev)
     nnz = torch.empty(1, dtype=torch.int64, device=dev)
-    if capacity is None:
-        snn_active_compact_bits(bits, V, T, B, N, theta, beta, row_ptr, None, None, 0, nnz, ws)
-        capacity = int(nnz.item())
     cap = max(int(capacity), 1)
     col = torch.empty(cap, dtype=torch.int32, device=dev)
     g = torch.empty(cap, dtype=torch.float32, device=dev) if with_g else None
     snn_active_compact_bits(bits, V, T, B, N, theta, beta, row_ptr, col, g, cap, nnz, ws)
     return Csr(row_ptr, col, g, nnz, cap)
+
+
+def active_compact_bits_counted(layers, theta, beta, with_g=True):
+    """CSRs of several layers [(bits, V or None, (T, B, N))], entry arrays sized by the counts: every layer is
+    counted, one host sync reads all counts, then the entries are placed (g where with_g and V is given)."""
+    dev = layers[0][0].device
+    nnz = torch.empty(len(layers), dtype=torch.int64, device=dev)
+    rows = []
+    for l, (bits, V, (T, B, N)) in enumerate(layers):
+        ws = workspace(snn_active_compact_bits_workspace(T, B, N), dev)
+        rows.append(torch.empty(T * B + 1, dtype=torch.int32, device=dev))
+        snn_active_compact_bits(bits, V, T, B, N, theta, beta, rows[l], None, None, 0, nnz[l:l + 1], ws)
+    out = []
+    for l, n in enumerate(nnz.tolist()):
+        bits, V, (T, B, N) = layers[l]
+        cap = max(n, 1)
+        col = torch.empty(cap, dtype=torch.int32, device=dev)
+        g = torch.empty(cap, dtype=torch.float32, device=dev) if with_g and V is not None else None
+        snn_active_compact_bits_place(bits, V, T, B, N, theta, beta, rows[l], col, g, cap)
+        out.append(Csr(rows[l], col, g, nnz[l:l + 1], cap))
+    return out
 
 
 def readout_ce(V_out: torch.Tensor, labels: torch.Tensor, mode: int, dense=False):
