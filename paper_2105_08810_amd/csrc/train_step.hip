@@ -21,7 +21,7 @@ namespace snn {
 namespace {
 
 constexpr int kCountThreads = 256;
-constexpr int kCountTargetBlocks = 1024;  // a few blocks per CU; each further time chunk is read again by reg_sample
+constexpr int kCountTargetBlocks = 2048;  // enough blocks to cover the chip several times
 constexpr int kRegThreads = 256;
 constexpr int kGradRows = 8;  // CSR rows per wave in the gradient add
 
