@@ -716,13 +716,9 @@ DenseDwPlan plan_dw_dense(int T, int B, int N_in, int N_out) {
   return p;
 }
 
-// Whether a layer with out_cap entry slots may hold enough of them for the dense product. csr_dense_g holds a
-// row per wavefront in LDS, within the 64 KB of a launch without a raised limit; wider layers go entry by entry.
-constexpr int kDenseCols = 4096;
-static_assert(kDenseWaves * kDenseCols * sizeof(float) <= 64 * 1024, "a block's rows fit the default LDS limit");
-
+// Whether a layer with out_cap entry slots may hold enough of them for the dense product.
 bool dw_dense_possible(int T, int B, int N_in, int N_out, int64_t out_cap) {
-  return N_out > 32 && N_out <= kDenseCols && out_cap >= plan_dw_dense(T, B, N_in, N_out).least;
+  return N_out > 32 && out_cap >= plan_dw_dense(T, B, N_in, N_out).least;
 }
 
 // ------------------------------------------------------------------ narrow layers

@@ -35,9 +35,6 @@ def _csr(rng, T, B, N, share, spare=0, with_g=True):
     (30, 37, 900, 130, 0.4, 90000, True),
     (40, 20, 1300, 300, 0.8, 7, True),
     (5, 120, 130, 1100, 1.0, 0, True),
-    (8, 40, 600, 4096, 0.9, 0, True),        # the widest rows the dense product takes, and wider ones
-    (8, 40, 600, 4100, 0.9, 0, True),
-    (4, 40, 500, 12000, 0.95, 0, True),
 ])
 def test_dw_wide_band(T, B, n_in, n_out, share, spare, with_g):
     rng = np.random.default_rng(n_in + n_out)
