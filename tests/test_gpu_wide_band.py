@@ -35,6 +35,7 @@ def _csr(rng, T, B, N, share, spare=0, with_g=True):
     (30, 37, 900, 130, 0.4, 90000, True),
     (40, 20, 1300, 300, 0.8, 7, True),
     (5, 120, 130, 1100, 1.0, 0, True),
+    (8, 40, 600, 4096, 0.9, 0, True),        # the widest layer the call takes: a block's rows fill 64 KB of LDS
 ])
 def test_dw_wide_band(T, B, n_in, n_out, share, spare, with_g):
     rng = np.random.default_rng(n_in + n_out)
