@@ -183,9 +183,10 @@ snn_status snn_active_compact_bits_noalloc(const uint64_t* active_bits, const fl
  *   copy of the active entries is built in it); for N_out <= 32 (narrow layers: G written
  *   densely, padded to 8, 16 or 32 columns) it holds that G and delta (T*B*ld floats each), a
  *   bitset of the rows with an entry and per-chunk partial dW, and does not depend on out_cap.
- *   When out_cap allows so many active entries that a dense product may be the faster way to dW
- *   (from about 13% of a large layer's T*B*N_out on), it also has room for G written densely
- *   (4 T*B*N_out bytes); which way is taken is decided on the device, by row_ptr[T*B].
+ *   When out_cap allows so many active entries that sums by column, or a dense product, may be the
+ *   faster way to dW (from about 4% and 20% of a large layer's T*B*N_out on), it also has room for
+ *   the entries sorted by column (8 bytes each) or G written densely (4 T*B*N_out bytes); which way
+ *   is taken is decided on the device, by row_ptr[T*B].
  *   aux_stream (may be NULL): a second hipStream_t. When given, the spike-gradient part runs on
  *   it beside the dW part on `stream`; the call makes aux_stream wait for the work already on
  *   `stream`, and `stream` wait for the aux work, so work enqueued on `stream` afterwards sees

@@ -24,6 +24,7 @@ SOURCES = [
     "lif_forward.hip",
     "sparse_backward.hip",
     "dw_mfma.hip",
+    "dw_columns.hip",
     "gemm.hip",
     "dense_backward.hip",
     "readout_ce.hip",

@@ -64,26 +64,46 @@ void mdw_enqueue_layout(int T, int B, int N_in, int N_out, const int32_t* out_ro
 void mdw_enqueue_rest(const float* trace_in, int T, int B, int N_in, int N_out, const float* out_g, const float* eps_out,
                       int64_t out_cap, float* dW, void* workspace, hipStream_t s);
 
-// Device-side choice between two ways to do a call's work, both enqueued: a kernel with a gate runs iff the
-// CSR holds at least `least` entries (or, with below, fewer). end NULL: it always runs. The entry arrays'
+// Device-side choice between several ways to do a call's work, all enqueued: a kernel with a gate runs iff the
+// CSR holds at least `least` and fewer than `under` entries. end NULL: it always runs. The entry arrays'
 // allocated length is only an upper bound of the entries, and reading the count back would wait for the GPU.
 struct Gate {
   const int32_t* end = nullptr;  // row_ptr[T * B]
   int64_t cap = 0;               // allocated entries
   int64_t least = 0;
-  bool below = false;
+  int64_t under = INT64_MAX;
 };
 
 __device__ __forceinline__ bool gate_open(const Gate& g) {
   if (!g.end) return true;
-  const int64_t n = *g.end;
-  return ((n > g.cap ? g.cap : n) >= g.least) != g.below;
+  int64_t n = *g.end;
+  n = n > g.cap ? g.cap : n;
+  return n >= g.least && n < g.under;
 }
+
+// Sparse dW by columns of row windows (dw_columns.hip): partial dW of n_chunks chunks (one chunk: dW itself).
+struct ColsParts {
+  float* part;
+  int n_chunks;
+};
+bool cols_fits(int N_out);
+void cols_seconds(int T, int B, int N_in, int N_out, double* fixed, double* per_entry);
+size_t cols_workspace(int T, int B, int N_in, int N_out, int64_t out_cap);
+ColsParts cols_enqueue(const float* trace_in, int T, int B, int N_in, int N_out, const int32_t* out_row_ptr,
+                       const int32_t* out_col_idx, const float* out_g, const float* eps_out, int64_t out_cap, float* dW,
+                       void* workspace, const Gate& gate, hipStream_t s);
 
 // Dense float32 products (gemm.hip). K slice z of `splits` goes to C + z * c_split.
 //   gemm_split_km  C = sum_k A[k, m] B[k, n], operands in three bf16 parts, float32 sums
 //   gemm_split_kc  C = sum_k A[m, k] B[n, k], the same
 //   gemm_f64_km    C = sum_k A[k, m] B[k, n], products and sums in float64
+// plan_splits: the K slices of a km product whose whole rounds of blocks run at mac_rate multiply-adds a second,
+// and the time this should take with the partials' sum.
+struct SplitPlan {
+  int splits;
+  double seconds;
+};
+SplitPlan plan_splits(int M, int N, int K, double mac_rate);
 void gemm_split_km(int M, int N, int K, const float* A, int lda, const float* B, int ldb, float* C, int ldc, int splits,
                    size_t c_split, hipStream_t s);
 void gemm_split_kc(int M, int N, int K, const float* A, int lda, const float* B, int ldb, float* C, int ldc,

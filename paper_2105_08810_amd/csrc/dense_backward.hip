@@ -69,15 +69,8 @@ __global__ void reduce_splits(const float* __restrict__ part, int n_split, size_
   }
 }
 
-// K slices of the dW product: about two blocks of 128 x 128 per CU, a multiple of 8 from 8 on (equally
-// many per XCD), at least 256 rows each.
-int dw_splits(int TB, int N_in, int N_out) {
-  const int tiles = ((N_in + 127) / 128) * ((N_out + 127) / 128);
-  int s = (2 * cu_count() + tiles - 1) / tiles;
-  s = std::min(s, std::max(1, TB / 256));
-  s = std::max(1, std::min(s, 64));
-  return s >= 8 ? s / 8 * 8 : s;
-}
+// K slices of the dW product (88e12 multiply-adds a second at 1024 x 1024 x 128000).
+int dw_splits(int TB, int N_in, int N_out) { return plan_splits(N_in, N_out, TB, 88e12).splits; }
 
 }  // namespace
 }  // namespace snn

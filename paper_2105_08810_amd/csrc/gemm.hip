@@ -449,6 +449,26 @@ __global__ __launch_bounds__(kThreads, 2) void gemm_f64(int M, int N, int K, con
 
 }  // namespace
 
+// Two blocks of 128 x 128 fit a CU, and the product takes as long as the CU with the most blocks: the splits are
+// those with the least time by that count (a block alone on its CU keeps the matrix cores about three quarters
+// busy). Splits that are no multiple of 8 lose slice_tile's L2 sharing (5%). Against "about two blocks per CU,
+// rounded to a multiple of 8", a sparse dW on the float64 product (with writing G): 76800 x 2312 x 200 3.12 ->
+// 1.82 ms (304 blocks before), 25600 x 1500 x 900 2.08 -> 1.54 (576), 25600 x 784 x 1300 1.71 -> 1.22 (539); a
+// dense backward of these layers 1.43 -> 1.26, 1.09 -> 1.03 and 0.96 -> 0.86 ms.
+SplitPlan plan_splits(int M, int N, int K, double mac_rate) {
+  const int tiles = ((M + kBM - 1) / kBM) * ((N + kBN - 1) / kBN);
+  const int cus = cu_count();
+  SplitPlan best{1, 0.0};
+  for (int s = 1; s <= 64 && (s == 1 || s <= K / 256); ++s) {
+    const int64_t blocks = (int64_t)s * tiles;
+    const double per_cu = blocks <= cus ? 1.35 : (double)((blocks + cus - 1) / cus);
+    const double product = per_cu * ((K + s - 1) / s) * kBM * kBN * cus / mac_rate;
+    const double t = product * (s % 8 ? 1.05 : 1.0) + (s > 1 ? 5e-6 + (double)s * M * N * 8.0 / 4e12 : 0.0);
+    if (s == 1 || t < best.seconds) best = {s, t};
+  }
+  return best;
+}
+
 void gemm_split_km(int M, int N, int K, const float* A, int lda, const float* B, int ldb, float* C, int ldc, int splits,
                    size_t c_split, hipStream_t s) {
   const int tm = (M + kBM - 1) / kBM, tn = (N + kBN - 1) / kBN;

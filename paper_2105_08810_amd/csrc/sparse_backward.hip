@@ -694,29 +694,43 @@ __global__ __launch_bounds__(kDenseWaves * kWave) void csr_dense_g(int TB, int N
   }
 }
 
-// The dense product's plan and the number of entries from which it is the faster way. Per multiply-add
-// the entry kernels run at the rate of their float64 LDS atomics, measured 3.05e12 a second (1024 -> 1024,
-// 12% active: 5.3 ms; 2312 -> 200, 12%: 1.43), the product at 31e12 (padded to 128 x 128 tiles: 4.3 ms), plus
-// 1.3 ps per slot for writing G and 15 us of launches; entries cost more than the product from about 11%.
+// The dense product's plan, and the entries from which the columns kernel and the dense product are the faster way.
+// Entry by entry: 15 us and 3.05e12 multiply-adds a second (the float64 LDS atomics; 1024 -> 1024, 12% active: 5.3
+// ms; 2312 -> 200: 1.43), fewer in a small layer (700 -> 400 at 600 rows 1.05e12, 784 -> 200 at 6400 2.2e12). By columns: cols_seconds. The product: 32e12 a second in whole rounds of 128 x 128 tiles,
+// 1.3 ps per slot for writing G and 15 us of launches.
 struct DenseDwPlan {
   int splits;
-  int64_t least;
+  int64_t cols_least, least;
 };
 
 DenseDwPlan plan_dw_dense(int T, int B, int N_in, int N_out) {
   DenseDwPlan p{};
   const double TB = (double)T * B;
-  const int tm = (N_in + 127) / 128, tn = (N_out + 127) / 128;
-  int s = (2 * cu_count() + tm * tn - 1) / (tm * tn);
-  s = std::min(s, std::max(1, T * B / 256));
-  s = std::max(1, std::min(s, 64));
-  p.splits = s >= 8 ? s / 8 * 8 : s;
-  const double dense_s = TB * (128.0 * tm) * (128.0 * tn) / 31e12 + TB * N_out * 1.3e-12 + 15e-6;
-  p.least = (int64_t)(1.03 * dense_s * 3.05e12 / (double)N_in) + 1;
+  const SplitPlan q = plan_splits(N_in, N_out, T * B, 32e12);
+  p.splits = q.splits;
+  const double dense_s = 1.03 * (q.seconds + TB * N_out * 1.3e-12 + 15e-6);
+  const double entry_s = (double)N_in / 3.05e12 * (1.0 + std::min(2.0, 3.2e8 / (TB * N_in * N_out)));  // per entry
+  p.least = (int64_t)(std::max(0.0, dense_s - 15e-6) / entry_s) + 1;
+  p.cols_least = p.least;
+  if (!cols_fits(N_out)) return p;
+  // time by columns = fixed + per_entry * entries
+  double fixed, per_entry;
+  cols_seconds(T, B, N_in, N_out, &fixed, &per_entry);
+  const double lo = std::max(0.0, 1.05 * fixed - 15e-6) / (entry_s - std::min(per_entry, 0.9 * entry_s));
+  const double hi = (dense_s - fixed) / per_entry;
+  if (lo < hi) {
+    p.cols_least = (int64_t)lo + 1;
+    p.least = std::max((int64_t)hi, p.cols_least) + 1;
+  }
   return p;
 }
 
-// Whether a layer with out_cap entry slots may hold enough of them for the dense product.
+// Whether a layer with out_cap entry slots may hold enough of them for the columns kernel; for the dense product.
+bool dw_cols_possible(int T, int B, int N_in, int N_out, int64_t out_cap) {
+  const DenseDwPlan p = plan_dw_dense(T, B, N_in, N_out);
+  return p.cols_least < p.least && out_cap >= p.cols_least;
+}
+
 bool dw_dense_possible(int T, int B, int N_in, int N_out, int64_t out_cap) {
   return N_out > 32 && out_cap >= plan_dw_dense(T, B, N_in, N_out).least;
 }
@@ -1431,6 +1445,8 @@ size_t dw_workspace(int T, int B, int N_in, int N_out, int64_t out_cap) {
     if (splits > 1) c.take<float>((size_t)splits * N_in * N_out);
     dense = c.off;
   }
+  if (dw_cols_possible(T, B, N_in, N_out, out_cap))
+    dense = std::max(dense, cols_workspace(T, B, N_in, N_out, out_cap));
   if (dw_rows_eligible(N_in, N_out)) {  // the chunk partials only
     const DwPlan p = plan_dw_rows(T, B, N_in, N_out);
     return std::max(dense, p.n_chunks > 1 ? (size_t)p.n_chunks * N_in * N_out * sizeof(float) : 256);
@@ -1550,16 +1566,28 @@ void enqueue_dw(const float* trace_in, int T, int B, int N_in, int N_out, const 
     if (rest) mdw_enqueue_rest(trace_in, T, B, N_in, N_out, out_g, eps_out, out_cap, dW, workspace, s);
     return;
   }
-  // Entry by entry below p.least active entries, a dense product from there on; which, the kernels decide
-  // by the CSR's own count (out_cap is an upper bound of it), so both are enqueued where both are possible.
-  Gate few{}, many{};
+  // Entry by entry with few active entries, by columns with more, a dense product with most slots active; which,
+  // the kernels decide by the CSR's own count (out_cap is an upper bound of it), so all that are possible are
+  // enqueued.
+  Gate few{}, wide{}, most{};
   DenseDwPlan dense{};
   const bool maybe_dense = dw_dense_possible(T, B, N_in, N_out, out_cap);
-  if (maybe_dense) {
+  const bool maybe_cols = dw_cols_possible(T, B, N_in, N_out, out_cap);
+  if (maybe_dense || maybe_cols) {
+    const int32_t* end = out_row_ptr + (size_t)T * B;
     dense = plan_dw_dense(T, B, N_in, N_out);
-    few = Gate{out_row_ptr + (size_t)T * B, out_cap, dense.least, true};
-    many = Gate{out_row_ptr + (size_t)T * B, out_cap, dense.least, false};
+    few = Gate{end, out_cap, 0, dense.cols_least};
+    wide = Gate{end, out_cap, dense.cols_least, dense.least};
+    most = Gate{end, out_cap, dense.least};
   }
+  const auto enqueue_cols = [&]() {
+    const ColsParts q = cols_enqueue(trace_in, T, B, N_in, N_out, out_row_ptr, out_col_idx, out_g, eps_out, out_cap, dW,
+                                     workspace, wide, s);
+    const size_t n = (size_t)N_in * N_out;
+    if (q.n_chunks > 1)
+      hipLaunchKernelGGL(reduce_chunks, dim3((unsigned)std::min<size_t>((n + 255) / 256, 4096)), dim3(256), 0, s, q.part,
+                         q.n_chunks, n, dW, wide);
+  };
   const auto enqueue_dense = [&]() {
     Carve ws(workspace);
     float* Gd = ws.take<float>((size_t)T * B * N_out);
@@ -1567,12 +1595,12 @@ void enqueue_dw(const float* trace_in, int T, int B, int N_in, int N_out, const 
     const size_t lds = (size_t)kDenseWaves * ((N_out + 3) & ~3) * sizeof(float);
     hipLaunchKernelGGL(csr_dense_g, dim3((unsigned)((T * B + kDenseWaves - 1) / kDenseWaves)),
                        dim3(kDenseWaves * kWave), lds, s, T * B, N_out, out_row_ptr, out_col_idx, out_g, eps_out,
-                       out_cap, Gd, many);
+                       out_cap, Gd, most);
     const size_t n = (size_t)N_in * N_out;
-    gemm_f64_km(N_in, N_out, T * B, trace_in, N_in, Gd, N_out, part, N_out, dense.splits, n, many, s);
+    gemm_f64_km(N_in, N_out, T * B, trace_in, N_in, Gd, N_out, part, N_out, dense.splits, n, most, s);
     if (dense.splits > 1)
       hipLaunchKernelGGL(reduce_chunks, dim3((unsigned)std::min<size_t>((n + 255) / 256, 4096)), dim3(256), 0, s, part,
-                         dense.splits, n, dW, many);
+                         dense.splits, n, dW, most);
   };
   if (dw_rows_eligible(N_in, N_out)) {  // straight from the CSR: no layout pass
     if (!rest) return;
@@ -1593,6 +1621,7 @@ void enqueue_dw(const float* trace_in, int T, int B, int N_in, int N_out, const 
       const unsigned blocks = (unsigned)std::min<size_t>((n + 255) / 256, 4096);
       hipLaunchKernelGGL(reduce_chunks, dim3(blocks), dim3(256), 0, s, part, p.n_chunks, n, dW, few);
     }
+    if (maybe_cols) enqueue_cols();
     if (maybe_dense) enqueue_dense();
     return;
   }
@@ -1632,6 +1661,7 @@ void enqueue_dw(const float* trace_in, int T, int B, int N_in, int N_out, const 
     const unsigned blocks = (unsigned)std::min<size_t>((n + 255) / 256, 4096);
     hipLaunchKernelGGL(reduce_chunks, dim3(blocks), dim3(256), 0, s, part, p.n_chunks, n, dW, few);
   }
+  if (maybe_cols) enqueue_cols();
   if (maybe_dense) enqueue_dense();
 }
 
@@ -1764,8 +1794,8 @@ void enqueue_grad_in(const float* W, int T, int B, int N_in, int N_out, float al
   if (gin_dense_possible(T, B, N_in, N_out, in_cap) &&
       workspace_bytes >= gin_workspace_full(T, B, N_in, N_out, in_cap)) {
     const int64_t least = gin_dense_least(T, B, N_in, N_out);
-    few = Gate{in_row_ptr + (size_t)T * B, in_cap, least, true};
-    many = Gate{in_row_ptr + (size_t)T * B, in_cap, least, false};
+    few = Gate{in_row_ptr + (size_t)T * B, in_cap, 0, least};
+    many = Gate{in_row_ptr + (size_t)T * B, in_cap, least};
     delta = ws.take<float>((size_t)T * B * N_out);
   }
 #define SNN_WALK_ONE(LAUNCH, NJ_, DENSE_, OUT, GATE)                                                               \

@@ -35,6 +35,10 @@ def _csr(rng, T, B, N, share, spare=0, with_g=True):
     (30, 37, 900, 130, 0.4, 90000, True),
     (40, 20, 1300, 300, 0.8, 7, True),
     (5, 120, 130, 1100, 1.0, 0, True),
+    (64, 100, 2312, 200, 0.15, 0, True),     # by columns: a last input tile of 8, two column groups, several chunks
+    (61, 105, 2309, 203, 0.15, 500, True),   # rows of no whole 16 bytes, a last window of five rows
+    (64, 100, 1900, 700, 0.11, 0, False),    # six column groups, the last in part, no g
+    (10, 160, 4000, 2999, 0.1, 0, True),     # one chunk
     (8, 40, 600, 4096, 0.9, 0, True),        # the widest layer the call takes: a block's rows fill 64 KB of LDS
 ])
 def test_dw_wide_band(T, B, n_in, n_out, share, spare, with_g):
@@ -50,11 +54,11 @@ def test_dw_wide_band(T, B, n_in, n_out, share, spare, with_g):
     assert (np.abs(dW.cpu().numpy() - tr.T @ G) <= 4 * U * (tr.T @ np.abs(G))).all()
 
 
-def test_dw_wide_band_truncated():
-    """A CSR with more entries than slots: the entries below the capacity count, on the dense way too."""
-    T, B, n_in, n_out = 60, 10, 700, 400
+@pytest.mark.parametrize("T,B,n_in,n_out,share", [(60, 10, 700, 400, 0.95), (64, 100, 2312, 200, 0.18)])
+def test_dw_wide_band_truncated(T, B, n_in, n_out, share):
+    """A CSR with more entries than slots: the entries below the capacity count, densely and by columns too."""
     rng = np.random.default_rng(3)
-    on, g, csr, _ = _csr(rng, T, B, n_out, 0.95)
+    on, g, csr, _ = _csr(rng, T, B, n_out, share)
     cap = len(g) - 20000
     cut = snn.Csr(csr.row_ptr, csr.col_idx[:cap].contiguous(), csr.g[:cap].contiguous(), csr.nnz_dev, cap)
     eps = rng.standard_normal(cap).astype(np.float32)
@@ -65,6 +69,27 @@ def test_dw_wide_band_truncated():
     G[r[:cap], c[:cap]] = (eps * g[:cap]).astype(np.float64)
     tr = trace.reshape(T * B, n_in).astype(np.float64)
     assert (np.abs(dW.cpu().numpy() - tr.T @ G) <= 4 * U * (tr.T @ np.abs(G))).all()
+
+
+def test_dw_wide_band_columns_outside():
+    """By columns, an entry with a column outside the layer does not count, as on the other ways."""
+    T, B, n_in, n_out = 64, 100, 2312, 200
+    rng = np.random.default_rng(4)
+    on, g, csr, _ = _csr(rng, T, B, n_out, 0.17)
+    eps = rng.standard_normal(len(g)).astype(np.float32)
+    trace = (rng.random((T, B, n_in)) * 2).astype(np.float32)
+    rp = csr.row_ptr.cpu().numpy()
+    first, last = int(rp[5]), int(rp[9]) - 1  # the first entry of row 5, the last of row 8
+    csr.col_idx[first], csr.col_idx[last] = -3, n_out + 2
+    dW = snn.sparse_dw(torch.from_numpy(trace).cuda(), csr, torch.from_numpy(eps).cuda(), n_out)
+    G = np.zeros(on.shape)
+    e = (eps * g).astype(np.float64)
+    e[[first, last]] = 0.0
+    G[on] = e
+    tr = trace.reshape(T * B, n_in).astype(np.float64)
+    assert (np.abs(dW.cpu().numpy() - tr.T @ G) <= 4 * U * (tr.T @ np.abs(G))).all()
+    again = snn.sparse_dw(torch.from_numpy(trace).cuda(), csr, torch.from_numpy(eps).cuda(), n_out)
+    assert torch.equal(dW, again)  # the order of the sums is fixed
 
 
 def _grad_in_reference(T, B, W, G, alpha):
