@@ -33,15 +33,26 @@ struct ColRec {
 
 __host__ __device__ inline int64_t win_stride(int N_out) { return 4 * (((int64_t)N_out * (kBatch - 1) + 3) / 4 + 1); }
 // First record of a window whose first entry is e0: whole batches, with room for every column's padding.
-__device__ __forceinline__ int64_t win_base(int win, int e0, int N_out) {
+__host__ __device__ inline int64_t win_base(int win, int e0, int N_out) {
   return (((int64_t)e0 + 3) & ~(int64_t)3) + win * win_stride(N_out);
+}
+// Length of the record array: every window's entries and padding, and a batch read ahead past the last.
+__host__ __device__ inline int64_t cols_records(int n_win, int N_out, int64_t cap) {
+  return ((cap + 3) & ~(int64_t)3) + n_win * win_stride(N_out) + 2 * kBatch;
+}
+// Records that fit from `base` on, whole batches. With row pointers that do not decrease a window never needs more
+// than there are; with others it may hold up to kRows records per column whatever the next window's base is, so
+// starts and stores are bounded by this.
+__host__ __device__ inline int win_room(int64_t recs, int64_t base) {
+  const int64_t left = recs - 2 * kBatch - base;
+  return (int)(left < 0 ? 0 : (left < (1 << 30) ? left : (1 << 30)));
 }
 
 __global__ __launch_bounds__(kThreads) void cols_layout(int TB, int N_out, const int32_t* __restrict__ rp,
                                                         const int32_t* __restrict__ col, const float* __restrict__ g,
                                                         const float* __restrict__ eps, int64_t cap,
                                                         int32_t* __restrict__ start, ColRec* __restrict__ rec,
-                                                        Gate gate) {
+                                                        int64_t recs, Gate gate) {
   extern __shared__ uint32_t mask[];  // [N_out][4] rows of each column, then [N_out + 1] starts
   __shared__ int red[kWaves];
   if (!gate_open(gate)) return;
@@ -80,9 +91,11 @@ __global__ __launch_bounds__(kThreads) void cols_layout(int TB, int N_out, const
   }
   if (tid == 0) st[N_out] = all;
   __syncthreads();
-  ColRec* dst = rec + win_base(win, clamp_entry(rp[r0], cap), N_out);
+  const int64_t base0 = win_base(win, clamp_entry(rp[r0], cap), N_out);
+  const int room = win_room(recs, base0);
+  ColRec* dst = rec + base0;
   int32_t* sg = start + (size_t)win * (N_out + 1);
-  for (int j = tid; j <= N_out; j += kThreads) sg[j] = st[j];
+  for (int j = tid; j <= N_out; j += kThreads) sg[j] = min(st[j], room);
   for (int row = w; row < nr; row += kWaves) {
     const int e1 = clamp_entry(rp[r0 + row + 1], cap);
     for (int e = clamp_entry(rp[r0 + row], cap) + l; e < e1; e += kWave) {
@@ -95,7 +108,7 @@ __global__ __launch_bounds__(kThreads) void cols_layout(int TB, int N_out, const
         const uint32_t m = mask[4 * j + k];
         pos += k < q ? __popc(m) : (k == q ? __popc(m & ((1u << (row & 31)) - 1u)) : 0);
       }
-      dst[pos] = ColRec{(uint32_t)(row * kInputs * sizeof(float)), eps[e] * (g ? g[e] : 1.0f)};
+      if (pos < room) dst[pos] = ColRec{(uint32_t)(row * kInputs * sizeof(float)), eps[e] * (g ? g[e] : 1.0f)};
     }
   }
   for (int j = tid; j < N_out; j += kThreads) {
@@ -105,7 +118,8 @@ __global__ __launch_bounds__(kThreads) void cols_layout(int TB, int N_out, const
 #pragma unroll
     for (int k = 0; k < 4; ++k)
       if (mask[4 * j + k]) row = 32 * k + 31 - __clz(mask[4 * j + k]);
-    for (int k = n; k < st[j + 1] - st[j]; ++k) dst[st[j] + k] = ColRec{(uint32_t)(row * kInputs * sizeof(float)), 0.0f};
+    const int end = min(st[j + 1], room);
+    for (int k = st[j] + n; k < end; ++k) dst[k] = ColRec{(uint32_t)(row * kInputs * sizeof(float)), 0.0f};
   }
 }
 
@@ -206,7 +220,7 @@ ColsPlan plan_cols(int T, int B, int N_in, int N_out, int64_t out_cap) {
   p.groups = (N_out + kWaves * kCols - 1) / (kWaves * kCols);
   p.cpw = (N_out + kWaves * p.groups - 1) / (kWaves * p.groups);
   p.n_chunks = std::max(1, std::min({2 * cu_count() / (p.n_itiles * p.groups), p.n_win, 64}));  // one round of blocks
-  p.recs = (size_t)(((out_cap + 3) & ~(int64_t)3) + p.n_win * win_stride(N_out) + 2 * kBatch);
+  p.recs = (size_t)cols_records(p.n_win, N_out, out_cap);
   return p;
 }
 
@@ -246,7 +260,8 @@ ColsParts cols_enqueue(const float* trace_in, int T, int B, int N_in, int N_out,
   ColRec* rec = ws.take<ColRec>(p.recs);
   float* part = p.n_chunks > 1 ? ws.take<float>((size_t)p.n_chunks * N_in * N_out) : dW;
   hipLaunchKernelGGL(cols_layout, dim3((unsigned)p.n_win), dim3(kThreads), (5 * (size_t)N_out + 1) * sizeof(int), s,
-                     T * B, N_out, out_row_ptr, out_col_idx, out_g, eps_out, out_cap, start, rec, gate);
+                     T * B, N_out, out_row_ptr, out_col_idx, out_g, eps_out, out_cap, start, rec,
+                     (int64_t)p.recs, gate);
   const dim3 grid((unsigned)(p.n_itiles * p.groups * p.n_chunks));
   const bool vec = N_in % 4 == 0 && reinterpret_cast<uintptr_t>(trace_in) % 16 == 0;
   if (vec)

@@ -92,6 +92,30 @@ def test_dw_wide_band_columns_outside():
     assert torch.equal(dW, again)  # the order of the sums is fixed
 
 
+# one chunk (the records are the workspace's last array), several, and the dense product
+@pytest.mark.parametrize("T,B,n_in,n_out,share", [(10, 160, 4000, 2999, 0.1), (64, 100, 2312, 200, 0.15),
+                                                  (60, 10, 700, 400, 0.9)])
+@pytest.mark.parametrize("kind", ["alternating", "falling", "wild"])
+def test_dw_wide_band_malformed_row_pointers(T, B, n_in, n_out, share, kind):
+    """Row pointers that decrease or lie outside the entry arrays: dW is unspecified, and nothing is written past
+    the workspace."""
+    TB = T * B
+    rng = np.random.default_rng(5)
+    cap = int(share * TB * n_out)
+    rp = {"alternating": np.where(np.arange(TB + 1) % 2, 0, cap),
+          "falling": cap - (np.arange(TB + 1) * cap) // TB,
+          "wild": rng.integers(-2 ** 31, 2 ** 31, TB + 1)}[kind].astype(np.int32)
+    rp[::128] = cap  # windows that start at the last entry
+    rp[TB] = cap     # the entry count by which the way is chosen
+    dev = lambda x: torch.from_numpy(x).cuda()
+    col = dev(rng.integers(-1, n_out + 1, cap).astype(np.int32))
+    csr = snn.Csr(dev(rp), col, None, None, cap)
+    need = snn.snn_sparse_dw_workspace(T, B, n_in, n_out, cap)
+    room = torch.full((need + (1 << 22),), 0x5A, dtype=torch.uint8, device="cuda")
+    snn.sparse_dw(torch.rand((T, B, n_in), device="cuda"), csr, torch.rand(cap, device="cuda"), n_out, ws=room[:need])
+    assert (room[need:] == 0x5A).all()
+
+
 def _grad_in_reference(T, B, W, G, alpha):
     d = np.zeros((T, B, W.shape[1]))
     G = G.reshape(T, B, -1)
