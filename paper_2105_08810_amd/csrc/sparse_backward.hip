@@ -231,7 +231,7 @@ __global__ __launch_bounds__(kRowWaves * kWave) void slab_fill(int TB, int N_out
     const EntryKey x = entry_key(ee, E1, rp, nr, N_out, n_slabs, slab, col_idx);
     const int kq = x.key >= 0 ? x.key : 0;
     const int pos = __shfl(first, kq, kWave) + dw[kq] + (l - x.h);
-    if (x.key >= 0 && pos < nrec) {
+    if (x.key >= 0 && pos >= 0 && pos < nrec) {  // (overlapping rows of a malformed CSR: their counts may wrap)
       const int sl = kq % n_slabs;
       SlabRec r;
       r.off = (x.j - sl * slab) * kLd * (int)sizeof(double);
@@ -285,7 +285,7 @@ __global__ __launch_bounds__(kDwThreads) void dw_slab_kernel(const float* __rest
   // trace values and records are in flight and the row pointers of the one after it. Rows past
   // TB read sp[TB] (empty ranges); a row with no entry in this slab reads the batch's first
   // trace row instead of its own (a cache hit, never used).
-  auto load_sp = [&](int rb) { return spl[min(rb + min(l, kRowsPerBatch), r_hi)]; };
+  auto load_sp = [&](int rb) { return clamp_entry(spl[min(rb + min(l, kRowsPerBatch), r_hi)], nrec); };
   auto load_rest = [&](int rb, int spv, float* t0, float* t1, int2& ra) {
 #pragma unroll
     for (int k = 0; k < kRowsPerBatch; ++k) {
@@ -535,7 +535,7 @@ __global__ __launch_bounds__(kDwThreads) void dw_slab_spikes_kernel(
     tr1[k] = ck[row + ic1];
   }
   // lane k <= 8: row pointer of row t B + b0 + min(k, nbv) (rows past the samples: empty ranges)
-  auto load_sp = [&](int t) { return spl[(size_t)t * B + min(b0, B - 1) + min(l, nbv)]; };
+  auto load_sp = [&](int t) { return clamp_entry(spl[(size_t)t * B + min(b0, B - 1) + min(l, nbv)], nrec); };
   auto load_rec = [&](int spv) { return rec2[min((int64_t)rdlane(spv, 0) + l, nrec - 1)]; };
   auto load_spk = [&](int t, uint32_t* sk) {  // S[t] of the 8 samples at the lane's two inputs
 #pragma unroll

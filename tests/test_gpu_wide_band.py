@@ -92,6 +92,21 @@ def test_dw_wide_band_columns_outside():
     assert torch.equal(dW, again)  # the order of the sums is fixed
 
 
+def test_dw_rows_that_count_past_32_bits():
+    """Rows of a malformed CSR that together hold more than 2^31 entries: the offsets of the slab records wrap, and
+    no record is read or written outside the workspace."""
+    T, B, n_in, n_out, cap = 64, 100, 2312, 200, 700000
+    rp = torch.zeros(T * B + 1, dtype=torch.int32, device="cuda")
+    rp[1::2] = cap  # every second row spans all entries; the count says that there are none
+    col = (torch.arange(cap, device="cuda") % n_out).to(torch.int32)
+    csr = snn.Csr(rp, col, None, None, cap)
+    need = snn.snn_sparse_dw_workspace(T, B, n_in, n_out, cap)
+    room = torch.full((need + (1 << 23),), 0x5A, dtype=torch.uint8, device="cuda")
+    ws = room[1 << 22:(1 << 22) + need]
+    snn.sparse_dw(torch.rand((T, B, n_in), device="cuda"), csr, torch.rand(cap, device="cuda"), n_out, ws=ws)
+    assert (room[:1 << 22] == 0x5A).all() and (room[(1 << 22) + need:] == 0x5A).all()
+
+
 # one chunk (the records are the workspace's last array), several, and the dense product
 @pytest.mark.parametrize("T,B,n_in,n_out,share", [(10, 160, 4000, 2999, 0.1), (64, 100, 2312, 200, 0.15),
                                                   (60, 10, 700, 400, 0.9)])
