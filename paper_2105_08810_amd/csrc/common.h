@@ -77,7 +77,7 @@ struct Gate {
 __device__ __forceinline__ bool gate_open(const Gate& g) {
   if (!g.end) return true;
   int64_t n = *g.end;
-  n = n > g.cap ? g.cap : n;
+  n = n < 0 ? 0 : (n > g.cap ? g.cap : n);  // malformed too: one way always runs
   return n >= g.least && n < g.under;
 }
 

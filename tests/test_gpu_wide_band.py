@@ -131,6 +131,24 @@ def test_dw_wide_band_malformed_row_pointers(T, B, n_in, n_out, share, kind):
     assert (room[need:] == 0x5A).all()
 
 
+@pytest.mark.parametrize("end", [-1, -2 ** 31, 2 ** 31 - 1])
+def test_wide_band_malformed_count(end):
+    """Whatever the last row pointer holds, dW and the spike gradient are written (their values are unspecified)."""
+    T, B, n_in, n_out = 30, 20, 900, 300
+    rng = np.random.default_rng(6)
+    _, g, out, _ = _csr(rng, T, B, n_out, 0.95)
+    _, _, inp, _ = _csr(rng, T, B, n_in, 0.95)
+    eps = torch.from_numpy(rng.standard_normal(len(g)).astype(np.float32)).cuda()
+    out.row_ptr[T * B], inp.row_ptr[T * B] = end, end
+    dW = torch.full((n_in, n_out), np.nan, device="cuda")
+    snn.sparse_dw(torch.rand((T, B, n_in), device="cuda"), out, eps, n_out, dW=dW)
+    e_in = torch.full((inp.capacity,), np.nan, device="cuda")
+    snn.sparse_grad_in(torch.rand((n_in, n_out), device="cuda"), 0.9, T, B, out, eps, inp, eps_in=e_in)
+    assert torch.isfinite(dW).all()
+    rp = inp.row_ptr.cpu().numpy()
+    assert torch.isfinite(e_in[:int(rp[T * B - 1])]).all()  # every row but the last has its bounds
+
+
 def _grad_in_reference(T, B, W, G, alpha):
     d = np.zeros((T, B, W.shape[1]))
     G = G.reshape(T, B, -1)
