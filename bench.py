@@ -505,7 +505,7 @@ class Runner:
             self.ck = [self.torch.empty((nck, B, sizes[l]), dtype=self.torch.float32, device="cuda:0")
                        for l in range(L)]
         else:
-            self.ws_dw = [snn.workspace(snn.snn_sparse_dw_workspace(T, B, sizes[l], sizes[l + 1], self.caps[l]))
+            self.ws_dw = [snn.workspace(snn.snn_sparse_dw_workspace_full(T, B, sizes[l], sizes[l + 1], self.caps[l]))
                           for l in range(L)]
         self.dW = [self.torch.empty((sizes[l], sizes[l + 1]), dtype=self.torch.float32, device="cuda:0")
                    for l in range(L)]
@@ -740,7 +740,7 @@ class Runner:
         for l in range(L):
             n_in, n_out = sizes[l], sizes[l + 1]
             sparse = 4 * (TB + 1) + 12 * nnz[l] + 4 * n_in * n_out  # CSR (index, g), eps, dW
-            sparse += snn.snn_sparse_dw_workspace(T, B, n_in, n_out, nnz[l])
+            sparse += snn.snn_sparse_dw_workspace_full(T, B, n_in, n_out, nnz[l])
             dense = 4 * TB * n_out + 4 * n_in * n_out + snn.snn_dense_backward_workspace(T, B, n_in, n_out)
             if l > 0:
                 sparse += 4 * nnz[l - 1] + snn.snn_sparse_grad_in_workspace(T, B, n_out)

@@ -183,10 +183,13 @@ snn_status snn_active_compact_bits_noalloc(const uint64_t* active_bits, const fl
  *   copy of the active entries is built in it); for N_out <= 32 (narrow layers: G written
  *   densely, padded to 8, 16 or 32 columns) it holds that G and delta (T*B*ld floats each), a
  *   bitset of the rows with an entry and per-chunk partial dW, and does not depend on out_cap.
- *   When out_cap allows so many active entries that sums by column, or a dense product, may be the
- *   faster way to dW (from about 4% and 20% of a large layer's T*B*N_out on), it also has room for
- *   the entries sorted by column (8 bytes each) or G written densely (4 T*B*N_out bytes); which way
- *   is taken is decided on the device, by row_ptr[T*B].
+ *   Wide bands: with a workspace of snn_sparse_backward_workspace_full the call may also sum dW by
+ *   column or as a dense product, and form eps_in by a dense product, where row_ptr[T*B] (read on
+ *   the device) says that this is the faster way: from about 4% and 20% of a large layer's T*B*N_out
+ *   slots active for dW, 13% of T*B*N_in for eps_in. That workspace depends on out_cap and in_cap for
+ *   all layers of more than 32 outputs (it holds the entries sorted by column, 8 bytes each, or G,
+ *   4 T*B*N_out bytes; and delta, 4 T*B*N_out bytes). With the least size above
+ *   every sum goes entry by entry; a size in between may have room for one of these ways.
  *   aux_stream (may be NULL): a second hipStream_t. When given, the spike-gradient part runs on
  *   it beside the dW part on `stream`; the call makes aux_stream wait for the work already on
  *   `stream`, and `stream` wait for the aux work, so work enqueued on `stream` afterwards sees
@@ -197,6 +200,7 @@ snn_status snn_active_compact_bits_noalloc(const uint64_t* active_bits, const fl
  * Supported: N_out <= 4096.
  */
 size_t snn_sparse_backward_workspace(int T, int B, int N_in, int N_out, int64_t out_cap);
+size_t snn_sparse_backward_workspace_full(int T, int B, int N_in, int N_out, int64_t out_cap, int64_t in_cap);
 snn_status snn_sparse_backward(const float* W, const float* trace_in, int T, int B, int N_in, int N_out,
                                float alpha, const int32_t* out_row_ptr, const int32_t* out_col_idx,
                                const float* out_g, const float* eps_out, int64_t out_cap,
@@ -207,18 +211,22 @@ snn_status snn_sparse_backward(const float* W, const float* trace_in, int T, int
 /*
  * The two halves of snn_sparse_backward as calls of their own, for callers that schedule them
  * on different streams (the combined call does this itself when given aux_stream). Arguments
- * mean the same as in snn_sparse_backward; the results are the same as its results.
+ * mean the same as in snn_sparse_backward; the results are the same as its results, bit for bit
+ * when all workspaces are of the least size or all of the full one (the ways that a full one
+ * allows add in another order).
  *
  * snn_sparse_dw: dW of one layer (sparse form of Eq. (w_grad)), overwriting dW [N_in,N_out].
- *   Needs no W. Workspace from snn_sparse_dw_workspace (depends on out_cap).
+ *   Needs no W. Workspace from snn_sparse_dw_workspace, or from snn_sparse_dw_workspace_full for
+ *   the ways of wide bands (see snn_sparse_backward on both sizes).
  * snn_sparse_grad_in: the spike gradient eps_in at the input layer's active entries (sparse
  *   form of Eq. (s_grad) with Proposition 1's recurrence). in_row_ptr is required; nothing is
  *   written when in_cap = 0. share_cu != 0 keeps the walk to two blocks per compute unit, so
  *   that a kernel launched beside it on another stream (dW) finds room; 0 uses the whole GPU.
- *   Workspace from snn_sparse_grad_in_workspace.
+ *   Workspace from snn_sparse_grad_in_workspace or snn_sparse_grad_in_workspace_full.
  * The two calls use separate workspaces and may run concurrently.
  */
 size_t snn_sparse_dw_workspace(int T, int B, int N_in, int N_out, int64_t out_cap);
+size_t snn_sparse_dw_workspace_full(int T, int B, int N_in, int N_out, int64_t out_cap);
 snn_status snn_sparse_dw(const float* trace_in, int T, int B, int N_in, int N_out,
                          const int32_t* out_row_ptr, const int32_t* out_col_idx, const float* out_g,
                          const float* eps_out, int64_t out_cap, float* dW, void* workspace,
@@ -228,10 +236,11 @@ snn_status snn_sparse_dw(const float* trace_in, int T, int B, int N_in, int N_ou
  * run early (right after compaction, before any eps exists) and off the critical path:
  * snn_sparse_dw_layout reads out_row_ptr and out_col_idx only and writes the per-(row, column
  * slab) entry counts and offsets (or, for N_out <= 32, the bitset of rows with an entry; for
- * layers that take the CSR-direct dW, nothing) into the workspace; snn_sparse_dw_prepared then does the rest of snn_sparse_dw (arguments as there) and
- * gives the same dW bit for bit, provided the layout ran on the same workspace with a CSR of the
- * same structure (row pointers and columns) and out_cap, and the workspace was not used in
- * between. Workspace from snn_sparse_dw_workspace. Errors as snn_sparse_dw.
+ * layers that take the CSR-direct dW or, by their count, a way of wide bands, nothing) into the
+ * workspace; snn_sparse_dw_prepared then does the rest of snn_sparse_dw (arguments as there) and
+ * gives the same dW bit for bit, provided the layout ran on the same workspace of the same
+ * workspace_bytes with a CSR of the same structure (row pointers and columns) and out_cap, and the
+ * workspace was not used in between. Workspaces and errors as snn_sparse_dw.
  */
 snn_status snn_sparse_dw_layout(int T, int B, int N_in, int N_out, const int32_t* out_row_ptr,
                                 const int32_t* out_col_idx, int64_t out_cap, void* workspace,
@@ -241,14 +250,7 @@ snn_status snn_sparse_dw_prepared(const float* trace_in, int T, int B, int N_in,
                                   const float* eps_out, int64_t out_cap, float* dW, void* workspace,
                                   size_t workspace_bytes, void* stream);
 size_t snn_sparse_grad_in_workspace(int T, int B, int N_out);
-/*
- * The spike gradient's workspace with room for delta written densely where in_cap allows so many input
- * entries that a dense product may be the faster way (from about 13% of a large layer's slots on); given at
- * least this much, snn_sparse_grad_in takes that way when in_row_ptr[T*B] says so. With the smaller workspace
- * it goes entry by entry. snn_sparse_backward likewise, with the second query.
- */
 size_t snn_sparse_grad_in_workspace_full(int T, int B, int N_in, int N_out, int64_t in_cap);
-size_t snn_sparse_backward_workspace_full(int T, int B, int N_in, int N_out, int64_t out_cap, int64_t in_cap);
 snn_status snn_sparse_grad_in(const float* W, int T, int B, int N_in, int N_out, float alpha,
                               const int32_t* out_row_ptr, const int32_t* out_col_idx,
                               const float* out_g, const float* eps_out, int64_t out_cap,

@@ -725,14 +725,28 @@ DenseDwPlan plan_dw_dense(int T, int B, int N_in, int N_out) {
   return p;
 }
 
-// Whether a layer with out_cap entry slots may hold enough of them for the columns kernel; for the dense product.
-bool dw_cols_possible(int T, int B, int N_in, int N_out, int64_t out_cap) {
-  const DenseDwPlan p = plan_dw_dense(T, B, N_in, N_out);
-  return p.cols_least < p.least && out_cap >= p.cols_least;
-}
+// The ways that a layer with out_cap entry slots may take beside entry by entry, and the workspace they need (each
+// uses it from the start: one of the ways runs).
+struct DwWays {
+  DenseDwPlan plan{};
+  bool cols = false, dense = false;
+  size_t bytes = 0;
+};
 
-bool dw_dense_possible(int T, int B, int N_in, int N_out, int64_t out_cap) {
-  return N_out > 32 && out_cap >= plan_dw_dense(T, B, N_in, N_out).least;
+DwWays plan_dw_ways(int T, int B, int N_in, int N_out, int64_t out_cap) {
+  DwWays q{};
+  if (N_out <= 32) return q;
+  q.plan = plan_dw_dense(T, B, N_in, N_out);
+  q.cols = q.plan.cols_least < q.plan.least && out_cap >= q.plan.cols_least;
+  q.dense = out_cap >= q.plan.least;
+  if (q.dense) {
+    Carve c(nullptr);
+    c.take<float>((size_t)T * B * N_out);
+    if (q.plan.splits > 1) c.take<float>((size_t)q.plan.splits * N_in * N_out);
+    q.bytes = c.off;
+  }
+  if (q.cols) q.bytes = std::max(q.bytes, cols_workspace(T, B, N_in, N_out, out_cap));
+  return q;
 }
 
 // ------------------------------------------------------------------ narrow layers
@@ -1437,19 +1451,9 @@ size_t dw_workspace(int T, int B, int N_in, int N_out, int64_t out_cap) {
     return c.off;
   }
   if (mdw_eligible(T, B, N_in, N_out, out_cap)) return mdw_workspace(T, B, N_in, N_out, out_cap);
-  size_t dense = 0;  // the dense product's G and partials, in the same place (one of the two ways runs)
-  if (dw_dense_possible(T, B, N_in, N_out, out_cap)) {
-    Carve c(nullptr);
-    c.take<float>((size_t)T * B * N_out);
-    const int splits = plan_dw_dense(T, B, N_in, N_out).splits;
-    if (splits > 1) c.take<float>((size_t)splits * N_in * N_out);
-    dense = c.off;
-  }
-  if (dw_cols_possible(T, B, N_in, N_out, out_cap))
-    dense = std::max(dense, cols_workspace(T, B, N_in, N_out, out_cap));
   if (dw_rows_eligible(N_in, N_out)) {  // the chunk partials only
     const DwPlan p = plan_dw_rows(T, B, N_in, N_out);
-    return std::max(dense, p.n_chunks > 1 ? (size_t)p.n_chunks * N_in * N_out * sizeof(float) : 256);
+    return p.n_chunks > 1 ? (size_t)p.n_chunks * N_in * N_out * sizeof(float) : 256;
   }
   const DwPlan p = plan_dw_interleaved(T, B, N_in, N_out);
   const int nsp = p.n_slabs * T * B;
@@ -1459,7 +1463,14 @@ size_t dw_workspace(int T, int B, int N_in, int N_out, int64_t out_cap) {
   c.take<int32_t>((size_t)nsp);
   c.take<int32_t>(scan_temp_elems(nsp));
   c.take<SlabRec>((size_t)std::max<int64_t>(out_cap, 1));
-  return std::max(dense, c.off);
+  return c.off;
+}
+
+// With room for the ways of wide bands where the layer may hold enough entries for them.
+size_t dw_workspace_full(int T, int B, int N_in, int N_out, int64_t out_cap) {
+  const size_t least = dw_workspace(T, B, N_in, N_out, out_cap);
+  if (mdw_eligible(T, B, N_in, N_out, out_cap)) return least;
+  return std::max(least, plan_dw_ways(T, B, N_in, N_out, out_cap).bytes);
 }
 
 // The spike gradient with many input entries: delta written densely by the walk, then delta W^T on the matrix
@@ -1527,7 +1538,7 @@ enum DwPhase { kDwAll, kDwLayout, kDwRest };
 
 void enqueue_dw(const float* trace_in, int T, int B, int N_in, int N_out, const int32_t* out_row_ptr,
                 const int32_t* out_col_idx, const float* out_g, const float* eps_out, int64_t out_cap, float* dW,
-                void* workspace, hipStream_t s, bool g_ready = false, DwPhase phase = kDwAll) {
+                void* workspace, size_t workspace_bytes, hipStream_t s, bool g_ready = false, DwPhase phase = kDwAll) {
   const bool layout = phase != kDwRest, rest = phase != kDwLayout;
   if (out_cap == 0) {  // no active output entry: dW = 0 and no entry array is read
     if (rest) fill_zero_async(dW, (size_t)N_in * N_out, s);
@@ -1568,14 +1579,14 @@ void enqueue_dw(const float* trace_in, int T, int B, int N_in, int N_out, const 
   }
   // Entry by entry with few active entries, by columns with more, a dense product with most slots active; which,
   // the kernels decide by the CSR's own count (out_cap is an upper bound of it), so all that are possible are
-  // enqueued.
+  // enqueued where the caller gave the room.
   Gate few{}, wide{}, most{};
-  DenseDwPlan dense{};
-  const bool maybe_dense = dw_dense_possible(T, B, N_in, N_out, out_cap);
-  const bool maybe_cols = dw_cols_possible(T, B, N_in, N_out, out_cap);
-  if (maybe_dense || maybe_cols) {
+  const DwWays ways = plan_dw_ways(T, B, N_in, N_out, out_cap);
+  const DenseDwPlan& dense = ways.plan;
+  const bool room = workspace_bytes >= ways.bytes;
+  const bool maybe_cols = ways.cols && room, maybe_dense = ways.dense && room;
+  if (maybe_cols || maybe_dense) {
     const int32_t* end = out_row_ptr + (size_t)T * B;
-    dense = plan_dw_dense(T, B, N_in, N_out);
     few = Gate{end, out_cap, 0, dense.cols_least};
     wide = Gate{end, out_cap, dense.cols_least, dense.least};
     most = Gate{end, out_cap, dense.least};
@@ -1841,6 +1852,11 @@ extern "C" size_t snn_sparse_dw_workspace(int T, int B, int N_in, int N_out, int
   return dw_workspace(T, B, N_in, N_out, out_cap);
 }
 
+extern "C" size_t snn_sparse_dw_workspace_full(int T, int B, int N_in, int N_out, int64_t out_cap) {
+  if (!dims_ok(T, B, N_in, N_out) || out_cap < 0) return 0;
+  return dw_workspace_full(T, B, N_in, N_out, out_cap);
+}
+
 extern "C" snn_status snn_sparse_dw(const float* trace_in, int T, int B, int N_in, int N_out,
                                     const int32_t* out_row_ptr, const int32_t* out_col_idx, const float* out_g,
                                     const float* eps_out, int64_t out_cap, float* dW, void* workspace,
@@ -1850,7 +1866,7 @@ extern "C" snn_status snn_sparse_dw(const float* trace_in, int T, int B, int N_i
   if (!workspace || workspace_bytes < dw_workspace(T, B, N_in, N_out, out_cap)) return SNN_ERR_INVALID_ARG;
   if (N_out > 4096) return SNN_ERR_UNSUPPORTED;
   enqueue_dw(trace_in, T, B, N_in, N_out, out_row_ptr, out_col_idx, out_g, eps_out, out_cap, dW, workspace,
-             static_cast<hipStream_t>(stream));
+             workspace_bytes, static_cast<hipStream_t>(stream));
   return launch_status();
 }
 
@@ -1862,7 +1878,7 @@ extern "C" snn_status snn_sparse_dw_layout(int T, int B, int N_in, int N_out, co
   if (!workspace || workspace_bytes < dw_workspace(T, B, N_in, N_out, out_cap)) return SNN_ERR_INVALID_ARG;
   if (N_out > 4096) return SNN_ERR_UNSUPPORTED;
   enqueue_dw(nullptr, T, B, N_in, N_out, out_row_ptr, out_col_idx, nullptr, nullptr, out_cap, nullptr, workspace,
-             static_cast<hipStream_t>(stream), false, kDwLayout);
+             workspace_bytes, static_cast<hipStream_t>(stream), false, kDwLayout);
   return launch_status();
 }
 
@@ -1875,7 +1891,7 @@ extern "C" snn_status snn_sparse_dw_prepared(const float* trace_in, int T, int B
   if (!workspace || workspace_bytes < dw_workspace(T, B, N_in, N_out, out_cap)) return SNN_ERR_INVALID_ARG;
   if (N_out > 4096) return SNN_ERR_UNSUPPORTED;
   enqueue_dw(trace_in, T, B, N_in, N_out, out_row_ptr, out_col_idx, out_g, eps_out, out_cap, dW, workspace,
-             static_cast<hipStream_t>(stream), false, kDwRest);
+             workspace_bytes, static_cast<hipStream_t>(stream), false, kDwRest);
   return launch_status();
 }
 
@@ -1948,7 +1964,7 @@ extern "C" size_t snn_sparse_backward_workspace(int T, int B, int N_in, int N_ou
 extern "C" size_t snn_sparse_backward_workspace_full(int T, int B, int N_in, int N_out, int64_t out_cap,
                                                      int64_t in_cap) {
   if (!dims_ok(T, B, N_in, N_out) || out_cap < 0 || in_cap < 0) return 0;
-  return align256(dw_workspace(T, B, N_in, N_out, out_cap)) + gin_workspace_full(T, B, N_in, N_out, in_cap);
+  return align256(dw_workspace_full(T, B, N_in, N_out, out_cap)) + gin_workspace_full(T, B, N_in, N_out, in_cap);
 }
 
 namespace {
@@ -1990,7 +2006,9 @@ extern "C" snn_status snn_sparse_backward(const float* W, const float* trace_in,
 
   hipStream_t s = static_cast<hipStream_t>(stream);
   char* dw_ws = static_cast<char*>(workspace);
-  const size_t dw_bytes = align256(dw_workspace(T, B, N_in, N_out, out_cap));
+  // dW's full share where it leaves room for the spike gradient's least
+  size_t dw_bytes = align256(dw_workspace_full(T, B, N_in, N_out, out_cap));
+  if (workspace_bytes < dw_bytes + gin_workspace(T, B, N_out)) dw_bytes = align256(dw_workspace(T, B, N_in, N_out, out_cap));
   char* gin_ws = dw_ws + dw_bytes;
   const bool do_gin = grad_in && in_cap > 0;
   // A narrow layer's dense G is written once, at the front of the dW workspace, before the fork.
@@ -2017,7 +2035,8 @@ extern "C" snn_status snn_sparse_backward(const float* W, const float* trace_in,
                     in_col_idx, in_cap, eps_in, sa != s && dw_longer, gin_ws, workspace_bytes - dw_bytes, sa,
                     narrow_g ? reinterpret_cast<const float*>(dw_ws) : nullptr);
   }
-  enqueue_dw(trace_in, T, B, N_in, N_out, out_row_ptr, out_col_idx, out_g, eps_out, out_cap, dW, dw_ws, s, narrow_g);
+  enqueue_dw(trace_in, T, B, N_in, N_out, out_row_ptr, out_col_idx, out_g, eps_out, out_cap, dW, dw_ws, dw_bytes, s,
+             narrow_g);
   if (sa != s && (hipEventRecord(ev_out, sa) != hipSuccess || hipStreamWaitEvent(s, ev_out, 0) != hipSuccess))
     return SNN_ERR_HIP;  // the join failed: later work on stream is not ordered after eps_in
   return launch_status();

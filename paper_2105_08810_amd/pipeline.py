@@ -176,7 +176,7 @@ class Network:
         with torch.cuda.stream(aux):
             for l in range(L - 1, -1, -1):  # top layer first: its dW comes first
                 n_in, n_out = self.Ws[l].shape
-                ws = snn.workspace(snn.snn_sparse_dw_workspace(T, B, n_in, n_out, csrs[l].capacity), self.X.device)
+                ws = snn.workspace(snn.snn_sparse_dw_workspace_full(T, B, n_in, n_out, csrs[l].capacity), self.X.device)
                 snn.sparse_dw_layout((T, B, n_in), csrs[l], n_out, ws, stream=aux)
                 ev = torch.cuda.Event()
                 ev.record(aux)

@@ -43,6 +43,7 @@ _SIGNATURES = {
     "snn_active_compact_bits_place": (_I, [_P, _P, _I, _I, _I, _F, _F, _P, _P, _P, _I64, _P]),
     "snn_active_compact_bits_noalloc": (_I, [_P, _P, _I, _I, _I, _F, _F, _P, _P, _P, _I64, _P, _P]),
     "snn_sparse_dw_workspace": (_SZ, [_I, _I, _I, _I, _I64]),
+    "snn_sparse_dw_workspace_full": (_SZ, [_I, _I, _I, _I, _I64]),
     "snn_sparse_dw": (_I, [_P, _I, _I, _I, _I, _P, _P, _P, _P, _I64, _P, _P, _SZ, _P]),
     "snn_sparse_dw_layout": (_I, [_I, _I, _I, _I, _P, _P, _I64, _P, _SZ, _P]),
     "snn_sparse_dw_prepared": (_I, [_P, _I, _I, _I, _I, _P, _P, _P, _P, _I64, _P, _P, _SZ, _P]),
@@ -223,6 +224,10 @@ def snn_sparse_backward(W, trace_in, T, B, N_in, N_out, alpha, out_row_ptr, out_
 
 def snn_sparse_dw_workspace(T, B, N_in, N_out, out_cap) -> int:
     return int(lib().snn_sparse_dw_workspace(T, B, N_in, N_out, int(out_cap)))
+
+
+def snn_sparse_dw_workspace_full(T, B, N_in, N_out, out_cap) -> int:
+    return int(lib().snn_sparse_dw_workspace_full(T, B, N_in, N_out, int(out_cap)))
 
 
 def snn_sparse_dw(trace_in, T, B, N_in, N_out, out_row_ptr, out_col_idx, out_g, eps_out, out_cap, dW, ws,
@@ -578,7 +583,7 @@ def sparse_dw(trace_in, out: Csr, eps_out, N_out, ws=None, stream=None, dW=None)
     if dW is None:
         dW = torch.empty((N_in, N_out), dtype=torch.float32, device=dev)
     if ws is None:
-        ws = workspace(snn_sparse_dw_workspace(T, B, N_in, N_out, out.capacity), dev)
+        ws = workspace(snn_sparse_dw_workspace_full(T, B, N_in, N_out, out.capacity), dev)
     snn_sparse_dw(trace_in, T, B, N_in, N_out, out.row_ptr, out.col_idx, out.g, eps_out, out.capacity, dW, ws,
                   stream)
     return dW

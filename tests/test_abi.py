@@ -240,6 +240,25 @@ def test_sparse_grad_in_rejects(lib, kw):
     assert _sgi(lib, **kw) == snn.SNN_ERR_INVALID_ARG
 
 
+@pytest.mark.parametrize("T,B,n_in,n_out", [(30, 37, 900, 130), (500, 256, 1024, 300), (100, 256, 784, 200)])
+def test_least_workspace_does_not_depend_on_the_capacity(lib, T, B, n_in, n_out):
+    """Layers of 33..300 outputs and at most 1024 inputs: a workspace sized once serves every capacity; the room for
+    the ways of wide bands is asked for by the _full queries."""
+    every = T * B * n_out
+    least = lib.snn_sparse_dw_workspace(T, B, n_in, n_out, 10)
+    both = lib.snn_sparse_backward_workspace(T, B, n_in, n_out, 10)
+    for cap in (0, every // 10, every // 4, every):
+        assert lib.snn_sparse_dw_workspace(T, B, n_in, n_out, cap) == least
+        assert lib.snn_sparse_backward_workspace(T, B, n_in, n_out, cap) == both
+        full = lib.snn_sparse_dw_workspace_full(T, B, n_in, n_out, cap)
+        assert full >= least
+        assert (lib.snn_sparse_backward_workspace_full(T, B, n_in, n_out, cap, T * B * n_in)
+                >= full + lib.snn_sparse_grad_in_workspace_full(T, B, n_in, n_out, T * B * n_in))
+    assert lib.snn_sparse_dw_workspace_full(T, B, n_in, n_out, every) >= 4 * every  # G for the dense product
+    assert lib.snn_sparse_dw_workspace_full(0, B, n_in, n_out, 1) == 0
+    assert lib.snn_sparse_dw_workspace_full(T, B, n_in, n_out, -1) == 0
+
+
 def test_split_workspaces(lib):
     dw = lib.snn_sparse_dw_workspace(500, 256, 1024, 1024, 10 ** 6)
     gi = lib.snn_sparse_grad_in_workspace(500, 256, 1024)

@@ -107,6 +107,43 @@ def test_dw_rows_that_count_past_32_bits():
     assert (room[:1 << 22] == 0x5A).all() and (room[(1 << 22) + need:] == 0x5A).all()
 
 
+@pytest.mark.parametrize("T,B,n_in,n_out,share", [(30, 37, 900, 130, 0.97), (60, 10, 700, 400, 0.9),
+                                                  (64, 100, 2312, 200, 0.15)])
+@pytest.mark.parametrize("full", [False, True])
+def test_wide_band_workspace_sizes(T, B, n_in, n_out, share, full):
+    """The least workspace (for some layers sized without regard to the capacity) and the full one: dW and the spike
+    gradient are right, the combined call gives the split calls' bits, and nothing is written behind either."""
+    rng = np.random.default_rng(8)
+    on, g, out, _ = _csr(rng, T, B, n_out, share)
+    on_i, _, inp, _ = _csr(rng, T, B, n_in, 0.95)
+    eps = rng.standard_normal(len(g)).astype(np.float32)
+    trace = (rng.random((T, B, n_in)) * 2).astype(np.float32)
+    W = rng.standard_normal((n_in, n_out)).astype(np.float32)
+    alpha = float(np.float32(0.9))
+    dev = lambda x: torch.from_numpy(x).cuda()
+    q = snn
+    cap = 100 if n_out <= 300 and n_in <= 1024 else out.capacity
+    sizes = ((q.snn_sparse_dw_workspace_full(T, B, n_in, n_out, out.capacity),
+              q.snn_sparse_grad_in_workspace_full(T, B, n_in, n_out, inp.capacity),
+              q.snn_sparse_backward_workspace_full(T, B, n_in, n_out, out.capacity, inp.capacity)) if full else
+             (q.snn_sparse_dw_workspace(T, B, n_in, n_out, cap), q.snn_sparse_grad_in_workspace(T, B, n_out),
+              q.snn_sparse_backward_workspace(T, B, n_in, n_out, cap)))
+    rooms = [torch.full((n + (1 << 20),), 0x5A, dtype=torch.uint8, device="cuda") for n in sizes]
+    ws = [r[:n] for r, n in zip(rooms, sizes)]
+    dW = snn.sparse_dw(dev(trace), out, dev(eps), n_out, ws=ws[0])
+    e_in = snn.sparse_grad_in(dev(W), alpha, T, B, out, dev(eps), inp, ws=ws[1])
+    dW2, e_in2 = snn.sparse_backward(dev(W), dev(trace), alpha, out, dev(eps), inp, ws=ws[2])
+    for r, n in zip(rooms, sizes):
+        assert (r[n:] == 0x5A).all()
+    assert torch.equal(dW, dW2) and torch.equal(e_in, e_in2)
+    G = np.zeros(on.shape)
+    G[on] = (eps * g).astype(np.float64)
+    tr = trace.reshape(T * B, n_in).astype(np.float64)
+    assert (np.abs(dW.cpu().numpy() - tr.T @ G) <= 4 * U * (tr.T @ np.abs(G))).all()
+    r, a = (_grad_in_reference(T, B, x, y, alpha)[on_i] for x, y in ((W, G), (np.abs(W), np.abs(G))))
+    assert (np.abs(e_in.cpu().numpy() - r) <= 50 * U * a).all()
+
+
 # one chunk (the records are the workspace's last array), several, and the dense product
 @pytest.mark.parametrize("T,B,n_in,n_out,share", [(10, 160, 4000, 2999, 0.1), (64, 100, 2312, 200, 0.15),
                                                   (60, 10, 700, 400, 0.9)])
@@ -125,7 +162,7 @@ def test_dw_wide_band_malformed_row_pointers(T, B, n_in, n_out, share, kind):
     dev = lambda x: torch.from_numpy(x).cuda()
     col = dev(rng.integers(-1, n_out + 1, cap).astype(np.int32))
     csr = snn.Csr(dev(rp), col, None, None, cap)
-    need = snn.snn_sparse_dw_workspace(T, B, n_in, n_out, cap)
+    need = snn.snn_sparse_dw_workspace_full(T, B, n_in, n_out, cap)
     room = torch.full((need + (1 << 22),), 0x5A, dtype=torch.uint8, device="cuda")
     snn.sparse_dw(torch.rand((T, B, n_in), device="cuda"), csr, torch.rand(cap, device="cuda"), n_out, ws=room[:need])
     assert (room[need:] == 0x5A).all()
