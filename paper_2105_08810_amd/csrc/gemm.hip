@@ -6,8 +6,8 @@
 // form 16-bit products exactly and sum them in float32. hh goes to one accumulator and the five small
 // terms to another, so the leading sum is rounded once per 8 products of K (a float32 MFMA chain: once
 // per 1 or 2). bf16 has float32's exponent range, so no scaling is needed; values of 2^127 and more (and
-// infinities, which a split would turn into NaN) make the block that met one form its tile again on the
-// float32 matrix cores.
+// infinities, which a split would turn into NaN) and sums that come out infinite or NaN make the block that met
+// one form its tile again on the float32 matrix cores.
 //
 // Bound: the matrix cores, six bf16 products per float32 one (2.5 PFLOP/s / 6 = 417 TFLOP/s of useful
 // work at the nominal rate; the float32 MFMA's nominal rate is 157). A block of four wavefronts owns
@@ -274,7 +274,19 @@ __global__ __launch_bounds__(kThreads, 2) void gemm_split3(int M, int N, int K, 
     __syncthreads();
   }
   fold();
-  if (__syncthreads_or(big >= kWide)) {  // a value out of the split's range: the same sums in float32
+  // a value out of the split's range, or a sum that is not finite (products past the range in several terms may
+  // have met as opposite infinities): the same sums in float32
+  bool again = big >= kWide;
+#pragma unroll
+  for (int a = 0; a < 4; ++a)
+#pragma unroll
+    for (int b = 0; b < TN; ++b)
+#pragma unroll
+      for (int v = 0; v < 4; ++v) {
+        if constexpr (GATHER) again |= !(fabs(total[a][b][v]) < INFINITY);
+        else again |= !(fabsf(lead[a][b][v] + rest[a][b][v]) < INFINITY);
+      }
+  if (__syncthreads_or(again)) {
     WideStage<kBM>& Aw = *reinterpret_cast<WideStage<kBM>*>(&As);
     WideStage<BN>& Bw = *reinterpret_cast<WideStage<BN>*>(&Bs);
     clear();

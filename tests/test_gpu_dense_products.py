@@ -63,3 +63,18 @@ def test_dense_products_outside_the_split(value):
         ok = np.isfinite(r)
         assert np.array_equal(x[np.isinf(r)], r[np.isinf(r)])
         assert (np.abs(x[ok] - r[ok]) <= 1e-5 * np.maximum(np.abs(r[ok]), 1.0)).all()
+
+
+def test_dense_products_past_the_range():
+    """Products past float32's range are infinities of the product's sign, as float32 products give them, whatever
+    the signs of the operands' parts."""
+    T, B, n_in, n_out = 2, 130, 140, 136
+    rng = np.random.default_rng(9)
+    eps = np.zeros((T, B, n_out), np.float32)
+    eps[1, np.arange(B), rng.integers(0, n_out, B)] = rng.uniform(0.5, 2, B) * 1e25 * rng.choice([-1, 1], B)
+    trace = (rng.random((T, B, n_in)) < 0.5).astype(np.float32)
+    W = (rng.uniform(0.5, 2, (n_in, n_out)) * 1e20 * rng.choice([-1, 1], (n_in, n_out))).astype(np.float32)
+    dW, gi = _run(T, B, n_in, n_out, eps, trace, W, 0.5)
+    rW, rg = _reference(eps, trace, W, 0.5)
+    assert (np.abs(rg[0]) > 1e44).all() and np.array_equal(gi[0], np.sign(rg[0]) * INF)
+    assert (np.abs(dW - rW) <= 1e-5 * np.abs(rW)).all()

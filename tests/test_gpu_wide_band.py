@@ -220,6 +220,22 @@ def test_grad_in_wide_band(T, B, n_in, n_out, share_out, share_in, spare):
     assert (got[len(r):] == 7.0).all()  # slots without an entry stay as they are
 
 
+def test_grad_in_wide_band_past_the_range():
+    """Products past float32's range are infinities of the product's sign."""
+    T, B, n_in, n_out = 2, 700, 640, 136
+    rng = np.random.default_rng(13)
+    j = rng.integers(0, n_out, B)  # one entry in every row of the last step; all input entries, enough for the dense product
+    rp = np.concatenate([np.zeros(B), np.arange(B + 1)]).astype(np.int32)
+    eps = (rng.uniform(0.5, 2, B) * 1e25 * rng.choice([-1, 1], B)).astype(np.float32)
+    W = (rng.uniform(0.5, 2, (n_in, n_out)) * 1e20 * rng.choice([-1, 1], (n_in, n_out))).astype(np.float32)
+    dev = lambda x: torch.from_numpy(x).cuda()
+    out = snn.Csr(dev(rp), dev(j.astype(np.int32)), None, None, B)
+    on_i, _, inp, _ = _csr(rng, T, B, n_in, 1.0)
+    e_in = snn.sparse_grad_in(dev(W), 0.5, T, B, out, dev(eps), inp).cpu().numpy().reshape(T, B, n_in)
+    assert np.array_equal(e_in[0], np.sign(eps[:, None] * W[:, j].T.astype(np.float64)) * np.inf)
+    assert (e_in[1] == 0).all()
+
+
 def test_grad_in_wide_band_truncated_and_columns_outside():
     """Entries past the input capacity are not written; an entry with a column outside the layer reads 0."""
     T, B, n_in, n_out = 30, 20, 900, 300
