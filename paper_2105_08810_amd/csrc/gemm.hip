@@ -5,9 +5,9 @@
 // leading one (hh, hm, mh, mm, hl, lh; what is left out is below 2^-24 of |x||y|), and the matrix cores
 // form 16-bit products exactly and sum them in float32. hh goes to one accumulator and the five small
 // terms to another, so the leading sum is rounded once per 8 products of K (a float32 MFMA chain: once
-// per 1 or 2). bf16 has float32's exponent range, so no scaling is needed; values of 2^127 and more (and
-// infinities, which a split would turn into NaN) and sums that come out infinite or NaN make the block that met
-// one form its tile again on the float32 matrix cores.
+// per 1 or 2). The operands are scaled by 2^24, so that the parts of every float32 value are normal bf16
+// values; a sum that comes out infinite or NaN (an operand of 2^104 and more, an infinity or a NaN, a sum of 2^80
+// and more) makes its block form the tile again on the float32 matrix cores.
 //
 // Bound: the matrix cores, six bf16 products per float32 one (2.5 PFLOP/s / 6 = 417 TFLOP/s of useful
 // work at the nominal rate; the float32 MFMA's nominal rate is 157). A block of four wavefronts owns
@@ -32,7 +32,11 @@ typedef float f32x4 __attribute__((ext_vector_type(4)));
 constexpr int kBM = 128, kBN = 128, kBK = 32;
 constexpr int kThreads = 256;
 constexpr int kKC = kBK / 8;      // pieces of 8 k per row and stage
-constexpr float kWide = 1.7e38f;  // 2^127 rounded down: bf16 rounding cannot overflow below it
+// Operands are taken times 2^24: the parts of every float32, down to the last bit of the smallest subnormal, are
+// then normal bf16 values (unscaled, values below 2^-109 lose bits of the third part, below 2^-117 of the second).
+// Sums come out times 2^48. A value that scaled rounds past bf16's range (2^104 and half a bf16 step below it) has an
+// infinite or NaN part, and every sum it enters is infinite or NaN (infinity times 0 included).
+constexpr float kUp = 0x1p24f, kDown = 0x1p-48f;
 
 // Eight values into their three parts, 16 bytes each.
 __device__ __forceinline__ void split8(const float (&x)[8], uint4& h, uint4& m, uint4& l) {
@@ -101,14 +105,15 @@ struct Stage {
 };
 
 template <bool KM, int ROWS>
-__device__ __forceinline__ void store_stage(Stage<ROWS>& S, const float (&x)[ROWS / 64][8], float& big) {
+__device__ __forceinline__ void store_stage(Stage<ROWS>& S, const float (&x)[ROWS / 64][8]) {
 #pragma unroll
   for (int q = 0; q < ROWS / 64; ++q) {
     int row, kc;
     piece_of<KM, ROWS>(q, row, kc);
+    float y[8];
 #pragma unroll
-    for (int u = 0; u < 8; u += 2) big = fmaxf(fmaxf(big, fabsf(x[q][u])), fabsf(x[q][u + 1]));
-    split8(x[q], S.x[0][kc][row], S.x[1][kc][row], S.x[2][kc][row]);
+    for (int u = 0; u < 8; ++u) y[u] = x[q][u] * kUp;
+    split8(y, S.x[0][kc][row], S.x[1][kc][row], S.x[2][kc][row]);
   }
 }
 
@@ -236,15 +241,14 @@ __global__ __launch_bounds__(kThreads, 2) void gemm_split3(int M, int N, int K, 
   }
 
   float xa[2][8], xb[BN / 64][8];
-  float big = 0.0f;
   if (k_lo < k_hi) {
     load_stage<KM, VEC, kBM>(A, lda, m0, M, k_lo, k_hi, xa);
     load_stage<KM, VEC, BN>(B, ldb, n0, N, k_lo, k_hi, xb);
   }
   int stage = 0;
   for (int k0 = k_lo; k0 < k_hi; k0 += kBK) {
-    store_stage<KM, kBM>(As, xa, big);
-    store_stage<KM, BN>(Bs, xb, big);
+    store_stage<KM, kBM>(As, xa);
+    store_stage<KM, BN>(Bs, xb);
     __syncthreads();
     if (k0 + kBK < k_hi) {
       load_stage<KM, VEC, kBM>(A, lda, m0, M, k0 + kBK, k_hi, xa);
@@ -274,9 +278,10 @@ __global__ __launch_bounds__(kThreads, 2) void gemm_split3(int M, int N, int K, 
     __syncthreads();
   }
   fold();
-  // a value out of the split's range, or a sum that is not finite (products past the range in several terms may
-  // have met as opposite infinities): the same sums in float32
-  bool again = big >= kWide;
+  float down = kDown;
+  // a sum that is not finite (a value or products out of the split's range, in several terms perhaps as opposite
+  // infinities; or a NaN of the operands): the same sums in float32
+  bool again = false;
 #pragma unroll
   for (int a = 0; a < 4; ++a)
 #pragma unroll
@@ -290,6 +295,7 @@ __global__ __launch_bounds__(kThreads, 2) void gemm_split3(int M, int N, int K, 
     WideStage<kBM>& Aw = *reinterpret_cast<WideStage<kBM>*>(&As);
     WideStage<BN>& Bw = *reinterpret_cast<WideStage<BN>*>(&Bs);
     clear();
+    down = 1.0f;
     for (int k0 = k_lo; k0 < k_hi; k0 += kBK) {
       load_stage<KM, VEC, kBM>(A, lda, m0, M, k0, k_hi, xa);
       load_stage<KM, VEC, BN>(B, ldb, n0, N, k0, k_hi, xb);
@@ -326,7 +332,7 @@ __global__ __launch_bounds__(kThreads, 2) void gemm_split3(int M, int N, int K, 
         for (int v = 0; v < 4; ++v) {
           const int m = m0 + wm + 16 * a + 4 * lk + v;
           const int n = n0 + wn + 16 * b + lr;
-          if (m < M && n < N) Cz[(size_t)m * ldc + n] = lead[a][b][v] + rest[a][b][v];
+          if (m < M && n < N) Cz[(size_t)m * ldc + n] = (lead[a][b][v] + rest[a][b][v]) * down;
         }
   } else {
     float(*tile)[BN + 4] = reinterpret_cast<float(*)[BN + 4]>(lds);
@@ -338,7 +344,7 @@ __global__ __launch_bounds__(kThreads, 2) void gemm_split3(int M, int N, int K, 
 #pragma unroll
           for (int b = 0; b < TN; ++b)
 #pragma unroll
-            for (int v = 0; v < 4; ++v) tile[16 * a + 4 * lk + v][wn + 16 * b + lr] = (float)total[a][b][v];
+            for (int v = 0; v < 4; ++v) tile[16 * a + 4 * lk + v][wn + 16 * b + lr] = (float)(total[a][b][v] * (double)down);
       }
       __syncthreads();
       constexpr int kRows = 4;  // rows of a wavefront in flight
