@@ -220,6 +220,23 @@ def test_grad_in_wide_band(T, B, n_in, n_out, share_out, share_in, spare):
     assert (got[len(r):] == 7.0).all()  # slots without an entry stay as they are
 
 
+@pytest.mark.parametrize("n_out", [1024, 300, 40])
+def test_grad_in_wide_band_errors_have_no_mean(n_out):
+    """The dense product's rounding errors are as often up as down: a mean would add up over the rows of the next
+    dW. Their mean lies within six standard errors."""
+    T, B, n_in = 3, 500, 1024
+    rng = np.random.default_rng(n_out)
+    on_o, g, out, _ = _csr(rng, T, B, n_out, 0.5)
+    on_i, _, inp, _ = _csr(rng, T, B, n_in, 0.95)
+    eps = rng.standard_normal(len(g)).astype(np.float32)
+    W = rng.standard_normal((n_in, n_out)).astype(np.float32)
+    e_in = snn.sparse_grad_in(torch.from_numpy(W).cuda(), 0.5, T, B, out, torch.from_numpy(eps).cuda(), inp)
+    G = np.zeros(on_o.shape)
+    G[on_o] = (eps * g).astype(np.float64)
+    d = e_in.cpu().numpy() - _grad_in_reference(T, B, W, G, 0.5)[on_i]
+    assert abs(d.mean()) <= 6 * d.std() / len(d) ** 0.5, (d.mean(), d.std(), len(d))
+
+
 def test_grad_in_wide_band_past_the_range():
     """Products past float32's range are infinities of the product's sign."""
     T, B, n_in, n_out = 2, 700, 640, 136
