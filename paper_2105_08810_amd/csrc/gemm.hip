@@ -225,9 +225,8 @@ __global__ __launch_bounds__(kThreads, 2) void gemm_split3(int M, int N, int K, 
   clear();
   double total[4][GATHER ? TN : 1][4];
   float up = GATHER && (bt.tm & 1) ? -kUp : kUp;  // A's scale; GATHER: its sign turns with every fold
-  const auto fold = [&]() {
+  const auto fold = [&](double down) {  // the sums times down into the float64 totals
     if constexpr (GATHER) {
-      const double down = up < 0.0f ? -(double)kDown : (double)kDown;
 #pragma unroll
       for (int a = 0; a < 4; ++a)
 #pragma unroll
@@ -236,17 +235,23 @@ __global__ __launch_bounds__(kThreads, 2) void gemm_split3(int M, int N, int K, 
           for (int v = 0; v < 4; ++v)
             total[a][b][v] = fma((double)lead[a][b][v] + (double)rest[a][b][v], down, total[a][b][v]);
       clear();
-      up = -up;
     }
   };
-  if constexpr (GATHER) {
+  const auto fold_scaled = [&]() {
+    fold(up < 0.0f ? -(double)kDown : (double)kDown);
+    if (GATHER) up = -up;
+  };
+  const auto clear_total = [&]() {
+    if constexpr (GATHER) {
 #pragma unroll
-    for (int a = 0; a < 4; ++a)
+      for (int a = 0; a < 4; ++a)
 #pragma unroll
-      for (int b = 0; b < TN; ++b)
+        for (int b = 0; b < TN; ++b)
 #pragma unroll
-        for (int v = 0; v < 4; ++v) total[a][b][v] = 0.0;
-  }
+          for (int v = 0; v < 4; ++v) total[a][b][v] = 0.0;
+    }
+  };
+  clear_total();
 
   float xa[2][8], xb[BN / 64][8];
   if (k_lo < k_hi) {
@@ -282,10 +287,10 @@ __global__ __launch_bounds__(kThreads, 2) void gemm_split3(int M, int N, int K, 
           acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(fa[kTerm[t][0]][a], fb[kTerm[t][1]], acc, 0, 0, 0);
         }
     }
-    if (GATHER && ++stage % kFold == 0) fold();
+    if (GATHER && ++stage % kFold == 0) fold_scaled();
     __syncthreads();
   }
-  fold();
+  fold_scaled();
   float down = kDown;
   // a sum that is not finite (a value or products out of the split's range, in several terms perhaps as opposite
   // infinities; or a NaN of the operands): the same sums in float32
@@ -303,6 +308,7 @@ __global__ __launch_bounds__(kThreads, 2) void gemm_split3(int M, int N, int K, 
     WideStage<kBM>& Aw = *reinterpret_cast<WideStage<kBM>*>(&As);
     WideStage<BN>& Bw = *reinterpret_cast<WideStage<BN>*>(&Bs);
     clear();
+    clear_total();
     down = 1.0f;
     for (int k0 = k_lo; k0 < k_hi; k0 += kBK) {
       load_stage<KM, VEC, kBM>(A, lda, m0, M, k0, k_hi, xa);
@@ -317,15 +323,8 @@ __global__ __launch_bounds__(kThreads, 2) void gemm_split3(int M, int N, int K, 
           for (int b = 0; b < TN; ++b)
             lead[a][b] = __builtin_amdgcn_mfma_f32_16x16x4f32(Aw.x[k + lk][wm + 16 * a + lr],
                                                              Bw.x[k + lk][wn + 16 * b + lr], lead[a][b], 0, 0, 0);
+      fold(1.0);  // after every stage: float32 products are rounded into the running sum one by one
       __syncthreads();
-    }
-    if constexpr (GATHER) {
-#pragma unroll
-      for (int a = 0; a < 4; ++a)
-#pragma unroll
-        for (int b = 0; b < TN; ++b)
-#pragma unroll
-          for (int v = 0; v < 4; ++v) total[a][b][v] = (double)lead[a][b][v];
     }
   }
 

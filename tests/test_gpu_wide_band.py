@@ -237,6 +237,31 @@ def test_grad_in_wide_band_errors_have_no_mean(n_out):
     assert abs(d.mean()) <= 6 * d.std() / len(d) ** 0.5, (d.mean(), d.std(), len(d))
 
 
+@pytest.mark.parametrize("big", [3e33, -2e38])  # past the split's range; past it unscaled too
+def test_grad_in_wide_band_values_past_the_split(big):
+    """A weight too large for the dense product's bf16 parts: its tiles (64 inputs) are formed from float32 operands,
+    the other entries in them no less precisely than entry by entry."""
+    T, B, n_in, n_out = 2, 700, 256, 1024
+    rng = np.random.default_rng(17)
+    on_o, g, out, _ = _csr(rng, T, B, n_out, 0.3)
+    on_i, _, inp, _ = _csr(rng, T, B, n_in, 1.0)
+    eps = (rng.standard_normal(len(g)) * 1e-3).astype(np.float32)
+    W = rng.standard_normal((n_in, n_out)).astype(np.float32)
+    W[70, 500], W[200, 3] = big, big  # in the second tile and the fourth
+    dev = lambda x: torch.from_numpy(x).cuda()
+    run = lambda ws: snn.sparse_grad_in(dev(W), 0.5, T, B, out, dev(eps), inp, ws=ws).cpu().numpy().astype(np.float64)
+    got, walk = run(None), run(snn.workspace(snn.snn_sparse_grad_in_workspace(T, B, n_out)))
+    G = np.zeros(on_o.shape)
+    G[on_o] = (eps * g).astype(np.float64)
+    r, a = (_grad_in_reference(T, B, x, y, 0.5)[on_i] for x, y in ((W, G), (np.abs(W), np.abs(G))))
+    assert (np.abs(got - r) <= 50 * U * a).all()
+    i = np.nonzero(on_i)[1]
+    other = (i // 64 % 2 == 1) & (i != 70) & (i != 200) & (a > 0)
+    rms = lambda x: np.sqrt(np.mean((x - r)[other] ** 2))
+    print("float32 tiles", rms(got), "entry by entry", rms(walk))
+    assert rms(got) <= rms(walk)
+
+
 def test_grad_in_wide_band_past_the_range():
     """Products past float32's range are infinities of the product's sign."""
     T, B, n_in, n_out = 2, 700, 640, 136
