@@ -227,6 +227,15 @@ snn_status snn_sparse_backward(const float* W, const float* trace_in, int T, int
  */
 size_t snn_sparse_dw_workspace(int T, int B, int N_in, int N_out, int64_t out_cap);
 size_t snn_sparse_dw_workspace_full(int T, int B, int N_in, int N_out, int64_t out_cap);
+/*
+ * The entry counts (row_ptr[T*B]) from which calls with a full workspace take a way of wide bands:
+ * dW by columns (up to the dense product's count) and as a dense product, by the output side's
+ * count, and the spike gradient as a dense product, by the input side's. INT64_MAX: never (a count
+ * may also lie above the layer's slots). Layers of 512 to 1024 outputs and N_in a multiple of 4
+ * keep to the matrix-core kernel of narrow bands while out_cap is at most 10% of T*B*N_out.
+ */
+snn_status snn_sparse_ways(int T, int B, int N_in, int N_out, int64_t* dw_columns, int64_t* dw_dense,
+                           int64_t* grad_in_dense);
 snn_status snn_sparse_dw(const float* trace_in, int T, int B, int N_in, int N_out,
                          const int32_t* out_row_ptr, const int32_t* out_col_idx, const float* out_g,
                          const float* eps_out, int64_t out_cap, float* dW, void* workspace,

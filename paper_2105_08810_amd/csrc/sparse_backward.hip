@@ -696,31 +696,40 @@ __global__ __launch_bounds__(kDenseWaves * kWave) void csr_dense_g(int TB, int N
 
 // The dense product's plan, and the entries from which the columns kernel and the dense product are the faster way.
 // Entry by entry: 15 us and 3.05e12 multiply-adds a second (the float64 LDS atomics; 1024 -> 1024, 12% active: 5.3
-// ms; 2312 -> 200: 1.43), fewer in a small layer (700 -> 400 at 600 rows 1.05e12, 784 -> 200 at 6400 2.2e12). By columns: cols_seconds. The product: 32e12 a second in whole rounds of 128 x 128 tiles,
-// 1.3 ps per slot for writing G and 15 us of launches.
+// ms), fewer in a small layer (700 -> 400 at 600 rows 1.05e12, 784 -> 200 at 6400 2.2e12). By columns: cols_seconds.
+// The product: 32e12 a second in whole rounds of 128 x 128 tiles, 1.3 ps per slot for writing G and 15 us of launches.
 struct DenseDwPlan {
-  int splits;
-  int64_t cols_least, least;
+  int splits = 1;
+  int64_t cols_least = INT64_MAX, least = INT64_MAX;
 };
 
-DenseDwPlan plan_dw_dense(int T, int B, int N_in, int N_out) {
+// INT64_MAX twice where neither way can be reached with out_cap entries, which is told without a search over the K
+// slices (the product takes no less than its multiply-adds at the full rate): 0.1 against 1.4 us of host time, for
+// calls at narrow bands.
+DenseDwPlan plan_dw_dense(int T, int B, int N_in, int N_out, int64_t out_cap) {
   DenseDwPlan p{};
   const double TB = (double)T * B;
+  const double entry_s = (double)N_in / 3.05e12 * (1.0 + std::min(2.0, 3.2e8 / (TB * N_in * N_out)));  // per entry
+  const auto dense_time = [&](double product_s) { return 1.03 * (product_s + TB * N_out * 1.3e-12 + 15e-6); };
+  const auto dense_least = [&](double dense_s) { return (int64_t)(std::max(0.0, dense_s - 15e-6) / entry_s) + 1; };
+  // time by columns = fixed + per_entry * entries
+  const bool cols = cols_fits(N_out);
+  double fixed = 0.0, per_entry = 0.0, lo = 0.0;
+  if (cols) {
+    cols_seconds(T, B, N_in, N_out, &fixed, &per_entry);
+    lo = std::max(0.0, 1.05 * fixed - 15e-6) / (entry_s - std::min(per_entry, 0.9 * entry_s));
+  }
+  if ((!cols || out_cap <= (int64_t)lo) && out_cap < dense_least(dense_time(TB * N_in * N_out / 32e12))) return p;
   const SplitPlan q = plan_splits(N_in, N_out, T * B, 32e12);
   p.splits = q.splits;
-  const double dense_s = 1.03 * (q.seconds + TB * N_out * 1.3e-12 + 15e-6);
-  const double entry_s = (double)N_in / 3.05e12 * (1.0 + std::min(2.0, 3.2e8 / (TB * N_in * N_out)));  // per entry
-  p.least = (int64_t)(std::max(0.0, dense_s - 15e-6) / entry_s) + 1;
-  p.cols_least = p.least;
-  if (!cols_fits(N_out)) return p;
-  // time by columns = fixed + per_entry * entries
-  double fixed, per_entry;
-  cols_seconds(T, B, N_in, N_out, &fixed, &per_entry);
-  const double lo = std::max(0.0, 1.05 * fixed - 15e-6) / (entry_s - std::min(per_entry, 0.9 * entry_s));
-  const double hi = (dense_s - fixed) / per_entry;
-  if (lo < hi) {
-    p.cols_least = (int64_t)lo + 1;
-    p.least = std::max((int64_t)hi, p.cols_least) + 1;
+  const double dense_s = dense_time(q.seconds);
+  p.cols_least = p.least = dense_least(dense_s);
+  if (cols) {
+    const double hi = (dense_s - fixed) / per_entry;
+    if (lo < hi) {
+      p.cols_least = (int64_t)lo + 1;
+      p.least = std::max((int64_t)hi, p.cols_least) + 1;
+    }
   }
   return p;
 }
@@ -736,7 +745,7 @@ struct DwWays {
 DwWays plan_dw_ways(int T, int B, int N_in, int N_out, int64_t out_cap) {
   DwWays q{};
   if (N_out <= 32) return q;
-  q.plan = plan_dw_dense(T, B, N_in, N_out);
+  q.plan = plan_dw_dense(T, B, N_in, N_out, out_cap);
   q.cols = q.plan.cols_least < q.plan.least && out_cap >= q.plan.cols_least;
   q.dense = out_cap >= q.plan.least;
   if (q.dense) {
@@ -1855,6 +1864,18 @@ extern "C" size_t snn_sparse_dw_workspace(int T, int B, int N_in, int N_out, int
 extern "C" size_t snn_sparse_dw_workspace_full(int T, int B, int N_in, int N_out, int64_t out_cap) {
   if (!dims_ok(T, B, N_in, N_out) || out_cap < 0) return 0;
   return dw_workspace_full(T, B, N_in, N_out, out_cap);
+}
+
+extern "C" snn_status snn_sparse_ways(int T, int B, int N_in, int N_out, int64_t* dw_columns, int64_t* dw_dense,
+                                      int64_t* grad_in_dense) {
+  if (!dims_ok(T, B, N_in, N_out) || !dw_columns || !dw_dense || !grad_in_dense) return SNN_ERR_INVALID_ARG;
+  *dw_columns = *dw_dense = *grad_in_dense = INT64_MAX;
+  if (N_out <= kNarrowOut) return SNN_OK;
+  const DenseDwPlan p = plan_dw_dense(T, B, N_in, N_out, INT64_MAX);
+  if (p.cols_least < p.least) *dw_columns = p.cols_least;
+  *dw_dense = p.least;
+  *grad_in_dense = gin_dense_least(T, B, N_in, N_out);
+  return SNN_OK;
 }
 
 extern "C" snn_status snn_sparse_dw(const float* trace_in, int T, int B, int N_in, int N_out,

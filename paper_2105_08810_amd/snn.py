@@ -44,6 +44,7 @@ _SIGNATURES = {
     "snn_active_compact_bits_noalloc": (_I, [_P, _P, _I, _I, _I, _F, _F, _P, _P, _P, _I64, _P, _P]),
     "snn_sparse_dw_workspace": (_SZ, [_I, _I, _I, _I, _I64]),
     "snn_sparse_dw_workspace_full": (_SZ, [_I, _I, _I, _I, _I64]),
+    "snn_sparse_ways": (_I, [_I, _I, _I, _I, _P, _P, _P]),
     "snn_sparse_dw": (_I, [_P, _I, _I, _I, _I, _P, _P, _P, _P, _I64, _P, _P, _SZ, _P]),
     "snn_sparse_dw_layout": (_I, [_I, _I, _I, _I, _P, _P, _I64, _P, _SZ, _P]),
     "snn_sparse_dw_prepared": (_I, [_P, _I, _I, _I, _I, _P, _P, _P, _P, _I64, _P, _P, _SZ, _P]),
@@ -224,6 +225,14 @@ def snn_sparse_backward(W, trace_in, T, B, N_in, N_out, alpha, out_row_ptr, out_
 
 def snn_sparse_dw_workspace(T, B, N_in, N_out, out_cap) -> int:
     return int(lib().snn_sparse_dw_workspace(T, B, N_in, N_out, int(out_cap)))
+
+
+def snn_sparse_ways(T, B, N_in, N_out):
+    """Entry counts from which dW goes by columns, dW as a dense product, the spike gradient as one."""
+    n = (ctypes.c_int64 * 3)()
+    p = [ctypes.addressof(n) + 8 * k for k in range(3)]
+    _check("snn_sparse_ways", lib().snn_sparse_ways(T, B, N_in, N_out, *p))
+    return tuple(n)
 
 
 def snn_sparse_dw_workspace_full(T, B, N_in, N_out, out_cap) -> int:

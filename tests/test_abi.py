@@ -259,6 +259,35 @@ def test_least_workspace_does_not_depend_on_the_capacity(lib, T, B, n_in, n_out)
     assert lib.snn_sparse_dw_workspace_full(T, B, n_in, n_out, -1) == 0
 
 
+@pytest.mark.parametrize("T,B,n_in,n_out", [(30, 37, 900, 130), (60, 10, 700, 400), (64, 100, 2312, 200),
+                                            (500, 256, 1024, 300), (8, 40, 600, 4096), (100, 256, 784, 200),
+                                            (10, 160, 4000, 2999), (20, 4, 64, 33)])
+def test_full_workspace_starts_at_the_ways_counts(lib, T, B, n_in, n_out):
+    """The room for sums by column and for the dense product is asked for from exactly the counts that
+    snn_sparse_ways states (below them no way of wide bands is planned)."""
+    cols, dense, gin = snn.snn_sparse_ways(T, B, n_in, n_out)
+    assert min(cols, dense) > 1 and gin > 1
+    query = lambda cap: (lib.snn_sparse_dw_workspace_full(T, B, n_in, n_out, cap),
+                         lib.snn_sparse_dw_workspace(T, B, n_in, n_out, cap))
+    first = min(cols, dense)
+    for cap in (0, 1, first // 7, first // 2, first - 1):
+        assert query(cap)[0] == query(cap)[1]
+    whole = 4 * T * B * n_out  # G
+    if first <= T * B * n_out:
+        full, least = query(first)
+        assert full >= (8 * first if cols < dense else whole) and full >= least
+    if dense <= T * B * n_out:
+        assert query(dense)[0] >= whole
+    room = lambda cap: (lib.snn_sparse_grad_in_workspace_full(T, B, n_in, n_out, cap)
+                        - lib.snn_sparse_grad_in_workspace(T, B, n_out))
+    assert room(gin - 1) < 256 and room(gin) >= whole  # delta
+    assert snn.snn_sparse_ways(T, B, n_in, 32) == (2 ** 63 - 1,) * 3
+    n = (ctypes.c_int64 * 1)()
+    a = ctypes.addressof(n)
+    assert lib.snn_sparse_ways(T, 0, n_in, n_out, a, a, a) == snn.SNN_ERR_INVALID_ARG
+    assert lib.snn_sparse_ways(T, B, n_in, n_out, a, a, None) == snn.SNN_ERR_INVALID_ARG
+
+
 def test_split_workspaces(lib):
     dw = lib.snn_sparse_dw_workspace(500, 256, 1024, 1024, 10 ** 6)
     gi = lib.snn_sparse_grad_in_workspace(500, 256, 1024)
