@@ -1,5 +1,5 @@
-"""Layers with many active entries: the dense products taken from a device-side count on, on both sides
-of it, against float64."""
+"""Layers with many active entries: the ways taken from a device-side count on (dW by columns and as a dense
+product, the spike gradient as one), on both sides of it, against float64. Each case states its way."""
 import numpy as np
 import pytest
 import torch
@@ -26,24 +26,40 @@ def _csr(rng, T, B, N, share, spare=0, with_g=True):
     return on, g if with_g else np.ones(n, np.float32), csr, pad
 
 
-# least: the count from which the dense product runs, which shares bracket (600 rows, 700 -> 400: 1.4e5)
-@pytest.mark.parametrize("T,B,n_in,n_out,share,spare,with_g", [
-    (60, 10, 700, 400, 0.9, 0, True),        # dense product, slab layer
-    (60, 10, 700, 400, 0.3, 150000, True),   # room for it, entry by entry
-    (30, 21, 701, 403, 0.95, 1000, True),    # rows of no whole 16 bytes
-    (30, 37, 900, 130, 0.97, 0, False),      # rows kernel's layer, no g
-    (30, 37, 900, 130, 0.4, 90000, True),
-    (40, 20, 1300, 300, 0.8, 7, True),
-    (5, 120, 130, 1100, 1.0, 0, True),
-    (64, 100, 2312, 200, 0.15, 0, True),     # by columns: a last input tile of 8, two column groups, several chunks
-    (61, 105, 2309, 203, 0.15, 500, True),   # rows of no whole 16 bytes, a last window of five rows
-    (64, 100, 1900, 700, 0.11, 0, False),    # six column groups, the last in part, no g
-    (10, 160, 4000, 2999, 0.1, 0, True),     # one chunk
-    (8, 40, 600, 4096, 0.9, 0, True),        # the widest layer the call takes: a block's rows fill 64 KB of LDS
+def _dw_way(T, B, n_in, n_out, csr):
+    """The way that snn_sparse_dw takes with a full workspace (layers that the matrix-core kernel of narrow bands
+    does not take)."""
+    cols, dense, _ = snn.snn_sparse_ways(T, B, n_in, n_out)
+    n = min(int(csr.row_ptr[-1]), csr.capacity)
+    assert csr.capacity >= min(cols, dense)  # the choice is made on the device
+    return "product" if n >= dense else "columns" if n >= cols else "entries"
+
+
+def _grad_in_way(T, B, n_in, n_out, inp):
+    least = snn.snn_sparse_ways(T, B, n_in, n_out)[2]
+    assert inp.capacity >= least
+    return "product" if min(int(inp.row_ptr[-1]), inp.capacity) >= least else "entries"
+
+
+@pytest.mark.parametrize("T,B,n_in,n_out,share,spare,with_g,way", [
+    (60, 10, 700, 400, 0.9, 0, True, "product"),        # slab layer
+    (60, 10, 700, 400, 0.3, 150000, True, "entries"),   # with room for the product
+    (30, 21, 701, 403, 0.95, 1000, True, "product"),    # rows of no whole 16 bytes
+    (30, 37, 900, 130, 0.97, 0, False, "product"),      # rows kernel's layer, no g
+    (30, 37, 900, 130, 0.4, 90000, True, "entries"),
+    (40, 20, 1300, 300, 0.8, 7, True, "product"),
+    (5, 120, 130, 1100, 1.0, 0, True, "product"),
+    (64, 100, 2312, 200, 0.15, 0, True, "columns"),     # a last input tile of 8, two column groups, several chunks
+    (61, 105, 2309, 203, 0.15, 500, True, "columns"),   # rows of no whole 16 bytes, a last window of five rows
+    (64, 100, 2312, 200, 0.05, 300000, True, "entries"),
+    (64, 100, 1900, 700, 0.11, 0, False, "columns"),    # six column groups, the last in part, no g
+    (10, 160, 4000, 2999, 0.1, 0, True, "columns"),     # one chunk
+    (8, 40, 600, 4096, 0.9, 0, True, "product"),        # the widest layer: a block's rows fill 64 KB of LDS
 ])
-def test_dw_wide_band(T, B, n_in, n_out, share, spare, with_g):
+def test_dw_wide_band(T, B, n_in, n_out, share, spare, with_g, way):
     rng = np.random.default_rng(n_in + n_out)
     on, g, csr, pad = _csr(rng, T, B, n_out, share, spare, with_g)
+    assert _dw_way(T, B, n_in, n_out, csr) == way
     eps = rng.standard_normal(len(g)).astype(np.float32)
     trace = (rng.random((T, B, n_in)) * 2).astype(np.float32)
     dW = snn.sparse_dw(torch.from_numpy(trace).cuda(), csr, torch.from_numpy(pad(eps, np.float32(np.nan))).cuda(), n_out)
@@ -54,13 +70,15 @@ def test_dw_wide_band(T, B, n_in, n_out, share, spare, with_g):
     assert (np.abs(dW.cpu().numpy() - tr.T @ G) <= 4 * U * (tr.T @ np.abs(G))).all()
 
 
-@pytest.mark.parametrize("T,B,n_in,n_out,share", [(60, 10, 700, 400, 0.95), (64, 100, 2312, 200, 0.18)])
-def test_dw_wide_band_truncated(T, B, n_in, n_out, share):
+@pytest.mark.parametrize("T,B,n_in,n_out,share,way", [(60, 10, 700, 400, 0.95, "product"),
+                                                      (64, 100, 2312, 200, 0.18, "columns")])
+def test_dw_wide_band_truncated(T, B, n_in, n_out, share, way):
     """A CSR with more entries than slots: the entries below the capacity count, densely and by columns too."""
     rng = np.random.default_rng(3)
     on, g, csr, _ = _csr(rng, T, B, n_out, share)
     cap = len(g) - 20000
     cut = snn.Csr(csr.row_ptr, csr.col_idx[:cap].contiguous(), csr.g[:cap].contiguous(), csr.nnz_dev, cap)
+    assert _dw_way(T, B, n_in, n_out, cut) == way
     eps = rng.standard_normal(cap).astype(np.float32)
     trace = (rng.random((T, B, n_in)) * 2).astype(np.float32)
     dW = snn.sparse_dw(torch.from_numpy(trace).cuda(), cut, torch.from_numpy(eps).cuda(), n_out)
@@ -81,6 +99,7 @@ def test_dw_wide_band_columns_outside():
     rp = csr.row_ptr.cpu().numpy()
     first, last = int(rp[5]), int(rp[9]) - 1  # the first entry of row 5, the last of row 8
     csr.col_idx[first], csr.col_idx[last] = -3, n_out + 2
+    assert _dw_way(T, B, n_in, n_out, csr) == "columns"
     dW = snn.sparse_dw(torch.from_numpy(trace).cuda(), csr, torch.from_numpy(eps).cuda(), n_out)
     G = np.zeros(on.shape)
     e = (eps * g).astype(np.float64)
@@ -144,6 +163,27 @@ def test_wide_band_workspace_sizes(T, B, n_in, n_out, share, full):
     assert (np.abs(e_in.cpu().numpy() - r) <= 50 * U * a).all()
 
 
+@pytest.mark.parametrize("T,B,n_in,n_out,share,spare,way", [
+    (60, 10, 700, 400, 0.9, 0, "product"), (60, 10, 700, 400, 0.3, 150000, "entries"),
+    (30, 37, 900, 130, 0.97, 0, "product"), (64, 100, 2312, 200, 0.15, 0, "columns"),
+    (64, 100, 2312, 200, 0.05, 300000, "entries")])
+def test_dw_wide_band_layout_then_prepared(T, B, n_in, n_out, share, spare, way):
+    """The layout and then the rest, on the full workspace and on the least, give one call's bits; the layout can be
+    used again with another eps."""
+    rng = np.random.default_rng(n_in)
+    _, g, csr, pad = _csr(rng, T, B, n_out, share, spare)
+    assert _dw_way(T, B, n_in, n_out, csr) == way
+    trace = torch.rand((T, B, n_in), device="cuda")
+    eps = torch.from_numpy(pad(rng.standard_normal(len(g)).astype(np.float32), np.float32(0))).cuda()
+    for query in (snn.snn_sparse_dw_workspace_full, snn.snn_sparse_dw_workspace):
+        n = query(T, B, n_in, n_out, csr.capacity)
+        ws, one = torch.full((n,), 0x5A, dtype=torch.uint8, device="cuda"), snn.workspace(n)[:n]
+        snn.sparse_dw_layout((T, B, n_in), csr, n_out, ws)
+        for e in (eps, 2.0 * eps):
+            assert torch.equal(snn.sparse_dw_prepared(trace, csr, e, n_out, ws),
+                               snn.sparse_dw(trace, csr, e, n_out, ws=one))
+
+
 # one chunk (the records are the workspace's last array), several, and the dense product
 @pytest.mark.parametrize("T,B,n_in,n_out,share", [(10, 160, 4000, 2999, 0.1), (64, 100, 2312, 200, 0.15),
                                                   (60, 10, 700, 400, 0.9)])
@@ -162,6 +202,7 @@ def test_dw_wide_band_malformed_row_pointers(T, B, n_in, n_out, share, kind):
     dev = lambda x: torch.from_numpy(x).cuda()
     col = dev(rng.integers(-1, n_out + 1, cap).astype(np.int32))
     csr = snn.Csr(dev(rp), col, None, None, cap)
+    assert _dw_way(T, B, n_in, n_out, csr) != "entries"
     need = snn.snn_sparse_dw_workspace_full(T, B, n_in, n_out, cap)
     room = torch.full((need + (1 << 22),), 0x5A, dtype=torch.uint8, device="cuda")
     snn.sparse_dw(torch.rand((T, B, n_in), device="cuda"), csr, torch.rand(cap, device="cuda"), n_out, ws=room[:need])
@@ -195,15 +236,17 @@ def _grad_in_reference(T, B, W, G, alpha):
 
 
 # share_in on both sides of the count from which the product runs; output widths at the ends of a K stage
-# and of its 256-wide slices, input widths at a tile's ends, rows that do not fill a tile
-@pytest.mark.parametrize("T,B,n_in,n_out,share_out,share_in,spare", [
-    (30, 20, 900, 300, 0.3, 0.95, 0), (30, 20, 900, 300, 0.3, 0.2, 500000), (129, 5, 1025, 257, 0.1, 0.9, 1000),
-    (3, 427, 640, 256, 0.5, 0.9, 0), (7, 91, 897, 100, 0.9, 1.0, 3), (64, 20, 700, 35, 0.9, 0.95, 0),
-    (2, 300, 1024, 1024, 0.2, 0.9, 0), (11, 61, 1000, 770, 0.02, 0.9, 0)])
-def test_grad_in_wide_band(T, B, n_in, n_out, share_out, share_in, spare):
+# and of the folds of two, input widths at a tile's ends, rows that do not fill a tile
+@pytest.mark.parametrize("T,B,n_in,n_out,share_out,share_in,spare,way", [
+    (30, 20, 900, 300, 0.3, 0.95, 0, "product"), (30, 20, 900, 300, 0.3, 0.2, 500000, "entries"),
+    (129, 5, 1025, 257, 0.1, 0.9, 1000, "product"), (3, 427, 640, 256, 0.5, 0.9, 0, "product"),
+    (7, 91, 897, 100, 0.9, 1.0, 3, "product"), (64, 20, 700, 35, 0.9, 0.95, 0, "product"),
+    (2, 300, 1024, 1024, 0.2, 0.9, 0, "product"), (11, 61, 1000, 770, 0.02, 0.9, 0, "product")])
+def test_grad_in_wide_band(T, B, n_in, n_out, share_out, share_in, spare, way):
     rng = np.random.default_rng(n_in * 7 + n_out)
     on_o, g, out, pad_o = _csr(rng, T, B, n_out, share_out)
     on_i, _, inp, _ = _csr(rng, T, B, n_in, share_in, spare)
+    assert _grad_in_way(T, B, n_in, n_out, inp) == way
     eps = rng.standard_normal(len(g)).astype(np.float32)
     W = rng.standard_normal((n_in, n_out)).astype(np.float32)
     alpha = float(np.float32(np.exp(-0.1)))
@@ -230,6 +273,7 @@ def test_grad_in_wide_band_errors_have_no_mean(n_out):
     on_i, _, inp, _ = _csr(rng, T, B, n_in, 0.95)
     eps = rng.standard_normal(len(g)).astype(np.float32)
     W = rng.standard_normal((n_in, n_out)).astype(np.float32)
+    assert _grad_in_way(T, B, n_in, n_out, inp) == "product"
     e_in = snn.sparse_grad_in(torch.from_numpy(W).cuda(), 0.5, T, B, out, torch.from_numpy(eps).cuda(), inp)
     G = np.zeros(on_o.shape)
     G[on_o] = (eps * g).astype(np.float64)
@@ -249,6 +293,7 @@ def test_grad_in_wide_band_values_past_the_split(big):
     W = rng.standard_normal((n_in, n_out)).astype(np.float32)
     W[70, 500], W[200, 3] = big, big  # in the second tile and the fourth
     dev = lambda x: torch.from_numpy(x).cuda()
+    assert _grad_in_way(T, B, n_in, n_out, inp) == "product"
     run = lambda ws: snn.sparse_grad_in(dev(W), 0.5, T, B, out, dev(eps), inp, ws=ws).cpu().numpy().astype(np.float64)
     got, walk = run(None), run(snn.workspace(snn.snn_sparse_grad_in_workspace(T, B, n_out)))
     G = np.zeros(on_o.shape)
@@ -273,6 +318,7 @@ def test_grad_in_wide_band_past_the_range():
     dev = lambda x: torch.from_numpy(x).cuda()
     out = snn.Csr(dev(rp), dev(j.astype(np.int32)), None, None, B)
     on_i, _, inp, _ = _csr(rng, T, B, n_in, 1.0)
+    assert _grad_in_way(T, B, n_in, n_out, inp) == "product"
     e_in = snn.sparse_grad_in(dev(W), 0.5, T, B, out, dev(eps), inp).cpu().numpy().reshape(T, B, n_in)
     assert np.array_equal(e_in[0], np.sign(eps[:, None] * W[:, j].T.astype(np.float64)) * np.inf)
     assert (e_in[1] == 0).all()
@@ -292,6 +338,7 @@ def test_grad_in_wide_band_truncated_and_columns_outside():
     col[first], col[last] = -3, n_in + 2
     cap = inp.capacity - 5000
     cut = snn.Csr(inp.row_ptr, col[:cap].contiguous(), None, None, cap)
+    assert _grad_in_way(T, B, n_in, n_out, cut) == "product"
     e_in = snn.sparse_grad_in(torch.from_numpy(W).cuda(), 0.9, T, B, out, torch.from_numpy(eps).cuda(), cut)
     G = np.zeros(on_o.shape)
     G[on_o] = (eps * g).astype(np.float64)
