@@ -34,6 +34,17 @@ __device__ __forceinline__ void max_merge(float& v, int& t, float v2, int t2) {
   }
 }
 
+// Classes up to which a thread counts the entries before its own; with more, the sample's keys are sorted (two counts
+// of C steps each took 188 us a call with 1000 classes and 21 ms with 16384, one sample; sorted 27 and 243 us).
+constexpr int kRankMax = 128;
+
+__host__ __device__ inline int sort_slots(int C) {
+  if (C <= kRankMax) return C;
+  int n = 2 * kRankMax;
+  while (n < C) n <<= 1;
+  return n;
+}
+
 // One block per sample b. Thread (tg, c) takes steps tg, tg + TG, ... of class c (classes past the
 // block's width in further rounds); the TG partial results of a class meet in LDS.
 template <int NT>
@@ -42,8 +53,8 @@ __global__ __launch_bounds__(NT) void ce_sample(const float* __restrict__ V, con
                                                 float* __restrict__ dlda, float* __restrict__ loss_b,
                                                 int32_t* __restrict__ cum, int32_t* __restrict__ sorted_c,
                                                 float* __restrict__ sorted_d) {
-  extern __shared__ float a[];                   // [C] logits; later the sorted arg-max steps
-  int* ts = reinterpret_cast<int*>(a + C);       // [C] arg-max steps
+  extern __shared__ float a[];                   // [C] logits
+  int* ts = reinterpret_cast<int*>(a + C);       // arg-max steps [C]; then the sorted keys [sort_slots(C)]
   __shared__ __attribute__((aligned(8))) char part_raw[NT * 8];
   __shared__ float red[NT / kWave];
   float* pv = reinterpret_cast<float*>(part_raw);
@@ -150,33 +161,53 @@ __global__ __launch_bounds__(NT) void ce_sample(const float* __restrict__ V, con
   const bool ok = y >= 0 && y < C;
   const float invB = 1.0f / (float)B;
   if (tid == 0) loss_b[b] = ok ? (logf(Z) - (a[y] - amax)) : NAN;
-  for (int c = tid; c < C; c += NT) {
+  const auto grad = [&](int c) {
     const float p = expf(a[c] - amax) / Z;
-    const float d = (p - (c == y ? 1.0f : 0.0f)) * invB;
-    dlda[(size_t)b * C + c] = d;
-    if (mode == 0) {  // the entry's place among the sample's entries: by step, then class
-      const int t = ts[c];
-      int pos = 0;
-      for (int k = 0; k < C; ++k) pos += ts[k] < t || (ts[k] == t && k < c);
-      sorted_c[(size_t)b * C + pos] = c;
-      sorted_d[(size_t)b * C + pos] = d;
-    }
-  }
+    return (p - (c == y ? 1.0f : 0.0f)) * invB;
+  };
+  for (int c = tid; c < C; c += NT) dlda[(size_t)b * C + c] = grad(c);
   if (mode != 0) return;
-  __syncthreads();  // every logit has been read: a takes the steps in sorted order
-  int* st = reinterpret_cast<int*>(a);
-  for (int c = tid; c < C; c += NT) {
-    const int t = ts[c];
-    int pos = 0;
-    for (int k = 0; k < C; ++k) pos += ts[k] < t || (ts[k] == t && k < c);
-    st[pos] = t;
+  // the sample's entries by step, then class: keys step * C + class (below T * C < 2^31) in order
+  if (C > kRankMax) {
+    int* key = ts;
+    for (int c = tid; c < C; c += NT) key[c] += (C - 1) * key[c] + c;
+    const int n = sort_slots(C);
+    for (int k = C + tid; k < n; k += NT) key[k] = INT_MAX;
+    __syncthreads();
+    for (int run = 2; run <= n; run <<= 1)  // bitonic
+      for (int j = run >> 1; j > 0; j >>= 1) {
+        for (int i = tid; i < n / 2; i += NT) {
+          const int lo = 2 * j * (i / j) + i % j;
+          const int u = key[lo], v = key[lo + j];
+          if ((u > v) == ((lo & run) == 0)) {
+            key[lo] = v;
+            key[lo + j] = u;
+          }
+        }
+        __syncthreads();
+      }
+    for (int k = tid; k < C; k += NT) {
+      const int c = key[k] % C;
+      sorted_c[(size_t)b * C + k] = c;
+      sorted_d[(size_t)b * C + k] = grad(c);
+    }
+  } else {
+    int pos = 0, t = 0;
+    if (tid < C) {  // C <= kRankMax <= NT
+      t = ts[tid];
+      for (int k = 0; k < C; ++k) pos += ts[k] < t || (ts[k] == t && k < tid);
+      sorted_c[(size_t)b * C + pos] = tid;
+      sorted_d[(size_t)b * C + pos] = grad(tid);
+    }
+    __syncthreads();
+    if (tid < C) ts[pos] = t * C + tid;
+    __syncthreads();
   }
-  __syncthreads();
   for (int t = tid; t <= T; t += NT) {  // classes with an arg-max step before t
     int lo = 0, hi = C;
     while (lo < hi) {
       const int mid = (lo + hi) >> 1;
-      if (st[mid] < t) lo = mid + 1; else hi = mid;
+      if (ts[mid] < t * C) lo = mid + 1; else hi = mid;
     }
     cum[(size_t)b * (T + 1) + t] = lo;
   }
@@ -191,9 +222,12 @@ __device__ __forceinline__ void mean_loss(const float* __restrict__ loss_b, int 
   if (lane_id() == 0) *loss = (float)(s / (double)B);
 }
 
-// Row pointers and entries of kRowSteps time steps per block, one thread per sample (mode 0).
+// Row pointers and entries of kRowSteps time steps per block, one thread per sample (mode 0). ALONG (a row holds one
+// entry and more on average): a step's entries of 256 samples are contiguous and the block copies them a thread per
+// entry, which finds its sample by bisection, in gridDim.y shares.
 constexpr int kRowSteps = 4;
 
+template <bool ALONG>
 __global__ __launch_bounds__(kThreads) void ce_rows(const int32_t* __restrict__ cum,
                                                     const int32_t* __restrict__ sorted_c,
                                                     const float* __restrict__ sorted_d,
@@ -201,6 +235,7 @@ __global__ __launch_bounds__(kThreads) void ce_rows(const int32_t* __restrict__ 
                                                     int32_t* __restrict__ row_ptr, int32_t* __restrict__ col_idx,
                                                     float* __restrict__ eps, float* __restrict__ loss) {
   __shared__ int red[kRowSteps][kThreads / kWave];
+  __shared__ int first[ALONG ? kThreads : 1], from[ALONG ? kThreads : 1];
   const int tid = threadIdx.x;
   const int w = tid / kWave;
   const int l = tid % kWave;
@@ -249,8 +284,26 @@ __global__ __launch_bounds__(kThreads) void ce_rows(const int32_t* __restrict__ 
         all += red[q][k];
       }
       const int row = base[q] + before + ex[q];
+      const int begin = base[q];
       base[q] += all;
-      if (b < B && t0 + q < T) {
+      if (ALONG) {
+        if (b < B && t0 + q < T && blockIdx.y == 0) row_ptr[(size_t)(t0 + q) * B + b] = row;
+        __syncthreads();  // first and from are rewritten
+        first[tid] = row;
+        from[tid] = x[q];
+        __syncthreads();
+        for (uint32_t u = begin + blockIdx.y * kThreads + tid; u < (uint32_t)(begin + all); u += gridDim.y * kThreads) {
+          const int e = (int)u;  // (unsigned steps: the last may pass 2^31)
+          int lo = 0, hi = kThreads - 1;  // the last sample that starts at or before e
+          while (lo < hi) {
+            const int mid = (lo + hi + 1) >> 1;
+            if (first[mid] <= e) lo = mid; else hi = mid - 1;
+          }
+          const size_t k = (size_t)(b0 + lo) * C + from[lo] + (e - first[lo]);
+          col_idx[e] = sorted_c[k];
+          eps[e] = sorted_d[k];
+        }
+      } else if (b < B && t0 + q < T) {
         row_ptr[(size_t)(t0 + q) * B + b] = row;
         for (int k = x[q]; k < x[q + 1]; ++k) {
           col_idx[row + k - x[q]] = sorted_c[(size_t)b * C + k];
@@ -259,7 +312,7 @@ __global__ __launch_bounds__(kThreads) void ce_rows(const int32_t* __restrict__ 
       }
     }
   }
-  if (blockIdx.x == 0) {
+  if (blockIdx.x == 0 && blockIdx.y == 0) {
     if (tid == 0) row_ptr[(size_t)T * B] = B * C;
     if (w == 0) mean_loss(loss_b, B, loss);
   }
@@ -337,7 +390,7 @@ extern "C" snn_status snn_readout_ce(const float* V_out, const int32_t* labels, 
     sorted_d = ws.take<float>((size_t)B * C);
   }
   // 1024 threads per sample where a sample holds enough values for them
-  const size_t lds = (size_t)C * (sizeof(float) + sizeof(int));
+  const size_t lds = (size_t)C * sizeof(float) + (size_t)sort_slots(C) * sizeof(int);
   if ((int64_t)T * C >= 8192 || C > kThreads) {
     ensure_dynamic_lds((const void*)ce_sample<1024>, (int)lds);
     hipLaunchKernelGGL(ce_sample<1024>, dim3(B), dim3(1024), lds, s, V_out, labels, T, B, C, mode, tstar, dlda, loss_b,
@@ -347,8 +400,15 @@ extern "C" snn_status snn_readout_ce(const float* V_out, const int32_t* labels, 
                        loss_b, cum, sorted_c, sorted_d);
   }
   if (mode == 0) {
-    hipLaunchKernelGGL(ce_rows, dim3((unsigned)((T + kRowSteps - 1) / kRowSteps)), dim3(kThreads), 0, s, cum, sorted_c,
-                       sorted_d, loss_b, T, B, C, row_ptr, col_idx, eps, loss);
+    const unsigned tb = (unsigned)((T + kRowSteps - 1) / kRowSteps);
+    if (C >= T) {
+      const unsigned shares = (unsigned)std::min<int64_t>(64, ((int64_t)B * C / tb + 16383) / 16384);
+      hipLaunchKernelGGL(ce_rows<true>, dim3(tb, shares), dim3(kThreads), 0, s, cum, sorted_c, sorted_d, loss_b, T, B, C,
+                         row_ptr, col_idx, eps, loss);
+    } else {
+      hipLaunchKernelGGL(ce_rows<false>, dim3(tb), dim3(kThreads), 0, s, cum, sorted_c, sorted_d, loss_b, T, B, C,
+                         row_ptr, col_idx, eps, loss);
+    }
   } else {
     const size_t n = (size_t)T * B * C;
     hipLaunchKernelGGL(ce_fill_sum, dim3((unsigned)std::min<size_t>((n + 255) / 256, 8192)), dim3(256), 0, s, dlda,

@@ -46,7 +46,8 @@ def _reference(V, labels, mode):
 @pytest.mark.parametrize("T,B,C,kind", [
     (1, 1, 1, "normal"), (1, 5, 7, "normal"), (100, 256, 10, "normal"), (37, 300, 4, "ties"), (9, 3, 255, "normal"),
     (33, 2, 257, "ties"), (5, 2, 1025, "normal"), (700, 3, 100, "normal"), (8192, 2, 1, "ties"), (50, 6, 12, "inf"),
-    (50, 6, 12, "nan")])
+    (50, 6, 12, "nan"), (1, 3, 128, "ties"), (1, 300, 130, "normal"), (7, 260, 129, "ties"), (2, 40, 5000, "ties"),
+    (3, 2, 16384, "normal"), (300, 3, 300, "ties"), (1, 1, 16384, "normal")])
 def test_readout_ce(mode, T, B, C, kind):
     rng = np.random.default_rng(T * 1000 + C)
     V = rng.standard_normal((T, B, C)).astype(np.float32)
