@@ -265,32 +265,28 @@ __device__ __forceinline__ void place_window(uint64_t x, int jbase, int64_t pos,
 }
 
 // Places the set bits of a wavefront's windows one window after the other, a lane per column: V is read and
-// the entries are written in whole runs. Lane k holds window x_k (a lane without one: 0), its row's start
-// row0_k in V, its first column jbase_k and its first slot pos_k. For tiles with many bits per window, where
-// place_window's lanes each write a run of their own, 4 bytes at a time: a fill of 35 M entries (27% of
-// 128000 x 1024) with its count 873 -> 321 us.
-constexpr int kGroupAhead = 8;
+// the entries are written in whole runs. Lane k holds window x_k (a lane without one: 0), its first column jbase_k,
+// that column's place in V (at_k) and its first slot pos_k (both below 2^31, as T*B*N is). For tiles with many bits
+// per window, where place_window's lanes each write a run of their own, 4 bytes at a time. Four windows ahead: the
+// scalars of more leave one block per CU (see bits_fill).
+constexpr int kGroupAhead = 4;
 
-__device__ __forceinline__ void place_group(uint64_t x, int64_t row0, int jbase, int64_t pos, int n,
+__device__ __forceinline__ void place_group(uint64_t x, uint32_t at, int jbase, uint32_t pos, int n,
                                             const float* __restrict__ V, float theta, float beta,
                                             int32_t* __restrict__ col_idx, float* __restrict__ g_act, int64_t cap) {
   const int l = lane_id();
-  const auto lane64 = [](int64_t v, int k) {
-    return (int64_t)(((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(v >> 32), k) << 32) |
-                     (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)v, k));
-  };
+  const auto lane32 = [](uint32_t v, int k) { return (uint32_t)__builtin_amdgcn_readlane((int)v, k); };
   for (int k0 = 0; k0 < n; k0 += kGroupAhead) {
     float v[kGroupAhead];
     int j[kGroupAhead];
-    int64_t e[kGroupAhead];
+    uint32_t e[kGroupAhead];
 #pragma unroll
     for (int u = 0; u < kGroupAhead; ++u) {
       const int k = min(k0 + u, kWave - 1);
-      const uint64_t m = k0 + u < n ? (uint64_t)lane64((int64_t)x, k) : 0ull;
-      const int jk = __builtin_amdgcn_readlane(jbase, k) + l;
-      e[u] = lane64(pos, k) + mask_prefix(m);
-      j[u] = (m >> l) & 1ull ? jk : -1;
-      v[u] = (g_act && j[u] >= 0) ? V[lane64(row0, k) + jk] : 0.0f;
+      const uint64_t m = k0 + u < n ? ((uint64_t)lane32((uint32_t)(x >> 32), k) << 32) | lane32((uint32_t)x, k) : 0ull;
+      e[u] = lane32(pos, k) + mask_prefix(m);
+      j[u] = (m >> l) & 1ull ? (int)lane32(jbase, k) + l : -1;
+      v[u] = (g_act && j[u] >= 0) ? V[lane32(at, k) + l] : 0.0f;
     }
 #pragma unroll
     for (int u = 0; u < kGroupAhead; ++u) {
@@ -302,17 +298,23 @@ __device__ __forceinline__ void place_group(uint64_t x, int64_t row0, int jbase,
   }
 }
 
-// Bits per window of a tile from which its windows are placed lane per column. The time of that form hardly
-// depends on the bits (128000 x 1024 slots: 292 us at 8%, 321 at 27%; 25600 x 300: 30 and 31), the other's does
-// (189 and 873; 17 and 39): they meet at 8 bits per window in the first, 12 in the second.
-constexpr int kGroupBits = 10;
+// Bits per window of a tile from which its windows are placed lane per column. The time of that form hardly depends
+// on the bits (a whole compaction of 128000 x 1024 slots: 245 us at 10%, 272 at 27%), the other's does (267 and 1118).
+// They meet at 6 to 7 bits where the fill fills the chip (128000 x 512 and x 1024, 76800 x 200 and x 2312, 25600 x 784
+// and x 4096), at 10 below (25600 x 300) and 12 with few tiles (6400 x 784).
+__device__ __forceinline__ int group_bits(int64_t slots) {
+  return slots >= (12 << 20) ? 7 : (slots >= (6 << 20) ? 10 : 12);
+}
 
 // tr <= kTileThreads * kMaxPerThread rows per tile.
 constexpr int kMaxPerThread = 8;
 
+// Held to 8 wavefronts per SIMD, two blocks per CU: with the scalars of eight windows ahead in place_group only one
+// fitted, and calls with few bits took 42 -> 50 us (1% of 128000 x 1024) and 79 -> 105 us (76800 x 2312), those with
+// 27% 322 against 272 us.
 // ROWS: the row pointers are there already (an earlier call's, over the same bitset) and only the entries are placed.
 template <bool ROWS>
-__global__ __launch_bounds__(kTileThreads) void bits_fill(const uint64_t* __restrict__ bits, const float* __restrict__ V,
+__global__ __launch_bounds__(kTileThreads) __attribute__((amdgpu_waves_per_eu(8))) void bits_fill(const uint64_t* __restrict__ bits, const float* __restrict__ V,
                                                           int T, int B, int N, int tr, int rpw, float theta, float beta,
                                                           const int32_t* __restrict__ counts,
                                                           const int32_t* __restrict__ tile_sum,
@@ -388,7 +390,7 @@ __global__ __launch_bounds__(kTileThreads) void bits_fill(const uint64_t* __rest
   if (cap <= 0) return;
   const int nw = (N + kWave - 1) / kWave;
   const size_t W64 = ((size_t)B * N + kWave - 1) / kWave;
-  const bool grouped = (int64_t)all >= (int64_t)kGroupBits * nw * (t1 - t0);
+  const bool grouped = (int64_t)all >= (int64_t)group_bits((int64_t)rows * N) * nw * (t1 - t0);
   if (grouped && rpw > 1) rpw = min(rpw, (tr + kTileWaves - 1) / kTileWaves);  // every wavefront a share
   for (int r0 = t0 + wv * rpw; r0 < t1; r0 += kTileWaves * rpw) {
     if (rpw > 1) {
@@ -404,7 +406,8 @@ __global__ __launch_bounds__(kTileThreads) void bits_fill(const uint64_t* __rest
       const int bef = first > 0 ? prev : 0;
       const int64_t pos = dst + (in - cw - bef);
       if (grouped)
-        place_group(x, (int64_t)r * N, kWave * w, pos, min(rpw, t1 - r0) * nw, V, theta, beta, col_idx, g_act, cap);
+        place_group(x, (uint32_t)r * N + kWave * w, kWave * w, (uint32_t)pos, min(rpw, t1 - r0) * nw, V, theta, beta,
+                    col_idx, g_act, cap);
       else
         place_window(x, kWave * w, pos, V + (size_t)(ok ? r : 0) * N, theta, beta, col_idx, g_act, cap);
     } else {
@@ -417,8 +420,8 @@ __global__ __launch_bounds__(kTileThreads) void bits_fill(const uint64_t* __rest
         const int cw = __popcll(x);
         const int in = wave_incl_scan(cw);
         if (grouped)
-          place_group(x, (int64_t)r * N, kWave * w, b0 + in - cw, min(kWave, nw - w0), V, theta, beta, col_idx, g_act,
-                      cap);
+          place_group(x, (uint32_t)r * N + kWave * w, kWave * w, (uint32_t)(b0 + in - cw), min(kWave, nw - w0), V, theta,
+                      beta, col_idx, g_act, cap);
         else
           place_window(x, kWave * w, b0 + in - cw, vrow, theta, beta, col_idx, g_act, cap);
         b0 += __shfl(in, kWave - 1, kWave);
