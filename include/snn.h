@@ -409,7 +409,11 @@ snn_status snn_maxpool_spikes(const uint8_t* S, int T, int B, int H, int W, int 
  * layer on them reads as its input trace: trace_pool [T,B,(H/2)*(W/2)*F] float32 (written unless NULL),
  * trace_pool[0] = 0, trace_pool[t+1] = alpha_next*trace_pool[t] + P[t], bit-identical to the trace_in that a
  * forward of that layer writes; alpha_next in (0,1], checked only with trace_pool. All outputs as the two calls'.
+ * snn_conv_forward_pools: 1 where one kernel does all of it (V 8-byte and s_out 2-byte aligned), 0 where pooling and
+ * trace are passes of their own behind the layer; the forward of the next layer then writes the trace beside its own
+ * work, in one launch less.
  */
+int snn_conv_forward_pools(int T, int B, int H, int W, int C, int F);
 snn_status snn_conv_lif_forward_pool(const uint8_t* s_in, const float* Wc, int T, int B, int H, int W, int C, int F,
                                      float alpha, float theta, float b_th, float* V, uint8_t* s_out,
                                      float* trace_in, uint64_t* active_bits, uint8_t* P, uint8_t* arg,

@@ -940,8 +940,14 @@ __global__ __launch_bounds__(kScanThreads) void conv_pool_scan(
   put_spikes(T - 1, sp);
 }
 
-// Whether conv_pool_scan takes the layer (its V and spike stores are 8 and 2 bytes wide).
-bool conv_pool_ok(int H, int W, int C, int F, const float* V, const uint8_t* s_out) {
+// Whether conv_pool_scan takes the layer: shapes and alignments it is written for (its V and spike stores are 8 and
+// 2 bytes wide), and enough wavefronts. It has a quarter of conv_scan's, each step's work is in one of them, and
+// below one per SIMD that step's latency sets the pace: 200 wavefronts, 100 steps 38 us conv_scan, 57 this one, 800
+// 54 and 59, 1156 74 and 67. With the pooling it saves two launches, which outweighs that from half as many on or
+// up to 50 steps (200 wavefronts: 20 steps 34 us in three passes, 27 so; 100 steps 63 and 88; 800: 92 and 94).
+bool conv_pool_ok(int T, int B, int H, int W, int C, int F, bool pool, const float* V, const uint8_t* s_out) {
+  const int64_t waves = (int64_t)B * (H / 2) * (W / 2) * (F / kWave);
+  if (waves < (pool ? 2 : 4) * cu_count() && !(pool && T <= 50)) return false;
   return F % kWave == 0 && (C == 1 || C == 2 || C == 4) && H % 2 == 0 && W % 2 == 0 &&
          (size_t)9 * C * F * sizeof(float) <= kPoolLds && reinterpret_cast<uintptr_t>(V) % 8 == 0 &&
          reinterpret_cast<uintptr_t>(s_out) % 2 == 0;
@@ -1093,7 +1099,7 @@ snn_status conv_forward_impl(const uint8_t* s_in, const float* Wc, int T, int B,
   if (bad_alpha(alpha) || isnan(theta)) return SNN_ERR_INVALID_ARG;
   if (active_bits && (isnan(b_th) || b_th < 0.0f)) return SNN_ERR_INVALID_ARG;
   hipStream_t s = static_cast<hipStream_t>(stream);
-  const bool fused = conv_pool_ok(H, W, C, F, V, s_out);
+  const bool fused = conv_pool_ok(T, B, H, W, C, F, P != nullptr, V, s_out);
   if (fused) {
     launch_conv_pool(s_in, Wc, T, B, H, W, C, F, alpha, theta, b_th, V, s_out, active_bits, P, arg, trace_pool,
                      alpha_next, s);
@@ -1122,6 +1128,11 @@ extern "C" snn_status snn_conv_lif_forward(const uint8_t* s_in, const float* Wc,
                                            float* trace_in, uint64_t* active_bits, void* stream) {
   return conv_forward_impl(s_in, Wc, T, B, H, W, C, F, alpha, theta, b_th, V, s_out, trace_in, active_bits, nullptr,
                            nullptr, nullptr, 1.0f, stream);
+}
+
+extern "C" int snn_conv_forward_pools(int T, int B, int H, int W, int C, int F) {
+  if (bad_dim(T) || bad_dim(B) || bad_dim(H) || bad_dim(W) || bad_dim(C) || bad_dim(F)) return 0;
+  return conv_pool_ok(T, B, H, W, C, F, true, nullptr, nullptr) ? 1 : 0;
 }
 
 extern "C" snn_status snn_conv_lif_forward_pool(const uint8_t* s_in, const float* Wc, int T, int B, int H, int W,

@@ -379,13 +379,14 @@ class ConvNetwork:
         if self.V is None:
             self.allocate()
         T, B, H, W, C, F = self.dims
+        pools = snn.snn_conv_forward_pools(T, B, H, W, C, F)  # else the readout's forward writes the pooled trace
         snn.snn_conv_lif_forward_pool(self.X, self.Wc, T, B, H, W, C, F, self.alpha, self.theta,
                                       0.0 if b_th is None else b_th, self.V, self.S, self.trace,
-                                      None if b_th is None else self.bits, self.P, self.arg, self.trace_out,
-                                      self.alpha_out)
+                                      None if b_th is None else self.bits, self.P, self.arg,
+                                      self.trace_out if pools else None, self.alpha_out)
         self.bits_bth = b_th
         snn.snn_lif_forward(self.P, self.W_out, T, B, self.Np, self.W_out.shape[1], self.alpha_out, INF, self.V_out,
-                            self.S_out, None)
+                            self.S_out, None if pools else self.trace_out)
         return self
 
     def readout(self, dense=False):

@@ -66,6 +66,7 @@ _SIGNATURES = {
     "snn_adam_step": (_I, [_P, _P, _P, _P, _I64, _F, _F, _F, _F, _I, _P]),
     "snn_conv_lif_forward": (_I, [_P, _P, _I, _I, _I, _I, _I, _I, _F, _F, _F, _P, _P, _P, _P, _P]),
     "snn_conv_lif_forward_pool": (_I, [_P, _P, _I, _I, _I, _I, _I, _I, _F, _F, _F, _P, _P, _P, _P, _P, _P, _P, _F, _P]),
+    "snn_conv_forward_pools": (_I, [_I, _I, _I, _I, _I, _I]),
     "snn_maxpool_spikes": (_I, [_P, _I, _I, _I, _I, _I, _P, _P, _P]),
     "snn_pool_route_bits": (_I, [_P, _P, _I, _I, _I, _I, _I, _P, _P]),
     "snn_pool_scatter_eps": (_I, [_I, _I, _I, _I, _I, _P, _P, _I64, _P, _P, _P, _P, _I64, _P, _P]),
@@ -385,6 +386,11 @@ def snn_conv_lif_forward(s_in, Wc, T, B, H, W, C, F, alpha, theta, b_th, V, s_ou
         _ptr(s_in, torch.uint8, "s_in"), _ptr(Wc, torch.float32, "Wc"), T, B, H, W, C, F, float(alpha), float(theta),
         float(b_th), _ptr(V, torch.float32, "V"), _ptr(s_out, torch.uint8, "s_out"),
         _ptr(trace_in, torch.float32, "trace_in"), _ptr(active_bits, torch.int64, "active_bits"), _stream(stream)))
+
+
+def snn_conv_forward_pools(T, B, H, W, C, F) -> bool:
+    """Whether snn_conv_lif_forward_pool is one kernel for these sizes."""
+    return bool(lib().snn_conv_forward_pools(T, B, H, W, C, F))
 
 
 def snn_conv_lif_forward_pool(s_in, Wc, T, B, H, W, C, F, alpha, theta, b_th, V, s_out, trace_in, active_bits, P, arg,

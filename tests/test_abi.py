@@ -288,6 +288,15 @@ def test_full_workspace_starts_at_the_ways_counts(lib, T, B, n_in, n_out):
     assert lib.snn_sparse_ways(T, B, n_in, n_out, a, a, None) == snn.SNN_ERR_INVALID_ARG
 
 
+def test_conv_forward_pools(lib):
+    """One kernel for even maps of 64 filters a group and 1, 2 or 4 channels, with wavefronts enough or steps few."""
+    f = lib.snn_conv_forward_pools
+    assert f(100, 256, 28, 28, 1, 64) == 1 and f(50, 8, 10, 10, 2, 64) == 1
+    assert f(100, 8, 10, 10, 1, 64) == 0  # 200 wavefronts over 100 steps
+    assert f(100, 256, 28, 28, 1, 32) == 0 and f(100, 256, 28, 28, 3, 64) == 0 and f(100, 256, 27, 28, 1, 64) == 0
+    assert f(0, 256, 28, 28, 1, 64) == 0 and f(100, 256, 28, 28, 1, -64) == 0
+
+
 def test_split_workspaces(lib):
     dw = lib.snn_sparse_dw_workspace(500, 256, 1024, 1024, 10 ** 6)
     gi = lib.snn_sparse_grad_in_workspace(500, 256, 1024)

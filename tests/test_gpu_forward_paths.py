@@ -22,10 +22,12 @@ def _same(x, r, what):
 
 
 # steps around a group of eight, one and two filter groups, 1, 2, 4 input channels (one launch), 3 channels and
-# 32 filters (pooling and trace behind the layer); spike bytes that are not 1; a full patch
+# 32 filters (pooling and trace behind the layer); spike bytes that are not 1; a full patch; as many wavefronts as
+# the layer alone needs to go by windows, one less, and few of them over many steps (pooling behind the layer)
 @pytest.mark.parametrize("T,B,H,W,C,Fo,rate,value", [
     (1, 1, 2, 2, 1, 64, 0.5, 1), (2, 3, 4, 2, 1, 64, 0.3, 1), (8, 2, 2, 6, 1, 128, 0.2, 7), (9, 1, 6, 4, 2, 64, 0.2, 1),
-    (10, 2, 4, 4, 4, 64, 0.1, 200), (18, 2, 8, 6, 1, 64, 1.0, 1), (11, 2, 4, 4, 3, 64, 0.2, 1), (9, 2, 4, 4, 1, 32, 0.3, 1)])
+    (10, 2, 4, 4, 4, 64, 0.1, 200), (18, 2, 8, 6, 1, 64, 1.0, 1), (11, 2, 4, 4, 3, 64, 0.2, 1), (9, 2, 4, 4, 1, 32, 0.3, 1),
+    (3, 512, 2, 4, 1, 64, 0.2, 1), (3, 1023, 2, 2, 2, 64, 0.2, 1), (53, 3, 4, 4, 1, 64, 0.2, 1)])
 def test_conv_forward_pool(T, B, H, W, C, Fo, rate, value):
     rng = np.random.default_rng(T * 100 + Fo + C)
     X = (rng.random((T, B, H, W, C)) < rate).astype(np.uint8) * np.uint8(value)
