@@ -186,7 +186,7 @@ snn_status snn_active_compact_bits_noalloc(const uint64_t* active_bits, const fl
  *   Wide bands: with a workspace of snn_sparse_backward_workspace_full the call may also sum dW by
  *   column or as a dense product, and form eps_in by a dense product, where row_ptr[T*B] (read on
  *   the device) says that this is the faster way: from about 4% and 20% of a large layer's T*B*N_out
- *   slots active for dW, 13% of T*B*N_in for eps_in. That workspace depends on out_cap and in_cap for
+ *   slots active for dW, 8 to 16% of T*B*N_in for eps_in. That workspace depends on out_cap and in_cap for
  *   all layers of more than 32 outputs (it holds the entries sorted by column, 8 bytes each, or G,
  *   4 T*B*N_out bytes; and delta, 4 T*B*N_out bytes). With the least size above
  *   every sum goes entry by entry; a size in between may have room for one of these ways.

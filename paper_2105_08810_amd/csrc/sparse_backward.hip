@@ -696,7 +696,8 @@ __global__ __launch_bounds__(kDenseWaves * kWave) void csr_dense_g(int TB, int N
 
 // The dense product's plan, and the entries from which the columns kernel and the dense product are the faster way.
 // Entry by entry: 15 us and 3.05e12 multiply-adds a second (the float64 LDS atomics; 1024 -> 1024, 12% active: 5.3
-// ms), fewer in a small layer (700 -> 400 at 600 rows 1.05e12, 784 -> 200 at 6400 2.2e12). By columns: cols_seconds.
+// ms), 4e12 up to 128 outputs (1000 -> 64 at 25600 rows, 20% active: 117 us, 147 as a product), fewer in a small layer
+// (700 -> 400 at 600 rows 1.05e12, 784 -> 200 at 6400 2.2e12). By columns: cols_seconds.
 // The product: 32e12 a second in whole rounds of 128 x 128 tiles, 1.3 ps per slot for writing G and 15 us of launches.
 struct DenseDwPlan {
   int splits = 1;
@@ -709,7 +710,8 @@ struct DenseDwPlan {
 DenseDwPlan plan_dw_dense(int T, int B, int N_in, int N_out, int64_t out_cap) {
   DenseDwPlan p{};
   const double TB = (double)T * B;
-  const double entry_s = (double)N_in / 3.05e12 * (1.0 + std::min(2.0, 3.2e8 / (TB * N_in * N_out)));  // per entry
+  const double entry_s = (double)N_in / (N_out <= 128 ? 4e12 : 3.05e12) *
+                         (1.0 + std::min(2.0, 3.2e8 / (TB * N_in * N_out)));  // per entry
   const auto dense_time = [&](double product_s) { return 1.03 * (product_s + TB * N_out * 1.3e-12 + 15e-6); };
   const auto dense_least = [&](double dense_s) { return (int64_t)(std::max(0.0, dense_s - 15e-6) / entry_s) + 1; };
   // time by columns = fixed + per_entry * entries
@@ -1483,16 +1485,26 @@ size_t dw_workspace_full(int T, int B, int N_in, int N_out, int64_t out_cap) {
 }
 
 // The spike gradient with many input entries: delta written densely by the walk, then delta W^T on the matrix
-// cores, read at the entries (gemm_split_kc_gather). An entry of the walk costs its W row's gather and dot,
-// measured 163 ps at 1024 outputs and 43 at 100 (26% active); the product runs at 70e12 multiply-adds a second
-// with its gather (N_in padded to 64, N_out to 32), 3 ps per entry and 3 ps per delta element. 3 x 1024 layers at
-// 27% active: 5.5 -> 2.4 ms per layer.
+// cores, read at the entries (gemm_split_kc_gather). The model, within a tenth or so of the times of 26 layers from
+// 160 to 128000 rows, 100 to 2312 inputs and 36 to 4096 outputs:
+//   an entry of the walk costs its W row's gather and dot, 54 ps up to 256 outputs, 59 to 512, 125 to 1024 and 110
+//   per 1024 above (a row is taken in whole registers), in proportion more with too few wavefronts for the chip;
+//   the product runs at 80e12 multiply-adds a second (N_in padded to 64, N_out to 32; 15% longer where rows are no
+//   whole 16 bytes), or 1.4 us per 32 outputs with few tiles; 2.2 ps per padded element of the result, 5 ps per
+//   entry, 0.9 ps per element of delta (4 above 2048 outputs) and 8 us.
+// The times meet between 8% (1024 -> 100 at 128000 rows) and 14% active (700 -> 400 at 25600); the line is taken
+// 5% on the walk's side. 3 x 1024 layers at 27% active: 5.5 -> 2.4 ms per layer.
 int64_t gin_dense_least(int T, int B, int N_in, int N_out) {
-  const double TB = (double)T * B;
-  const double product_s = TB * (64.0 * ((N_in + 63) / 64)) * (32.0 * ((N_out + 31) / 32)) / 70e12 +
-                           TB * N_out * 3e-12 + 15e-6;
-  const double entry_s = N_out * 1.3e-13 + 27e-12;
-  return (int64_t)(1.1 * product_s / entry_s) + 1;
+  const double TB = (double)T * B, in = 64.0 * ((N_in + 63) / 64), stages = (N_out + 31) / 32;
+  const double product_s = std::max(TB * in * 32.0 * stages / 80e12 * (N_out % 4 ? 1.15 : 1.0), stages * 1.4e-6) +
+                           TB * in * 2.2e-12 + TB * N_out * (N_out > 2048 ? 4e-12 : 0.9e-12) + 8e-6;
+  const double full_s = N_out <= 256 ? 54e-12
+                        : N_out <= 512 ? 59e-12
+                        : N_out <= 1024 ? 125e-12
+                                        : 110e-12 * ((N_out + 1023) / 1024);
+  const double waves = (double)plan_walk(T).C * B;
+  const double entry_s = full_s * std::max(1.0, (N_out <= 256 ? 2500.0 : 1500.0) / waves);
+  return (int64_t)(1.05 * product_s / (entry_s - 5e-12)) + 1;
 }
 
 bool gin_dense_possible(int T, int B, int N_in, int N_out, int64_t in_cap) {

@@ -238,7 +238,7 @@ def _grad_in_reference(T, B, W, G, alpha):
 # share_in on both sides of the count from which the product runs; output widths at the ends of a K stage
 # and of the folds of two, input widths at a tile's ends, rows that do not fill a tile
 @pytest.mark.parametrize("T,B,n_in,n_out,share_out,share_in,spare,way", [
-    (30, 20, 900, 300, 0.3, 0.95, 0, "product"), (30, 20, 900, 300, 0.3, 0.2, 500000, "entries"),
+    (30, 20, 900, 300, 0.3, 0.95, 0, "product"), (30, 20, 900, 300, 0.3, 0.1, 500000, "entries"),
     (129, 5, 1025, 257, 0.1, 0.9, 1000, "product"), (3, 427, 640, 256, 0.5, 0.9, 0, "product"),
     (7, 91, 897, 100, 0.9, 1.0, 3, "product"), (64, 20, 700, 35, 0.9, 0.95, 0, "product"),
     (2, 300, 1024, 1024, 0.2, 0.9, 0, "product"), (11, 61, 1000, 770, 0.02, 0.9, 0, "product")])
