@@ -246,12 +246,12 @@ __global__ __launch_bounds__(kRowWaves * kWave) void slab_fill(int TB, int N_out
 // holds inputs 128 it + l and 128 it + 64 + l, so one record read, conversion and address serve
 // two float64 LDS atomics (the second at an immediate offset): on this hardware the VALU work of
 // an atomic adds to its LDS time instead of overlapping it. Blocks of one chunk are numbered so
-// that they land on one XCD and share its L2 lines.
-__global__ __launch_bounds__(kDwThreads) void dw_slab_kernel(const float* __restrict__ trace, int TB, int N_in,
-                                                             int N_out, const int32_t* __restrict__ sp,
-                                                             const SlabRec* __restrict__ rec, int64_t nrec,
-                                                             float* __restrict__ out, int n_chunks,
-                                                             int n_itiles, int n_slabs, int slab, Gate gate) {
+// that they land on one XCD and share its L2 lines. Held to two blocks of 1024 threads per CU (64 VGPRs; with one
+// more a single block fits: 700 -> 400 at 25600 rows 64 -> 75 us).
+__global__ __launch_bounds__(kDwThreads) __attribute__((amdgpu_waves_per_eu(8))) void dw_slab_kernel(
+    const float* __restrict__ trace, int TB, int N_in, int N_out, const int32_t* __restrict__ sp,
+    const SlabRec* __restrict__ rec, int64_t nrec, float* __restrict__ out, int n_chunks, int n_itiles, int n_slabs,
+    int slab, Gate gate) {
   extern __shared__ double acc[];  // [slab][kLd]
   if (!gate_open(gate)) return;
   int id = blockIdx.x;
@@ -281,11 +281,13 @@ __global__ __launch_bounds__(kDwThreads) void dw_slab_kernel(const float* __rest
   // activity lies in time. Wavefront w takes rows [8 w, 8 w + 8) of each of its chunk's groups.
   const int r_hi = TB;
   const int2* rec2 = reinterpret_cast<const int2*>(rec);
+  // last record, as unsigned: the offsets of a malformed CSR may wrap, and negative ones clamp to it too
+  const uint32_t last = (uint32_t)(nrec < INT32_MAX ? nrec - 1 : INT32_MAX - 1);
   // Software pipeline over batches of 8 rows: while a batch is processed, the next batch's
   // trace values and records are in flight and the row pointers of the one after it. Rows past
   // TB read sp[TB] (empty ranges); a row with no entry in this slab reads the batch's first
   // trace row instead of its own (a cache hit, never used).
-  auto load_sp = [&](int rb) { return clamp_entry(spl[min(rb + min(l, kRowsPerBatch), r_hi)], nrec); };
+  auto load_sp = [&](int rb) { return spl[min(rb + min(l, kRowsPerBatch), r_hi)]; };
   auto load_rest = [&](int rb, int spv, float* t0, float* t1, int2& ra) {
 #pragma unroll
     for (int k = 0; k < kRowsPerBatch; ++k) {
@@ -294,7 +296,7 @@ __global__ __launch_bounds__(kDwThreads) void dw_slab_kernel(const float* __rest
       t0[k] = trace[row + ic0];
       t1[k] = trace[row + ic1];
     }
-    ra = rec2[min((int64_t)rdlane(spv, 0) + l, nrec - 1)];  // lane s holds the batch's record s
+    ra = rec2[min((uint32_t)(rdlane(spv, 0) + l), last)];  // lane s holds the batch's record s
   };
   const int kStride = kDwWaves * kRowsPerBatch * n_chunks;
   int rb = c * kDwWaves * kRowsPerBatch + w * kRowsPerBatch;
@@ -333,7 +335,7 @@ __global__ __launch_bounds__(kDwThreads) void dw_slab_kernel(const float* __rest
         const int lo = rdlane(spv, k);
         const int hi = rdlane(spv, k + 1);
         for (int s = lo; s < hi; ++s) {
-          const int2 x = rec2[min((int64_t)s, nrec - 1)];  // clamped: malformed input cannot read past the records
+          const int2 x = rec2[min((uint32_t)s, last)];  // clamped: malformed input cannot read outside the records
           const double G = (double)__int_as_float(x.y);
           double* a = reinterpret_cast<double*>(accb + min(max(x.x, 0), max_off));
           atomicAdd(a, t0 * G);
@@ -527,6 +529,8 @@ __global__ __launch_bounds__(kDwThreads) void dw_slab_spikes_kernel(
   const int b0 = bb * kSamplesPerChunk + w * kRowsPerBatch;
   const int nbv = max(0, min(kRowsPerBatch, B - b0));  // this wavefront's samples
   const int2* rec2 = reinterpret_cast<const int2*>(rec);
+  // last record, as unsigned: the offsets of a malformed CSR may wrap, and negative ones clamp to it too
+  const uint32_t last = (uint32_t)(nrec < INT32_MAX ? nrec - 1 : INT32_MAX - 1);
   float tr0[kRowsPerBatch], tr1[kRowsPerBatch];
 #pragma unroll
   for (int k = 0; k < kRowsPerBatch; ++k) {
@@ -535,8 +539,8 @@ __global__ __launch_bounds__(kDwThreads) void dw_slab_spikes_kernel(
     tr1[k] = ck[row + ic1];
   }
   // lane k <= 8: row pointer of row t B + b0 + min(k, nbv) (rows past the samples: empty ranges)
-  auto load_sp = [&](int t) { return clamp_entry(spl[(size_t)t * B + min(b0, B - 1) + min(l, nbv)], nrec); };
-  auto load_rec = [&](int spv) { return rec2[min((int64_t)rdlane(spv, 0) + l, nrec - 1)]; };
+  auto load_sp = [&](int t) { return spl[(size_t)t * B + min(b0, B - 1) + min(l, nbv)]; };
+  auto load_rec = [&](int spv) { return rec2[min((uint32_t)(rdlane(spv, 0) + l), last)]; };
   auto load_spk = [&](int t, uint32_t* sk) {  // S[t] of the 8 samples at the lane's two inputs
 #pragma unroll
     for (int k = 0; k < kRowsPerBatch; ++k) {
@@ -580,7 +584,7 @@ __global__ __launch_bounds__(kDwThreads) void dw_slab_spikes_kernel(
           const int lo = rdlane(spv, k);
           const int hi = rdlane(spv, k + 1);
           for (int s = lo; s < hi; ++s) {
-            const int2 x = rec2[min((int64_t)s, nrec - 1)];
+            const int2 x = rec2[min((uint32_t)s, last)];
             const double G = (double)__int_as_float(x.y);
             double* a = reinterpret_cast<double*>(accb + min(max(x.x, 0), max_off));
             atomicAdd(a, t0 * G);

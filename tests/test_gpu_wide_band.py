@@ -114,7 +114,7 @@ def test_dw_wide_band_columns_outside():
 def test_dw_rows_that_count_past_32_bits():
     """Rows of a malformed CSR that together hold more than 2^31 entries: the offsets of the slab records wrap, and
     no record is read or written outside the workspace."""
-    T, B, n_in, n_out, cap = 64, 100, 2312, 200, 700000
+    T, B, n_in, n_out, cap = 64, 100, 64, 310, 700000
     rp = torch.zeros(T * B + 1, dtype=torch.int32, device="cuda")
     rp[1::2] = cap  # every second row spans all entries; the count says that there are none
     col = (torch.arange(cap, device="cuda") % n_out).to(torch.int32)
