@@ -63,6 +63,7 @@ def test_grad_difference_matches_oracle():
 def test_roofline_peaks():
     assert bench.HBM_PEAK_GBS == 8000.0
     assert bench.MFMA_F32_TFLOPS == 157.3
+    assert math.isclose(bench.MFMA_SPLIT_TFLOPS * 6, 2500.0)  # bf16
 
 
 def test_forward_bytes_by_hand():
