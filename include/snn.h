@@ -188,8 +188,10 @@ snn_status snn_active_compact_bits_noalloc(const uint64_t* active_bits, const fl
  *   the device) says that this is the faster way: from about 4% and 20% of a large layer's T*B*N_out
  *   slots active for dW, 8 to 16% of T*B*N_in for eps_in. That workspace depends on out_cap and in_cap for
  *   all layers of more than 32 outputs (it holds the entries sorted by column, 8 bytes each, or G,
- *   4 T*B*N_out bytes; and delta, 4 T*B*N_out bytes). With the least size above
- *   every sum goes entry by entry; a size in between may have room for one of these ways.
+ *   4 T*B*N_out bytes; and delta, 4 T*B*N_out bytes). All ways that the capacities allow are
+ *   enqueued, and those not taken cost their launches, 5 to 25 us a call: with capacities far above
+ *   the counts of narrow bands the least size above, with which every sum goes entry by entry, is
+ *   the better one. A size in between may have room for some of these ways.
  *   aux_stream (may be NULL): a second hipStream_t. When given, the spike-gradient part runs on
  *   it beside the dW part on `stream`; the call makes aux_stream wait for the work already on
  *   `stream`, and `stream` wait for the aux work, so work enqueued on `stream` afterwards sees

@@ -479,8 +479,11 @@ __global__ __launch_bounds__(256) void mdw_reduce(const float* __restrict__ part
 // A block's sixteen wavefronts own 64 columns each; below 512 columns more than half of them would
 // idle, and the slab kernels are as fast there (measured at 200, 300 and 400 columns). Above ~10%
 // of the entries active (the capacity is the compaction's count) a window's entries need several
-// record rounds and the lockstep quads cost more than the slab kernel's atomics (stress at 27%
-// active: 67 against 45 ms); the dense chain is the faster one there anyway.
+// record rounds, and sums by column and the dense product, chosen by the count on the device, take
+// those layers with less (1024 -> 1024 at 128000 rows, 11% active: 2.5 ms by columns, 4.3 entry by
+// entry). By columns would lead from below that (8% takes 2.7 ms here, more than 11% by columns),
+// but this line is drawn by the capacity, on the host: further down, a capacity well above the
+// count would send layers at narrow bands to the slab kernels.
 bool mdw_eligible(int T, int B, int N_in, int N_out, int64_t out_cap) {
   if (N_out < kMWaves * kWave / 2 || N_out > kMWaves * kWave || N_in % 4 != 0) return false;
   return (double)out_cap <= 0.1 * (double)T * (double)B * (double)N_out;

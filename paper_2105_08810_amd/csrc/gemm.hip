@@ -15,10 +15,10 @@
 // loaded into registers while the previous one is multiplied, split there and stored to LDS as
 // [part][k / 8][row] pieces of 16 bytes, which the fragment reads (lane = row, 8 consecutive k) take
 // without bank conflicts; two blocks per CU overlap one's split with the other's products. Measured at
-// 128000 x 1024 x 1024: 1.52 ms, 176 TFLOP/s (1056 in bf16 terms; a large bf16 product of the library
-// reaches 1290 on this card), 1.75 ms with the six terms of a tile issued one after another, 1.54 with
-// 32 x 32 x 16 tiles. Error against 64 bits with 16000 products of random sign per sum: 0.8e-6 of the
-// result, float32 MFMA 3.3e-6.
+// 128000 x 1024 x 1024: 1.55 (k down the rows) and 1.46 ms, 173 and 184 TFLOP/s (1040 and 1100 in bf16
+// terms; a large bf16 product of the library reaches 1290 on this card), 1.75 ms with the six terms of
+// a tile issued one after another; tiles of 32 x 32 x 16 are 1% slower. Error against 64 bits with 16000
+// products of random sign per sum: 0.8e-6 of the result, float32 MFMA 3.3e-6.
 #include "common.h"
 
 namespace snn {

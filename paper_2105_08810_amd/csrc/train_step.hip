@@ -112,7 +112,7 @@ __device__ __forceinline__ int count_of(const int32_t* __restrict__ partial, int
 // One block per sample b: counts, the per-sample penalty and the coefficient of every neuron. A thread's first
 // kRegKeep counts stay in registers between the sums and the coefficients (more neurons are counted again).
 // Sums run in float64 in a fixed order, so the results are deterministic. Bound: latency of the partial counts
-// (300 neurons, 28 chunks: 20 -> 4.7 us; two serial passes over the chunks and two 8-step block sums before).
+// (300 neurons, 28 chunks: 20 -> 5.9 us; two serial passes over the chunks and two 8-step block sums before).
 constexpr int kRegKeep = 4;
 
 __global__ void __launch_bounds__(kRegThreads) reg_sample(const int32_t* __restrict__ partial, int chunks, int B,
